@@ -18,7 +18,8 @@ struct GemmCut {
     GemmPlan head, tail;
 };
 
-// 16 rows so far apart that their byte offsets need more than 32 bits
+// 16 rows so far apart that their byte offsets need more than 32 bits: 15 ld and at most 256 columns, 4 bytes each, stay
+// below 2^32 for every ld < 2^26
 inline bool gemm_f32_wide(uint64_t ld) { return ld >= (1ull << 26); }
 
 GemmPlan gemm_f32_plan(bool a_kn, bool b_kn, uint64_t M, uint64_t N, uint64_t K, uint64_t ld_max, bool lower_only,
