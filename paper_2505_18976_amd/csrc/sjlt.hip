@@ -398,7 +398,9 @@ static bool plan_sjlt(uint64_t n, uint64_t d, bool masked, uint32_t k, const voi
         V = force_v;
     } else if (!masked) {
         // rows P apart start at the same offset inside a 128-byte line; group them if there are enough rows
-        const uint32_t period = R == 1 ? 1 : line_period;     // a single row has one alignment, whatever it is
+        // (a launch that is cut with one row per workgroup needs no grouping: a single row has one alignment, whatever it is;
+        // a large one keeps it, its groups set the number of chunks and so the scratch memory below)
+        const uint32_t period = cut && R == 1 ? 1 : line_period;
         if (period == 1 || n >= (uint64_t)period * R) {
             P = period; V = (int)vmax; align_lines = true;
         } else if (aligned(g, 16) && ldg % vmax == 0) V = (int)vmax;

@@ -123,6 +123,16 @@ def test_noalloc_entry_point_refuses_oversized_problems_on_the_host(lib):
     assert lib.grass_sjlt_noalloc(fake, 4, 100, 100, null, 0, 16, 3, 0, 1, fake, 16, null) == b.GRASS_EINVAL  # s does not divide k
 
 
+@pytest.mark.parametrize("n,p,k,s", [(1012, 2149742, 12077, 1), (1022, 17608759, 12864, 4), (1000, 3000001, 16384, 1)])
+def test_batches_that_fill_the_chip_in_groups_need_no_scratch(lib, n, p, k, s):
+    """About a thousand rows of odd length, one per workgroup: grouped by their offset inside a line they make 1,024 groups,
+    one chunk and no partial sums, so the entry point with the fixed buffer takes them (two chunks would need 97 MB)."""
+    from paper_2505_18976_amd import binding as b
+    text = ctypes.create_string_buffer(200)
+    assert lib.grass_sjlt_describe(None, 0, n, p, p, 0, k, s, 1, None, text, 200) == b.GRASS_OK
+    assert " chunks=1 " in text.value.decode()
+
+
 def test_tuning_is_a_per_call_argument(lib):
     """Launch-shape overrides travel with the call: the same query with and without them, interleaved, keeps
     answering the same (there is no process-wide setting to leak from one call into the next)."""
