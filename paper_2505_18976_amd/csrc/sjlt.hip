@@ -343,9 +343,9 @@ static uint64_t chunk_limit(uint64_t n, uint64_t d, bool masked) {
 // Measured against the rule before it, which always filled LDS with rows: 64 x 8,192 kept of 65,536 to 1,024: 12.9 -> 8.9
 // us; 301 bf16 rows, 40,001 kept of 1.86 M, s = 4: 157 -> 145; 200 rows of 11.2 M: 1,667 -> 1,553; 376 rows of 3.3 M, s = 4:
 // 3,322 -> 2,752; 300 bf16 rows of 4,000,001 (rows on any 2-byte boundary): 2,583 -> 675.
-// Large batches (row groups for two or more rounds of workgroups: a masked batch of 1,024 groups, an unmasked one of 512
-// whose rows can be grouped by line offset) share the hash of a position between up to 8 rows; everything else keeps one
-// row per workgroup, or two where hashing is what bounds it, and is cut by pick_chunks.
+// Large batches (row groups for two or more rounds of workgroups: a masked batch of 1,024 groups, an unmasked one of 512,
+// which always has enough rows to group them by line offset) share the hash of a position between up to 8 rows; everything
+// else keeps one row per workgroup, or two where hashing is what bounds it, and is cut by pick_chunks.
 static bool plan_sjlt(uint64_t n, uint64_t d, bool masked, uint32_t k, const void* g, uint64_t ldg, SjltPlan* pl, int force_v,
                       uint32_t in_bytes, uint32_t s, const grass_tuning* tune, uint64_t p, size_t max_ws = ~(size_t)0) {
     // launch-shape overrides of this call (experiments); zero = heuristic
@@ -377,7 +377,7 @@ static bool plan_sjlt(uint64_t n, uint64_t d, bool masked, uint32_t k, const voi
     uint32_t gcd = E;                                         // gcd(ld mod E, E); E when ld mod E == 0
     while ((uint32_t)(ldg % E) % gcd != 0) gcd >>= 1;
     const uint32_t line_period = E / gcd;                     // rows that far apart start at the same offset inside a line
-    const bool large = masked ? ceil_div(n, R) >= 1024 : ceil_div(n, R) >= 512 && (force_v != 0 || n >= 4ull * line_period * R);
+    const bool large = ceil_div(n, R) >= (masked ? 1024 : 512);
     const bool tuned = tune_rows || tune_chunks || tune_threads || tune_acc;
     const bool cut = !large && !tuned;
     if (cut && force_v == 0) {
@@ -547,11 +547,6 @@ extern "C" grass_status grass_sjlt_workspace_bytes(uint64_t n, uint64_t p, uint3
         if (!plan_sjlt(n, masked ? kprime_or_0 : p, masked, k, nullptr, 0, &pl, v, 4, s, host_tuning, p)) return GRASS_EUNSUPPORTED;
         const size_t need = pl.table ? pl.table_offset + pl.table_bytes : pl.ws_bytes;
         if (need > worst) worst = need;
-        // unmasked batches that would be large enough to share hashes may still have rows that cannot be grouped
-        const uint64_t limit = masked || host_tuning ? 1 : chunk_limit(n, p, false);
-        size_t cut = limit > 1 ? (size_t)limit * n * k * 4 : 0;
-        if (cut && pl.table) cut = (cut + 255) / 256 * 256 + pl.table_bytes;
-        if (cut > worst) worst = cut;
     }
     *host_bytes = worst;
     return GRASS_OK;

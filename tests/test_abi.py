@@ -133,6 +133,15 @@ def test_batches_that_fill_the_chip_in_groups_need_no_scratch(lib, n, p, k, s):
     assert " chunks=1 " in text.value.decode()
 
 
+@pytest.mark.parametrize("n,chunks", [(600, 2), (511, 4), (1100, 0)])
+def test_sjlt_query_reserves_what_the_call_can_use(lib, n, chunks):
+    """511 rows of k = 16,384 are cut into up to four chunks; from 512 on a batch is large and has two at most, from 1,024
+    on one and no partial sums."""
+    out = ctypes.c_size_t(0)
+    assert lib.grass_sjlt_workspace_bytes(n, 2_000_000, 0, 16_384, 4, None, ctypes.byref(out)) == 0
+    assert out.value == chunks * n * 16_384 * 4
+
+
 def test_tuning_is_a_per_call_argument(lib):
     """Launch-shape overrides travel with the call: the same query with and without them, interleaved, keeps
     answering the same (there is no process-wide setting to leak from one call into the next)."""
