@@ -309,25 +309,45 @@ struct SjltPlan {
 // Column chunks of a launch without enough row groups to fill the chip several times over.  Workgroups of 1,024 threads
 // run two to a CU (LDS permitting), 512 at a time; one that has its CU to itself takes `us_per_pos` for a position, two
 // take twice that each; starting and draining one costs about a microsecond plus 0.4 per 1,000 sums; cutting rows costs
-// a second launch and the traffic of the partial sums.  Fitted to 422 drawn shapes measured with every combination of 1
-// to 8 rows and 1 to 96 chunks per workgroup: the choice is within 4 % of the best combination on average, where the rule
-// before it (8 rows per workgroup if LDS holds them, 4 rounds of workgroups) was 63 % (plain) and 22 % (masked) behind.
+// a second launch and the traffic of the partial sums.  Nothing is gained below the time that the host needs for the call:
+// 8.5 us, 12 with the second launch and its workspace.
 static uint32_t pick_chunks(uint64_t groups, uint64_t n, uint64_t d, uint64_t step, int R, uint32_t k, size_t lds_bytes,
-                            double us_per_pos, uint64_t max_chunks) {
+                            double us_per_pos, uint64_t max_chunks, double* est_us) {
     const uint64_t slots = (lds_bytes * 2 <= kLdsBytes ? 2 : 1) * (uint64_t)kNumCU;
     const double start = 0.95 + 0.4e-3 * R * k;
-    uint32_t best = 1;
+    uint64_t best = 1, last = 0;
     double best_us = 0.0;
-    for (uint64_t c = 1; c <= max_chunks; c += c < 16 ? 1 : c < 32 ? 4 : 8) {
-        const uint64_t len = ceil_div(ceil_div(d, c), step) * step, seg = len < d ? len : d;
-        if (c > 1 && ceil_div(d, len) != c) continue;          // the same chunks as a smaller c
+    for (uint64_t q = 1; q <= max_chunks; q += q < 16 ? 1 : q < 32 ? 4 : 8) {
+        const uint64_t len = ceil_div(ceil_div(d, q), step) * step, seg = len < d ? len : d;
+        const uint64_t c = ceil_div(d, len);                   // whole steps: often fewer chunks than asked for
+        if (c == last) continue;
+        last = c;
         const uint64_t wgs = groups * c, rest = wgs % slots;
-        const double us = (double)(wgs / slots) * (start + (double)seg * us_per_pos * (double)(slots / kNumCU)) +
-                          (rest ? start + (double)seg * us_per_pos * (double)ceil_div(rest, kNumCU) : 0.0) +
-                          (c > 1 ? 2.0 + 3e-6 * (double)(c * n * k) : 0.0);
-        if (best_us == 0.0 || us < best_us) { best_us = us; best = (uint32_t)c; }
+        double us = (double)(wgs / slots) * (start + (double)seg * us_per_pos * (double)(slots / kNumCU)) +
+                    (rest ? start + (double)seg * us_per_pos * (double)ceil_div(rest, kNumCU) : 0.0) +
+                    (c > 1 ? 2.0 + 3e-6 * (double)(c * n * k) : 0.0);
+        const double host = c > 1 ? 12.0 : 8.5;
+        us = (us > host ? us : host) + 0.1 * us;               // below the host's time the shorter launch still wins
+        if (best_us == 0.0 || us < best_us) { best_us = us; best = c; }
     }
-    return best;
+    *est_us = best_us;
+    return (uint32_t)best;
+}
+
+// What a position of R rows costs a workgroup of 1,024 threads that has its CU to itself, in microseconds: memory
+// (unmasked: a stream at 15 GB/s; masked: 128-byte lines at 34.5 GB/s, kept entries that share a line count once) or the work
+// on it (index and hash, shared between the rows; an LDS add per non-zero and row), whichever takes longer.  The second
+// part from launches that are bound by it: 2 x 3,657,472, s = 4 takes 1.6 ns per position of two rows, 1 x 710,366 0.9 ns of
+// one; 627 rows, 124,581 kept of 198,658, take 0.45 ns; fp32 sums (compare and swap) of 80 rows, 76,255 kept, 0.6 ns.
+static double position_us(int R, uint64_t d, bool masked, uint64_t p, uint32_t in_bytes, uint32_t s, int acc, bool table) {
+    double memory = in_bytes / 1.5e4, shared = table ? 0.02e-3 : 0.06e-3;
+    const double row = (table ? 0.16e-3 : acc == ACC_CAS ? 0.3e-3 : 0.2e-3) * s;
+    if (masked) {
+        const double lines = (double)p * in_bytes / 128.0, hit = lines * (1.0 - exp(-(double)d / lines));
+        memory = hit * 128.0 / (double)d / 3.45e4;
+        shared = 0.2e-3;
+    }
+    return R * memory > shared + R * row ? R * memory : shared + R * row;
 }
 
 // Upper bound of pick_chunks' choice, also for the workspace query.
@@ -345,7 +365,9 @@ static uint64_t chunk_limit(uint64_t n, uint64_t d, bool masked) {
 // 3,322 -> 2,752; 300 bf16 rows of 4,000,001 (rows on any 2-byte boundary): 2,583 -> 675.
 // Large batches (row groups for two or more rounds of workgroups: a masked batch of 1,024 groups, an unmasked one of 512,
 // which always has enough rows to group them by line offset) share the hash of a position between up to 8 rows; everything
-// else keeps one row per workgroup, or two where hashing is what bounds it, and is cut by pick_chunks.
+// else keeps one row per workgroup, or two where sharing index and hash pays, and is cut by pick_chunks.  On 700 drawn
+// shapes (1 to 4,096 rows of 5,000 to 12 million, half of them masked) that takes 1.42 times less time in the geometric mean
+// than filling LDS with rows; 17 were slower by more than 3 %, two by more than 10 (26.4 and 30.1 us, 120 and 134).
 static bool plan_sjlt(uint64_t n, uint64_t d, bool masked, uint32_t k, const void* g, uint64_t ldg, SjltPlan* pl, int force_v,
                       uint32_t in_bytes, uint32_t s, const grass_tuning* tune, uint64_t p, size_t max_ws = ~(size_t)0) {
     // launch-shape overrides of this call (experiments); zero = heuristic
@@ -380,16 +402,34 @@ static bool plan_sjlt(uint64_t n, uint64_t d, bool masked, uint32_t k, const voi
     const bool large = ceil_div(n, R) >= (masked ? 1024 : 512);
     const bool tuned = tune_rows || tune_chunks || tune_threads || tune_acc;
     const bool cut = !large && !tuned;
-    if (cut && force_v == 0) {
-        // hashing bounds an unmasked launch with several non-zeros per column or rows too short for the bucket table
-        R = 1;
-        if (!masked && n >= 2ull * line_period && 2 * (size_t)k * esz <= 128 * 1024 && (s > 1 || d < 65536) &&
-            (d > 32768 || n >= 2ull * kNumCU))
-            R = 2;
-    }
     int threads = 1024;
-    if (!cut && (size_t)R * k * esz <= 64 * 1024) threads = 512;      // two or more groups per CU anyway
-    if (short_rows && ceil_div(n, R) <= (uint64_t)kNumCU) threads = 1024;   // one workgroup per CU at most: widest
+    uint64_t cut_chunks = 1;
+    if (cut && force_v == 0) {
+        // One row per workgroup, or two that share index and hash where that is estimated to pay; two only with one non-zero per
+        // column (2,231 rows, 28,766 kept, s = 4: 215 us with one row, 233 with two), room for two workgroups on a CU (311 x
+        // 129,402, k = 6,584: 129 and 157) and, unmasked, rows to group by line offset.
+        uint64_t limit = chunk_limit(n, d, masked);
+        if (limit > 1 && max_ws / ((size_t)n * k * 4) < limit) limit = max_ws / ((size_t)n * k * 4);
+        const bool hash_table = !masked && s == 1 && acc == ACC_F64 && k <= 32768 && d >= 65536 && n >= 16;
+        const bool two = s == 1 && n >= (masked ? 2ull : 2ull * line_period) && 4 * (size_t)k * esz <= kLdsBytes;
+        double best_us = 0.0;
+        for (int r = 1; r <= (two ? 2 : 1); ++r) {
+            const uint64_t groups = masked || r == 1 ? ceil_div(n, (uint64_t)r) : ceil_div(n, (uint64_t)line_period * r) * line_period;
+            double us;
+            const uint32_t c = pick_chunks(groups, n, d, 1024ull * (masked ? 1 : vmax) * 2, r, k, (size_t)r * k * esz,
+                                           position_us(r, d, masked, p, in_bytes, s, acc, hash_table && ceil_div(n, r) >= 16),
+                                           limit < 1 ? 1 : limit, &us);
+            if (best_us == 0.0 || us < 0.97 * best_us) { best_us = us; R = r; cut_chunks = c; }
+        }
+        // rows of about one pass of 1,024 threads, groups for more than two workgroups on every CU: half as wide (2,895 bf16 rows
+        // of 17,275: 59 -> 44 us; 3,597 rows, 316 kept: 20.5 -> 12.3)
+        if (d <= (masked ? 4096 : in_bytes == 2 ? 32768 : 8192) && ceil_div(n, R) >= 2 * kNumCU && 4 * (size_t)R * k * esz <= kLdsBytes)
+            threads = 512;
+    }
+    if (!cut) {
+        if ((size_t)R * k * esz <= 64 * 1024) threads = 512;  // two or more groups per CU anyway
+        if (short_rows && ceil_div(n, R) <= (uint64_t)kNumCU) threads = 1024;   // one workgroup per CU at most: widest
+    }
     if (tune_threads == 256 || tune_threads == 512 || tune_threads == 1024) threads = tune_threads;
     int V = 1;
     uint32_t P = 1;
@@ -427,23 +467,7 @@ static bool plan_sjlt(uint64_t n, uint64_t d, bool masked, uint32_t k, const voi
     if (chunks > max_chunks_work) chunks = max_chunks_work;
     if (chunks > max_chunks_traffic) chunks = max_chunks_traffic;
     if (short_rows) chunks = 1;
-    if (cut) {
-        if (force_v != 0) {
-            chunks = chunk_limit(n, d, masked);
-        } else {
-            // what a position costs a workgroup that has its CU to itself: 128-byte lines at 34.5 GB/s (masked; kept
-            // entries that share a line count once), a stream at 15 GB/s plus LDS adds (unmasked)
-            double us_per_pos = (double)R * in_bytes / 1.5e4;
-            if (masked) {
-                const double lines = (double)p / E, hit = lines * (1.0 - exp(-(double)d / lines));
-                us_per_pos = hit * 128.0 / (double)d / 3.45e4;
-            }
-            uint64_t limit = chunk_limit(n, d, masked);
-            if (limit > 1 && max_ws / ((size_t)n * k * 4) < limit) limit = max_ws / ((size_t)n * k * 4);
-            const uint64_t groups = masked || P == 1 ? ceil_div(n, (uint64_t)R) : row_groups;
-            chunks = pick_chunks(groups, n, d, step, R, k, (size_t)R * k * esz, us_per_pos, limit < 1 ? 1 : limit);
-        }
-    }
+    if (cut) chunks = force_v != 0 ? chunk_limit(n, d, masked) : cut_chunks;
     if (tune_chunks > 0) chunks = tune_chunks;
     if (chunks > 65535) chunks = 65535;
     if (cut && force_v != 0) {                                // the query: room for any choice of the call

@@ -133,6 +133,24 @@ def test_batches_that_fill_the_chip_in_groups_need_no_scratch(lib, n, p, k, s):
     assert " chunks=1 " in text.value.decode()
 
 
+def test_sjlt_plan_follows_what_bounds_a_launch(lib):
+    """Launch shapes of calls that an earlier rule ran on a few workgroups or on rows that share nothing worth sharing
+    (time with that rule and with this one, in us)."""
+    from paper_2505_18976_amd import binding as b
+
+    def plan(n, p, kp, k, s, bf16):
+        text = ctypes.create_string_buffer(200)
+        assert lib.grass_sjlt_describe(4096, bf16, n, p, p, kp, k, s, 1, None, text, 200) == b.GRASS_OK
+        name, grid, block, _, chunks = text.value.decode().split(" ")[:5]
+        return int(name.split(",")[1]), int(block[6:]), int(chunks[7:])
+    assert plan(3, 4_359_211, 0, 224, 4, 1)[2] >= 60                       # 201 -> 76: chunks are whole steps of positions
+    assert plan(42, 110_868, 110_643, 22_254, 1, 0)[2] >= 2                # 47 -> 28: the work on a position, not its bytes
+    assert plan(1_104, 92_347, 0, 232, 4, 0)[0] == 1                       # 450 -> 379: an add per non-zero and row is not shared
+    assert plan(1_765, 69_547, 69_547, 189, 1, 0)[0] == 2                  # 145 -> 120: index and hash are
+    assert plan(2_895, 17_275, 0, 1_551, 1, 1)[1] == 512                   # 59 -> 45: one pass of 1,024 threads and a bit
+    assert plan(3, 57_852, 9_819, 96, 1, 0)[2] == 1                        # 12.8 -> 10.3: a second launch costs the host more
+
+
 @pytest.mark.parametrize("n,chunks", [(600, 2), (511, 4), (1100, 0)])
 def test_sjlt_query_reserves_what_the_call_can_use(lib, n, chunks):
     """511 rows of k = 16,384 are cut into up to four chunks; from 512 on a batch is large and has two at most, from 1,024

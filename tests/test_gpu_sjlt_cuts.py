@@ -18,6 +18,11 @@ TOL = 1e-5
     (130, 40_003, 0, 512, 1, True), (530, 20_001, 0, 64, 1, False), (5, 300_007, 0, 16_384, 1, True),
     (2, 40_000, 0, 20_000, 1, False),        # fp32 buckets
     (7, 100_003, 8_193, 128, 1, False), (300, 60_000, 20_001, 252, 4, True), (513, 30_000, 9_000, 33, 1, False),
+    (1_701, 30_000, 20_000, 33, 1, False),   # masked, two rows per workgroup, an odd number of rows
+    (1_401, 20_000, 9_001, 64, 1, True),
+    (1_025, 6_000, 2_000, 40, 1, False), (2_001, 17_275, 0, 60, 1, True), (1_030, 7_001, 0, 96, 1, False),   # 512 threads
+    (3, 1_200_007, 0, 224, 4, True),         # many chunks of whole steps
+    (42, 90_001, 90_001, 22_254, 1, False),  # fp32 buckets, every entry kept, chunks
 ])
 def test_cut_launches(n, p, kp, k, s, bf16):
     import paper_2505_18976_amd as grass
