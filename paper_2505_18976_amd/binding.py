@@ -24,6 +24,9 @@ GRASS_MAX_FACTOR = 128
 
 _u64, _u32, _sz, _vp, _int = ctypes.c_uint64, ctypes.c_uint32, ctypes.c_size_t, ctypes.c_void_p, ctypes.c_int
 
+_U64_MAX = (1 << 64) - 1           # seeds and stream ids are taken modulo 2^64, as ctypes does for plain arguments
+
+
 class FactgrassLayer(ctypes.Structure):
     """Mirror of `factgrass_layer` in include/grass.h."""
     _fields_ = [("x", _vp), ("gout", _vp), ("idx_in", _vp), ("idx_out", _vp),
@@ -336,7 +339,7 @@ def factgrass_layers(layers, k: int, s: int, seed: int, out: torch.Tensor, ws: t
         xs, gs = x.shape, g.shape
         assert x.dtype == torch.bfloat16 and g.dtype == torch.bfloat16 and x.is_contiguous() and g.is_contiguous()
         assert xs[0] == gs[0] == n and xs[1] == gs[1] == T and ii.numel() == kin_p and io.numel() == kout_p
-        flat += (x.data_ptr(), g.data_ptr(), ii.data_ptr(), io.data_ptr(), xs[2], gs[2], stream_id, out_ptr)
+        flat += (x.data_ptr(), g.data_ptr(), ii.data_ptr(), io.data_ptr(), xs[2], gs[2], stream_id & _U64_MAX, out_ptr)
         out_ptr += 4 * k
     # packed in one go: filling 112 ctypes structures field by field took twice as long as everything else here
     table = (FactgrassLayer * len(layers)).from_buffer_copy(struct.pack("=" + "4Q2I2Q" * len(layers), *flat))

@@ -181,6 +181,29 @@ def test_tuning_is_a_per_call_argument(lib):
                           null) == b.GRASS_EWORKSPACE
 
 
+@pytest.mark.parametrize("stream_id", [0, 18, (1 << 64) - 1, -1, (1 << 64) + 5])
+def test_layer_table_takes_stream_ids_modulo_2_64(monkeypatch, stream_id):
+    """As every other entry point does with its integers."""
+    import torch
+    from paper_2505_18976_amd import binding
+
+    class Lib:
+        def factgrass_layers(self, table, n_layers, *rest):
+            self.table = (binding.FactgrassLayer * n_layers).from_buffer_copy(table)
+            return binding.GRASS_OK
+    lib = Lib()
+    monkeypatch.setattr(binding, "load_library", lambda: lib)
+    monkeypatch.setattr(binding, "_stream", lambda: 0)
+    x, g = torch.zeros(2, 3, 8, dtype=torch.bfloat16), torch.zeros(2, 3, 16, dtype=torch.bfloat16)
+    ii, io = torch.zeros(4, dtype=torch.int32), torch.zeros(5, dtype=torch.int32)
+    out = torch.zeros(2, 14)
+    binding.factgrass_layers([(x, g, ii, io, 3), (g, x, ii, io, stream_id)], 7, 1, 0, out, ws=torch.zeros(8, dtype=torch.uint8))
+    a, b = lib.table
+    assert (a.x, a.gout, a.idx_in, a.idx_out, a.d_in, a.d_out, a.stream_id, a.out) == (
+        x.data_ptr(), g.data_ptr(), ii.data_ptr(), io.data_ptr(), 8, 16, 3, out.data_ptr())
+    assert (b.d_in, b.d_out, b.stream_id, b.out) == (16, 8, stream_id % (1 << 64), out.data_ptr() + 28)
+
+
 def test_binding_refuses_to_run_without_the_library(monkeypatch, tmp_path):
     from paper_2505_18976_amd import binding
     monkeypatch.setattr(binding, "_lib", None)
