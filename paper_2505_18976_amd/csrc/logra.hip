@@ -12,8 +12,9 @@
 //            the same time whatever the shape (few tokens, d_in != d_out).
 //   logra_outer_kernel    out_i = sum_t a_t (x) b_t from the fp32 partial sums of the ranges
 //            (out of the caches), on the fp32 matrix cores.
-// The single kernel before this gave each workgroup 64 tokens of one sample and all columns of both factors: 112
-// workgroups for 7 x 1,000 tokens, all as long as the wider factor.  Measured, kernels together (calls back to back):
+// A single kernel (logra_short.hip) gives each workgroup 64 tokens of one sample and all columns of both factors; it remains
+// for calls whose two launches cost more than that, see short_logra.  7 x 1,000 tokens were 112 such workgroups, all as long
+// as the wider factor.  Measured against it, kernels together (calls back to back):
 //   7 x 1,000 tokens, 2,048 -> 8,192            82 -> 41 us (78 -> 40)
 //   32 x 512 tokens, 4,096 -> 4,096             57 -> 53 us (54 -> 51); the projection reads at 5.7 TB/s
 //   9 x 21 tokens, 2,224 -> 7,008               (53 -> 17, launches included)
@@ -24,6 +25,11 @@ namespace grass {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// logra_short.hip
+hipError_t launch_logra_short(const uint16_t* x, const uint16_t* g, uint64_t n, uint64_t T, uint32_t d_in, uint32_t d_out,
+                              const uint16_t* pin, uint32_t k_in, const uint16_t* pout, uint32_t k_out, float* out, uint64_t ldo,
+                              hipStream_t st);
 
 constexpr int LP = 64;                 // projected width handled (k_in, k_out <= 64)
 constexpr int kProjTokens = 128;       // tokens per workgroup of the projection
@@ -330,20 +336,45 @@ static void plan_logra(uint64_t n, uint64_t T, LograPlan* pl) {
 // a CU at a time, so a cut costs (rounds of 256 workgroups) x (len + 3): about three groups' worth of time (0.76 us each
 // at 5.5 TB/s) go to filling the pipeline and to the partial sum.  Every range adds a partial sum that the second kernel
 // reads (0.17 us per 1,000 tokens).  Ranges of fewer than 4 groups are not tried.  16,384 tokens, 8,192 -> 2,048: 75 us in
-// one range each, 64 in three and one.
-static void cut_logra(const LograPlan& pl, uint32_t gx, uint32_t gg, uint32_t* len_x, uint32_t* len_g) {
+// one range each, 64 in three and one.  Returns the estimated time of the projection: between that of whole rounds and
+// that of the same work spread evenly (the ranges of the shorter factor end early).
+static double cut_logra(const LograPlan& pl, uint32_t gx, uint32_t gg, uint32_t* len_x, uint32_t* len_g) {
     const uint32_t longest = gx > gg ? gx : gg;
-    double best = 0.0;
+    double best = 0.0, us = 0.0;
     for (uint32_t ranges = 1; ranges <= pl.max_ranges; ++ranges) {             // of the longer factor
         uint32_t len = (longest + ranges - 1) / ranges;
         if (ranges > 1 && len < 4) break;
         const uint32_t rx = (gx + len - 1) / len, rg = (gg + len - 1) / len;
         if (rx + rg > pl.max_ranges) break;
         const double rounds = (double)(((uint64_t)pl.tiles * (rx + rg) + kNumCU - 1) / kNumCU);
-        const double cost = rounds * (len + 3.0) + (rx + rg) * (double)pl.tokens * 2.2e-4;
-        if (best == 0.0 || cost < best) { best = cost; *len_x = (gx + rx - 1) / rx; *len_g = (gg + rg - 1) / rg; }
+        const double sums = (rx + rg) * (double)pl.tokens * 2.2e-4, cost = rounds * (len + 3.0) + sums;
+        if (best == 0.0 || cost < best) {
+            best = cost; *len_x = (gx + rx - 1) / rx; *len_g = (gg + rg - 1) / rg;
+            us = 0.38 * (cost + (double)pl.tiles * (gx + gg + 3.0 * (rx + rg)) / kNumCU + sums);
+        }
     }
+    return us;
 }
+
+// One launch of logra_short_kernel instead of the two: rounds of one sample per CU, 64 tokens at a time, 5 us and 1 us per
+// 128 columns of the longer factor, against the projection and the outer products (16 workgroups per sample, four on a CU);
+// neither takes less than the host needs for it.  Of 418 drawn shapes (1 to 2,048 samples of 1 to 4,096 tokens) the choice
+// was within 5 % of the better one on 416 and 9 % at most; with two launches throughout 116 were slower than with one, up
+// to twice: 345 x 24 tokens, 112 -> 48 columns 26.8 us (12.5 in one launch), 256 x 64, 768 -> 768 22.4 (14.3), 3 x 40, 512 ->
+// 512 13.2 (12.2).
+static bool short_logra(uint64_t n, uint64_t T, uint32_t d_in, uint32_t d_out, uint32_t k_in, double project_us) {
+    if (T > 256) return false;
+    const uint32_t longest = d_in > d_out ? d_in : d_out;
+    double one = (double)(ceil_div(n, kNumCU) * ceil_div(T, 64)) * (5.0 + (double)ceil_div(longest, 128));
+    double two = project_us + (double)ceil_div(n * 16, 4 * kNumCU) * (0.8 + 0.65 * (double)ceil_div(k_in, 16)) + 2.0;
+    one = one > 8.7 ? one : 8.7;
+    two = two > 12.5 ? two : 12.5;
+    return one < two;
+}
+
+// Without a workspace one launch is the only way.  Calls that never needed one keep running without: the tokens of a sample
+// are one chunk of at most 64, or of at most 256 where the samples alone fill the chip.
+static bool logra_needs_no_workspace(uint64_t n, uint64_t T) { return T <= 64 || (T <= 256 && n >= (uint64_t)kNumCU); }
 
 }  // namespace grass
 
@@ -385,13 +416,17 @@ extern "C" grass_status logra_linear(const void* x, const void* gout, uint64_t n
     if (d_in > (1u << 24) || d_out > (1u << 24)) return GRASS_EUNSUPPORTED;   // 32-bit byte offsets inside a row
     LograPlan pl;
     plan_logra(n, T, &pl);
-    if (!ws || ws_bytes < pl.ws_bytes || !aligned(ws, 256)) return GRASS_EWORKSPACE;
-    unsigned char* base = static_cast<unsigned char*>(ws);
-
+    const bool have_ws = ws && ws_bytes >= pl.ws_bytes && aligned(ws, 256);
+    if (!have_ws && !logra_needs_no_workspace(n, T)) return GRASS_EWORKSPACE;
     LograProjectArgs p;
     uint32_t len_x, len_g;
     const uint32_t gx = (d_in + 63) / 64, gg = (d_out + 63) / 64;
-    cut_logra(pl, gx, gg, &len_x, &len_g);
+    const double project_us = cut_logra(pl, gx, gg, &len_x, &len_g);
+    if (!have_ws || short_logra(n, T, d_in, d_out, k_in, project_us))
+        return launch_logra_short(static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(gout), n, T, d_in, d_out,
+                                  static_cast<const uint16_t*>(P_in), k_in, static_cast<const uint16_t*>(P_out), k_out, out, ldo,
+                                  as_stream(stream)) == hipSuccess ? GRASS_OK : GRASS_EHIP;
+    unsigned char* base = static_cast<unsigned char*>(ws);
     const uint32_t rx = (gx + len_x - 1) / len_x, rg = (gg + len_g - 1) / len_g;
     float* part = reinterpret_cast<float*>(base);
     float* part_g = part + (uint64_t)rx * pl.tokens * LP;
