@@ -285,15 +285,20 @@ static bool plan_fg(uint64_t n_layers, uint64_t n, uint64_t T, uint32_t ka, uint
     pl->TB = tiles_for(kb);
     // tokens per workgroup: every workgroup pays a fixed price (SJLT of its partial accumulator, one k-vector
     // written and re-read), so take the largest chunk that still yields enough workgroups: about one per CU for
-    // chunks of 256 tokens and more (many layers in one launch: up to whole sequences, no partial sums at all),
-    // three quarters of a workgroup per CU for the short chunks of a single small layer (measured on 7 ... 112 layers of
-    // 8 x 1,024 tokens and on one layer of 32 x 512 tokens: chunks of 32, 64, 96, 128, 160 tokens 35.7, 35.9, 35.8,
-    // 38.0, 43.5 us).  Sequences of at most two token tiles are one chunk: the kernel that adds partial sums costs more
-    // than the second tile (60 x 40 tokens: 14.3 us in two chunks, 12.6 in one).
+    // chunks of 256 tokens and more (many layers in one launch: up to whole sequences, no partial sums at all; measured on
+    // 7 ... 112 layers of 8 x 1,024 tokens), three quarters of a workgroup per CU for the short chunks of a single small layer.
+    // Of those, 96 tokens are worth a place of their own between 128 and 64 while they make at most one workgroup per CU: 10 x
+    // 1,889 tokens 49.7, 44.3 and 55.4 us with 128, 96 and 64; 19 x 1,101 52.5, 49.6, 56.1; 32 x 512 37.9, 35.7, 35.7.  Just
+    // above that a second round is nearly empty, and 128 are better: 88 x 241 tokens (264 workgroups of 96) 26.1, 34.3, 28.7.
+    // Over 70 such layers: 11, 6 and 10 % behind the best chunk of each, this rule 3.  64 tokens pay from half a workgroup per CU
+    // on (6 x 1,407 tokens: 18.5 us, 20.5 in chunks of 32).  A chunk that is the whole sequence saves
+    // the kernel that adds partial sums and pays from half a workgroup per CU on (131 x 77 tokens: 14.8 us, 22.7 in chunks of
+    // 64), one of two token tiles always (60 x 40 tokens: 14.3 us in two chunks, 12.6 in one).
     uint64_t tpb = T <= 2 * kTokTile ? 2 * kTokTile : kTokTile;
     for (uint64_t cand : {1024ull, 512ull, 256ull, 128ull, 96ull, 64ull}) {
-        const uint64_t need = cand >= 256 ? (uint64_t)kNumCU * 7 / 8 : (uint64_t)kNumCU * 3 / 4;
-        if (n_layers * n * ceil_div(T, cand) >= need) { tpb = cand; break; }
+        const uint64_t need = cand >= 256 ? (uint64_t)kNumCU * 7 / 8 : T <= cand || cand == 64 ? (uint64_t)kNumCU / 2 : (uint64_t)kNumCU * 3 / 4;
+        const uint64_t wgs = n_layers * n * ceil_div(T, cand);
+        if (wgs >= need) { tpb = cand == 96 && wgs > (uint64_t)kNumCU ? 128 : cand; break; }
     }
     if (tpb > ceil_div(T, kTokTile) * kTokTile) tpb = ceil_div(T, kTokTile) * kTokTile;
     if (tune_tokens > 0) tpb = ceil_div((uint64_t)tune_tokens, kTokTile) * kTokTile;

@@ -160,6 +160,21 @@ def test_sjlt_query_reserves_what_the_call_can_use(lib, n, chunks):
     assert out.value == chunks * n * 16_384 * 4
 
 
+@pytest.mark.parametrize("n,T,chunks", [(32, 512, 6), (10, 1889, 20), (88, 241, 2), (66, 103, 1), (131, 77, 1), (60, 40, 1),
+                                        (127, 130, 2)])
+def test_factgrass_chunks(lib, n, T, chunks):
+    """Partial sums the query reserves = chunks of a sample.  88 x 241 would be 264 workgroups of 96 tokens (34 us, 26 with
+    128) and 131 x 77 262 of 64 and a kernel that adds them (23 us, 15 with whole sequences)."""
+    out = ctypes.c_size_t(0)
+    layers = 2 if (n, T) == (66, 103) else 1
+    if layers == 2:
+        assert lib.factgrass_layers_workspace_bytes(2, n, T, 64, 64, 512, 1, None, ctypes.byref(out)) == 0
+        assert out.value < 1 << 16
+    else:
+        assert lib.factgrass_linear_workspace_bytes(n, T, 64, 64, 512, 1, None, ctypes.byref(out)) == 0
+        assert out.value == (0 if chunks == 1 else chunks * n * 512 * 4)
+
+
 def test_tuning_is_a_per_call_argument(lib):
     """Launch-shape overrides travel with the call: the same query with and without them, interleaved, keeps
     answering the same (there is no process-wide setting to leak from one call into the next)."""

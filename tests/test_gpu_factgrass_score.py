@@ -72,9 +72,10 @@ def test_factgrass_parity(grass, n, T, d_in, d_out, ka, kb, k, s, layer):
     assert orc.max_rel_err(out.cpu().numpy(), ref) <= TOL_FACT
 
 
-@pytest.mark.parametrize("n,T", [(20, 960), (20, 949), (60, 40), (3, 65)])
+@pytest.mark.parametrize("n,T", [(20, 960), (20, 949), (60, 40), (3, 65), (88, 241), (131, 77)])
 def test_factgrass_chunk_rule(grass, n, T):
-    """Chunks of 96 tokens (whole and with a short last one), two token tiles in one chunk, and one token more."""
+    """Chunks of 96 tokens (whole and with a short last one), two token tiles in one chunk, and one token more; 264 workgroups of
+    96 tokens (128 instead) and a sequence of three tiles in one chunk."""
     x, g = synth.linear_layer_factors(n, T, 64, 48, seed=47, device=_dev())
     ii = grass.grass_mask_indices(0, 16, 64, 32, device=_dev())
     io = grass.grass_mask_indices(0, 17, 48, 40, device=_dev())
