@@ -130,9 +130,11 @@ grass_status grass_sjlt_tables(uint64_t seed, uint64_t stream_id, uint64_t d, ui
  * of at least 4 bytes works.
  * Workspace: partial sums of the column chunks, and for long unmasked inputs
  * with s == 1 room for a per-call table of 16-bit (bucket, sign) entries.  A
- * workspace that is too small for the partial sums is GRASS_EWORKSPACE; one
- * that holds them but not the table is accepted and the call hashes every
- * position instead (same result bit for bit, a few per cent slower).         */
+ * workspace that is too small for the partial sums is GRASS_EWORKSPACE, unless
+ * the call can do in one chunk per row group at little cost (short rows, rows
+ * for every CU): such calls run without a workspace, on fewer workgroups.  One
+ * that holds the partial sums but not the table is accepted and the call hashes
+ * every position instead (same result bit for bit, a few per cent slower).   */
 grass_status grass_sjlt_workspace_bytes(uint64_t n, uint64_t p, uint32_t kprime_or_0,
                                         uint32_t k, uint32_t s, const grass_tuning* host_tuning,
                                         size_t* host_bytes);
@@ -173,10 +175,11 @@ grass_status grass_sjlt_describe(const void* g, int input_is_bf16, uint64_t n, u
  * of GRASS_NOALLOC_SCRATCH_BYTES that is part of the library's device code, one
  * copy per GPU for the life of the process.  The call allocates and frees
  * nothing; its first call on a device looks up the buffer's address.
- * A problem whose partial sums (column chunks x n x k x 4 bytes) exceed the
- * buffer is refused with GRASS_ETOOLARGE before anything is launched: use
- * grass_sjlt with a workspace for those.  Large batches of the fused mask path
- * need no scratch memory at all and are never refused.
+ * Batches that are cut into chunks to fill the chip take no more chunks than
+ * the buffer holds.  A large batch whose partial sums (column chunks x n x k x 4
+ * bytes) exceed the buffer is refused with GRASS_ETOOLARGE before anything is
+ * launched: use grass_sjlt with a workspace for those.  Large batches of the
+ * fused mask path need no scratch memory at all and are never refused.
  * All calls on one GPU share the buffer: calls that may overlap in time (on
  * different streams, or from different threads) race on it and must be ordered
  * by the caller.  Nothing in the buffer needs to start at zero.               */

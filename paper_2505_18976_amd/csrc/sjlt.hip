@@ -369,7 +369,8 @@ static uint64_t chunk_limit(uint64_t n, uint64_t d, bool masked) {
 // shapes (1 to 4,096 rows of 5,000 to 12 million, half of them masked) that takes 1.42 times less time in the geometric mean
 // than filling LDS with rows; 17 were slower by more than 3 %, two by more than 10 (26.4 and 30.1 us, 120 and 134).
 static bool plan_sjlt(uint64_t n, uint64_t d, bool masked, uint32_t k, const void* g, uint64_t ldg, SjltPlan* pl, int force_v,
-                      uint32_t in_bytes, uint32_t s, const grass_tuning* tune, uint64_t p, size_t max_ws = ~(size_t)0) {
+                      uint32_t in_bytes, uint32_t s, const grass_tuning* tune, uint64_t p, size_t max_ws = ~(size_t)0,
+                      bool may_cut = true) {
     // launch-shape overrides of this call (experiments); zero = heuristic
     const int tune_rows = tune ? tune->sjlt_rows_per_block : 0;
     const int tune_chunks = tune ? tune->sjlt_column_chunks : 0;
@@ -401,7 +402,7 @@ static bool plan_sjlt(uint64_t n, uint64_t d, bool masked, uint32_t k, const voi
     const uint32_t line_period = E / gcd;                     // rows that far apart start at the same offset inside a line
     const bool large = ceil_div(n, R) >= (masked ? 1024 : 512);
     const bool tuned = tune_rows || tune_chunks || tune_threads || tune_acc;
-    const bool cut = !large && !tuned;
+    const bool cut = !large && !tuned && may_cut;
     int threads = 1024;
     uint64_t cut_chunks = 1;
     if (cut && force_v == 0) {
@@ -441,7 +442,7 @@ static bool plan_sjlt(uint64_t n, uint64_t d, bool masked, uint32_t k, const voi
         // (a launch that is cut with one row per workgroup needs no grouping: a single row has one alignment, whatever it is;
         // a large one keeps it, its groups set the number of chunks and so the scratch memory below)
         const uint32_t period = cut && R == 1 ? 1 : line_period;
-        if (period == 1 || n >= (uint64_t)period * R) {
+        if (period == 1 || n >= (cut ? 1ull : 4ull) * period * R) {
             P = period; V = (int)vmax; align_lines = true;
         } else if (aligned(g, 16) && ldg % vmax == 0) V = (int)vmax;
         else if (in_bytes == 4 && aligned(g, 8) && ldg % 2 == 0) V = 2;
@@ -576,6 +577,17 @@ extern "C" grass_status grass_sjlt_workspace_bytes(uint64_t n, uint64_t p, uint3
     return GRASS_OK;
 }
 
+// The plan of a call that has ws_bytes of workspace (0: none).  Without room for the partial sums of the cut launch a call runs
+// the launch that large batches use, if that needs no more than it has: short rows and batches that fill the chip never needed
+// a workspace.
+static grass_status plan_call(uint64_t n, uint64_t d, bool masked, uint32_t k, const void* g, uint64_t ldg, SjltPlan* pl,
+                              uint32_t in_bytes, uint32_t s, const grass_tuning* tune, uint64_t p, size_t max_ws, size_t ws_bytes) {
+    if (!plan_sjlt(n, d, masked, k, g, ldg, pl, 0, in_bytes, s, tune, p, max_ws)) return GRASS_EUNSUPPORTED;
+    if (pl->ws_bytes <= ws_bytes) return GRASS_OK;
+    if (!plan_sjlt(n, d, masked, k, g, ldg, pl, 0, in_bytes, s, tune, p, max_ws, false)) return GRASS_EUNSUPPORTED;
+    return pl->ws_bytes <= ws_bytes ? GRASS_OK : GRASS_EWORKSPACE;
+}
+
 static grass_status run_sjlt(const void* g, uint32_t in_bytes, uint64_t n, uint64_t p, uint64_t ldg, const int32_t* idx,
                              uint32_t kprime, uint32_t k, uint32_t s, uint64_t seed, uint64_t stream_id, float* out,
                              uint64_t ldo, void* ws, size_t ws_bytes, const grass_tuning* tune, grass_stream stream,
@@ -588,8 +600,8 @@ static grass_status run_sjlt(const void* g, uint32_t in_bytes, uint64_t n, uint6
     if (n * ldg >= (1ull << 62)) return GRASS_EINVAL;
     const uint64_t d = masked ? kprime : p;
     SjltPlan pl;
-    if (!plan_sjlt(n, d, masked, k, g, ldg, &pl, 0, in_bytes, s, tune, p, max_ws)) return GRASS_EUNSUPPORTED;
-    if (pl.ws_bytes > 0 && (!ws || ws_bytes < pl.ws_bytes || !aligned(ws, 256))) return GRASS_EWORKSPACE;
+    st = plan_call(n, d, masked, k, g, ldg, &pl, in_bytes, s, tune, p, max_ws, ws && aligned(ws, 256) ? ws_bytes : 0);
+    if (st != GRASS_OK) return st;
 
     SjltArgs a;
     a.g = g; a.idx = idx; a.ldg = ldg; a.n = n; a.d = d;
@@ -658,7 +670,9 @@ extern "C" grass_status grass_sjlt_describe(const void* g, int input_is_bf16, ui
     if (n == 0 || ldg < p) return GRASS_EINVAL;
     const uint32_t in_bytes = input_is_bf16 ? 2 : 4;
     SjltPlan pl;
-    if (!plan_sjlt(n, masked ? kprime_or_0 : p, masked, k, g, ldg, &pl, 0, in_bytes, s, host_tuning, p)) return GRASS_EUNSUPPORTED;
+    st = plan_call(n, masked ? kprime_or_0 : p, masked, k, g, ldg, &pl, in_bytes, s, host_tuning, p, ~(size_t)0,
+                   with_workspace ? ~(size_t)0 : 0);
+    if (st != GRASS_OK && st != GRASS_EWORKSPACE) return st;
     const uint32_t m = k / s;
     int mode = (s == 1 && m >= 2 && (m & (m - 1)) == 0) ? MODE_FAST : MODE_GENERAL;
     if (pl.table && with_workspace) mode = MODE_TABLE;

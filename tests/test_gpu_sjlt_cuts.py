@@ -49,3 +49,31 @@ def test_fixed_scratch_limits_the_chunks():
     grass.grass_sjlt_noalloc(g, 8_192, 1, 5, 1, out)
     ref = orc.sjlt(g[[0, 99]].cpu().numpy(), 8_192, 1, 5, 1)
     assert orc.max_rel_err(out[[0, 99]].cpu().numpy(), ref) <= TOL
+
+
+@pytest.mark.parametrize("n,p,kp,k,s,bf16,free", [
+    (2, 118_046, 0, 14_076, 4, False, True), (3, 24_051, 16_195, 49, 1, False, True), (8, 27_147, 27_147, 1_451, 1, True, True),
+    (7, 123_835, 0, 23_666, 1, False, True), (21, 80_117, 0, 7_172, 4, True, True),
+    (6, 31_000, 31_000, 64, 1, False, True),
+    (1, 1 << 20, 0, 16, 1, False, False),
+])
+def test_calls_that_never_needed_a_workspace(n, p, kp, k, s, bf16, free):
+    """Without a workspace a call that would be cut into chunks runs uncut if that needs none, and is refused otherwise."""
+    import ctypes
+    import paper_2505_18976_amd as grass
+    from paper_2505_18976_amd import binding as b
+    dev = torch.device("cuda:0")
+    g = synth.bernoulli_sparse_normal(n, p, 0.3, 1.0, seed=n + p, device=dev)
+    g = g.to(torch.bfloat16) if bf16 else g
+    idx = grass.grass_mask_indices(5, 0, p, kp, device=dev) if kp else None
+    out = torch.full((n, k), 7.0, device=dev)
+    f = grass.load_library().grass_sjlt_bf16 if bf16 else grass.load_library().grass_sjlt
+    status = f(g.data_ptr(), n, p, p, idx.data_ptr() if kp else None, kp, k, s, 5, 1, out.data_ptr(), k, ctypes.c_void_p(0), 0, None,
+               torch.cuda.current_stream().cuda_stream)
+    assert status == (b.GRASS_OK if free else b.GRASS_EWORKSPACE)
+    if not free:
+        assert bool((out == 7.0).all())
+        return
+    gh = g.float().cpu().numpy()
+    ref = orc.grass(gh, idx.cpu().numpy(), k, s, 5, 1) if kp else orc.sjlt(gh, k, s, 5, 1)
+    assert orc.max_rel_err(out.cpu().numpy(), ref) <= TOL
