@@ -256,8 +256,10 @@ grass_status logra_linear(const void* x, const void* gout,
  * Sec. 2.1, attribute stage: scores[m, i] = <test_m, train_i> for all pairs of
  * compressed gradients (no preconditioner).
  * train: N x K fp32 (ld_train >= K), test: M x K fp32, scores: M x N fp32.
- * compute_mode 0: fp32 MFMA.  1: inputs rounded to bf16 (nearest-even), bf16
- * MFMA with fp32 accumulation.
+ * compute_mode 0: fp32 products and accumulation (each operand exactly split
+ * into three bf16 pieces, six products of pieces on the bf16 matrix cores; the
+ * three left out are below 2^-24 of a product together).  1: inputs rounded to
+ * bf16 (nearest-even), bf16 MFMA with fp32 accumulation.
  * Workspace (optional, from grass_score_workspace_bytes): with it, mode 1
  * rounds both operands once into the workspace and runs the direct-to-LDS bf16
  * kernel (about twice as fast as rounding on the fly), and products whose M x N
@@ -292,7 +294,7 @@ grass_status grass_score_bf16(const void* train, const void* test,
  * grass_gauss_matrix writes columns [p0, p0+pc) of P as a k x pc fp32 matrix
  * (ldP >= pc); grass_gauss_project computes out = g P^T (n x k fp32) in
  * p-chunks of at most p_chunk columns, regenerating P chunk by chunk in the
- * workspace.  compute_mode 0: fp32 MFMA.  1: both the chunk of P and the chunk
+ * workspace.  compute_mode as in grass_score; 1: both the chunk of P and the chunk
  * of g are rounded to bf16 (nearest-even), bf16 MFMA, fp32 accumulation.      */
 grass_status grass_gauss_matrix(uint64_t seed, uint64_t stream_id, uint64_t p, uint32_t k,
                                 uint64_t p0, uint64_t pc, float* P, uint64_t ldP, grass_stream stream);
@@ -311,11 +313,10 @@ grass_status grass_gauss_project(const float* g, uint64_t n, uint64_t p, uint64_
  *
  * grass_fim: F = (1/N) sum_i g_i g_i^T for the rows of G (N x k fp32 device,
  * ldg >= k).  F is k x k fp32 (ldf >= k), written in full and exactly
- * symmetric.  fp32 MFMA, accumulated over interleaved ranges of the rows of G
- * in a fixed order (bit-reproducible).  Fastest when G is 16-byte aligned and k
- * and ldg are multiples of 4: G is then read in place, otherwise transposed
- * chunks go through the workspace.  Workspace from
- * grass_fim_workspace_bytes(N, k), 256-byte aligned.
+ * symmetric.  fp32 products as in grass_score mode 0, accumulated over
+ * contiguous ranges of the rows of G whose partial sums are added in a fixed
+ * order (bit-reproducible).  G is read in place, whatever its alignment.
+ * Workspace from grass_fim_workspace_bytes(N, k), 256-byte aligned.
  *
  * grass_fim_inverse: W = (F + lambda I)^{-1}, k x k fp32 (ldw >= k), lambda >= 0
  * absolute.  Only the lower triangle of F is read.  The factorisation runs in
@@ -326,7 +327,7 @@ grass_status grass_gauss_project(const float* g, uint64_t n, uint64_t p, uint64_
  * 2 * kp^2 * 8 bytes with kp = k rounded up to 64.
  *
  * grass_ifvp: out (N x k fp32, ldo >= k), row i = W g_i for the rows g_i of G
- * (N x k).  W must be symmetric (as grass_fim_inverse writes it).  fp32 MFMA.
+ * (N x k).  W must be symmetric (as grass_fim_inverse writes it).  fp32 products.
  * Scores with the preconditioner are then grass_score(out_train, test) =
  * <g_test, (F + lambda I)^{-1} g_i>.
  * Errors: GRASS_EINVAL for null pointers, k = 0, N = 0 in grass_fim, short
@@ -352,15 +353,14 @@ grass_status grass_ifvp(const float* G, uint64_t N, uint32_t k, uint64_t ldg,
  *
  * grass_selective_mask_grad: objective value and gradient with respect to S.
  *   G  (n x p fp32, ldg)  train gradients;  Gt (m x p fp32, ldgt) test gradients
- *      (fastest when G is 16-byte aligned and ldg is a multiple of 4: both large
- *      products then take G in place from HBM; any 4-byte alignment works);
+ *      (read in place by both large products, at any 4-byte alignment);
  *   A  (m x n fp32, lda)  exact scores A[t][i] = <gt_t, g_i>, i.e.
  *                         grass_score(train = G, test = Gt), computed once;
  *   S  (p fp32) logits;  grad (p fp32) receives d objective / d S;
  *   objective (device double, may be NULL) receives the objective value.
  *   n >= 2, m >= 1.  A test row whose exact or masked scores are constant over i
  *   has no correlation: it contributes 0 to the value and to the gradient.
- *   Two fp32 MFMA GEMMs of 2*m*n*p flops each; reductions in fp64, fixed order.
+ *   Two fp32 products of 2*m*n*p flops each; reductions in fp64, fixed order.
  *
  * grass_selective_mask_indices: index extraction.  k == 0: every j with
  *   sigma(S_j) >= 1/2 (S_j >= 0), ascending; their number goes to *count (device
