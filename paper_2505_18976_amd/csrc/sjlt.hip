@@ -309,7 +309,7 @@ struct SjltPlan {
 // Column chunks of a launch without enough row groups to fill the chip several times over.  Workgroups of 1,024 threads
 // run two to a CU (LDS permitting), 512 at a time; one that has its CU to itself takes `us_per_pos` for a position, two
 // take twice that each; starting and draining one costs about a microsecond plus 0.4 per 1,000 sums; cutting rows costs
-// a second launch, which takes 0.13 us for every chunk that it adds, and the traffic of the partial sums.  Nothing is gained below the time that the host needs for the call:
+// a second launch, which takes 0.13 us and more for every chunk that it adds, and the traffic of the partial sums.  Nothing is gained below the time that the host needs for the call:
 // 8.5 us, 12 with the second launch and its workspace.
 static uint32_t pick_chunks(uint64_t groups, uint64_t n, uint64_t d, uint64_t step, int R, uint32_t k, size_t lds_bytes,
                             double us_per_pos, uint64_t max_chunks, double* est_us) {
@@ -325,7 +325,7 @@ static uint32_t pick_chunks(uint64_t groups, uint64_t n, uint64_t d, uint64_t st
         const uint64_t wgs = groups * c, rest = wgs % slots;
         double us = (double)(wgs / slots) * (start + (double)seg * us_per_pos * (double)(slots / kNumCU)) +
                     (rest ? start + (double)seg * us_per_pos * (double)ceil_div(rest, kNumCU) : 0.0) +
-                    (c > 1 ? 2.0 + 0.13 * (double)c + 3e-6 * (double)(c * n * k) : 0.0);
+                    (c > 1 ? 2.0 + 0.2 * (double)c + 3e-6 * (double)(c * n * k) : 0.0);
         const double host = c > 1 ? 12.0 : 8.5;
         us = (us > host ? us : host) + 0.1 * us;               // below the host's time the shorter launch still wins
         if (best_us == 0.0 || us < best_us) { best_us = us; best = c; }
@@ -335,22 +335,24 @@ static uint32_t pick_chunks(uint64_t groups, uint64_t n, uint64_t d, uint64_t st
 }
 
 // What a position of R rows costs a workgroup of 1,024 threads that has its CU to itself, in microseconds: memory
-// (unmasked: a stream at 20 GB/s, 15 with the bucket table, which is read as well; masked: 128-byte lines at 34.5 GB/s, kept
+// (unmasked: a stream at 24 GB/s, 15 with the bucket table, which is read as well; masked: 128-byte lines at 34.5 GB/s, kept
 // entries that share a line count once) or the work on it (index and hash, shared between the rows; loads and LDS adds of
-// every row), whichever takes longer; masked loads are only partly covered by the work.  The second part from launches that
-// are bound by it, in ns per position of one and of two rows: unmasked 0.22 and 0.39, with s = 4 0.83 and 1.55 (2,968 x 56,501;
-// 698 x 572,596), with the bucket table 0.17 (200 x 11.2 M), fp32 sums 0.32; masked fp32 0.31 and 0.44, bf16 0.42 and 0.77
-// (2,348 x 23,867 and 1,061 x 32,219, all kept), s = 4 0.85 (2,015 rows, 15,629 kept of 28,918), 1.3 with more lines (63 bf16
-// rows, 11,454 kept of 171,408).
+// every row), whichever takes longer; masked loads are only partly covered by the work.  The second part is measured on
+// launches that are bound by it, half of them on dense rows, half with 30 % (masked: 50 %) zeros, which need no add; medians in
+// ns per position of one row and of two:
+//   unmasked fp32 0.21 0.35, bf16 0.28 0.44, s = 4 0.79 1.37, with the bucket table 0.17 0.34
+//   masked (less 0.4 of the lines) fp32 0.32 0.48, s = 4 0.58 1.05; bf16 0.35 0.74, s = 4 0.63 1.2
 static double position_us(int R, uint64_t d, bool masked, uint64_t p, uint32_t in_bytes, uint32_t s, int acc, bool table) {
-    double memory = in_bytes / 2.0e4, uncovered = 0.0, shared = 0.025 + 0.025 * s, row = 0.17 + 0.178 * (s - 1);
+    const bool f32 = in_bytes == 4;
+    double memory = in_bytes / 2.4e4, uncovered = 0.0, shared = (f32 ? 0.065 : 0.12) + 0.07 * (s - 1),
+           row = (f32 ? 0.145 : 0.155) + 0.122 * (s - 1);
     if (table) { memory = in_bytes / 1.5e4; shared = 0.0; row = 0.17; }
     if (masked) {
         const double lines = (double)p * in_bytes / 128.0, hit = lines * (1.0 - exp(-(double)d / lines));
         memory = hit * 128.0 / (double)d / 3.45e4;
         uncovered = 0.4 * memory;
-        shared = in_bytes == 4 ? 0.18 : 0.08;
-        row = (in_bytes == 4 ? 0.0 : 0.18) + 0.15 * s;
+        shared = f32 ? 0.14 : 0.03;
+        row = f32 ? 0.17 + 0.1 * (s - 1) : 0.34 + 0.09 * (s - 1);
     }
     if (acc == ACC_CAS) row += 0.1 * s;
     const double work = 1e-3 * (shared + R * row) + R * uncovered;
@@ -373,8 +375,9 @@ static uint64_t chunk_limit(uint64_t n, uint64_t d, bool masked) {
 // Large batches (row groups for two or more rounds of workgroups: a masked batch of 1,024 groups, an unmasked one of 512,
 // which always has enough rows to group them by line offset) share the hash of a position between up to 8 rows; everything
 // else keeps one row per workgroup, or two where sharing index and hash pays, and is cut by pick_chunks.  On 1,400 drawn
-// shapes (1 to 4,096 rows of 5,000 to 12 million, half of them masked) that is 1.44 times as fast in the geometric mean as
-// filling LDS with rows; 33 were slower by more than 3 %, five by more than 10, 15 at most.
+// shapes (1 to 4,096 rows of 5,000 to 12 million, half of them masked), each with dense rows and with zeros, that is 1.43
+// times as fast in the geometric mean as filling LDS with rows; 16 of the 2,800 calls were slower by more than 10 %, most of
+// them calls of 12 us.
 static bool plan_sjlt(uint64_t n, uint64_t d, bool masked, uint32_t k, const void* g, uint64_t ldg, SjltPlan* pl, int force_v,
                       uint32_t in_bytes, uint32_t s, const grass_tuning* tune, uint64_t p, size_t max_ws = ~(size_t)0,
                       bool may_cut = true) {
@@ -413,14 +416,12 @@ static bool plan_sjlt(uint64_t n, uint64_t d, bool masked, uint32_t k, const voi
     int threads = 1024;
     uint64_t cut_chunks = 1;
     if (cut && force_v == 0) {
-        // One row per workgroup, or two that share index and hash where that is estimated to pay; two not with the bucket table
-        // (314 bf16 rows of 211,504: 59 us with one row, 66 with two) nor masked with several non-zeros per column (2,231 rows,
-        // 28,766 kept, s = 4: 215 and 233), only with room for two workgroups on a CU (311 x 129,402, k = 6,584: 129 and 157) and,
-        // unmasked, rows to group by line offset.
+        // One row per workgroup, or two that share index and hash where that is estimated to gain 6 %: not with the bucket table,
+        // where they gain nothing, and unmasked only if there are rows to group by line offset.
         uint64_t limit = chunk_limit(n, d, masked);
         if (limit > 1 && max_ws / ((size_t)n * k * 4) < limit) limit = max_ws / ((size_t)n * k * 4);
         const bool hash_table = !masked && s == 1 && acc == ACC_F64 && k <= 32768 && d >= 65536 && n >= 16;
-        const bool two = (masked ? s == 1 && n >= 2 : !hash_table && n >= 2ull * line_period) && 4 * (size_t)k * esz <= kLdsBytes;
+        const bool two = !hash_table && n >= (masked ? 2ull : 2ull * line_period) && 2 * (size_t)k * esz <= 128 * 1024;
         double best_us = 0.0;
         for (int r = 1; r <= (two ? 2 : 1); ++r) {
             const uint64_t groups = masked || r == 1 ? ceil_div(n, (uint64_t)r) : ceil_div(n, (uint64_t)line_period * r) * line_period;
@@ -428,7 +429,7 @@ static bool plan_sjlt(uint64_t n, uint64_t d, bool masked, uint32_t k, const voi
             const uint32_t c = pick_chunks(groups, n, d, 1024ull * (masked ? 1 : vmax) * 2, r, k, (size_t)r * k * esz,
                                            position_us(r, d, masked, p, in_bytes, s, acc, hash_table),
                                            limit < 1 ? 1 : limit, &us);
-            if (best_us == 0.0 || us < (masked ? 0.9 : 0.97) * best_us) { best_us = us; R = r; cut_chunks = c; }
+            if (best_us == 0.0 || us < 0.94 * best_us) { best_us = us; R = r; cut_chunks = c; }
         }
         // rows of about one pass of 1,024 threads, groups for more than two workgroups on every CU: half as wide (2,895 bf16 rows
         // of 17,275: 59 -> 44 us; 3,597 rows, 316 kept: 20.5 -> 12.3)
