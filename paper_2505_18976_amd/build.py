@@ -1,7 +1,7 @@
 """Builds libgrass.so (all HIP kernels + the C ABI) for gfx950 with hipcc.
 
 The library is built in-tree next to this file; tests, the smoke check and the
-benchmark load that file and never build implicitly on a GPU machine.  Every source
+benchmark load that file and never build implicitly on a machine with a GPU.  Every source
 is compiled to an object of its own (in parallel, into a temporary directory)
 and the objects are linked into one shared library.
 """
