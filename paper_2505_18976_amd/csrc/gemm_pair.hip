@@ -1,0 +1,794 @@
+// fp32 products on the fp16 matrix cores: C[M x N] = or += A * B^T with fp32 operands, fp32 accumulation and an error that is
+// not larger than that of the products of three bf16 pieces (gemm_split.hip), for workgroups that contract at least 256 k.
+//
+// Every row of an operand ("slot") is scaled by a power of two and split into two fp16 numbers, a = a0 + a1 with a0 = fp16(a)
+// and a1 = fp16(a - a0), both rounded to nearest: 23 of the 24 significant bits, the last one with an error of one unit at
+// most.  Three of the four products of two such sums are accumulated by v_mfma_f32_16x16x32_f16; a1 b1 is below 2^-22 |a b|,
+// 2^-24.8 in the root mean square.  The sums take half as many roundings as six products of bf16 pieces do, which more than
+// makes up for the bit.  Error against fp64, 2-norm, one K range, normal data (three bf16 pieces in brackets): K = 64 1.1e-7
+// (1.1e-7), 256 1.9e-7 (2.4e-7), 1,024 3.6e-7 (4.9e-7), 4,096 7.1e-7 (1.0e-6); 100 x 1,000 x 1,863,690 in 64 ranges 5.9e-6
+// (1.1e-5); FIM of 65,536 x 4,096 rows 4.0e-7 (2.8e-6); largest deviations likewise.  Below 256 k there is next to nothing to
+// gain (launches start 8 us later, the bit shows), so shorter ranges stay with gemm_split.hip.
+//
+// Scales.  fp16 reaches from 2^-24 to 2^16.  A workgroup takes the largest |x| of 32 or 128 values of every slot (a group of
+// 32 k, with three more spread over ranges of 2,048 k and more) and scales it to 2^5..2^6: values up to 2^9 times the sample's
+// largest fit, smaller ones lose nothing above 2^-7 of it and are off by 2^-30 of it below.  A value that is too large
+// becomes infinite and makes every sum of its slot infinite or NaN, so the finished sums tell.  Slots whose sample is zero are
+// scaled like the largest of the tile, and their largest value is recorded on the way.  Where either does not fit, the tile
+// runs again with the largest values of the whole range (pair_general); where only infinities and NaNs were found, their
+// sums are contracted again by v_mfma_f32_16x16x4_f32.
+// A slot is of wide range if an eighth of the quads of its sample are 2^12 below its largest value or the largest value of
+// the range is 2^18 above that of the sample.  What is small beside that value is then known to few bits, which shows where
+// the other operand is zero at the large ones.  Such sums are found by their size, below 2^10 times the bound of what the
+// scale took from them (2^-25 a k), and contracted again if half of those of a row or column of 16 x 16 are so small.
+//
+// Bound: the power that the matrix cores and the data on the way to them draw.  1,024 x 65,536 x 4,096 takes 1.45 ms = 1,140
+// TFLOP/s of fp16 products at 1.5 GHz, matrix cores 74 % busy; without loads and splitting it would be 1.15 ms, a loop of
+// matrix instructions alone 0.95.  What counts is therefore work beside the matrix instructions: 16 x 16 x 32 instructions
+// (1,806 TFLOP/s alone on random data; 32 x 32 x 16: 1,611), whole lines of 32 k per load, one exclusive or against bank
+// conflicts (26 % of the cycles before), no arithmetic on addresses, five vector operations per pair of values.
+//   three bf16 pieces -> two fp16 pieces
+//   1,024 x 65,536 x 4,096, A B^T                     2.25 -> 1.45 ms
+//   65,536 x 4,096 x 4,096, A B^T                     9.5  -> 5.1
+//   65,536 x 4,096, lower tiles of A^T A              5.3  -> 2.9
+//   100 x 1,000 x 1,863,690, A B^T, unaligned rows    3.3  -> 1.85
+//   100 x 327,680 x 1,000, A B                        0.50 -> 0.38
+// Two groups on their way instead of one (150 us for 64 x 65,536 x 2,048 either way) and vector instructions that are not
+// spread over the matrix instructions (4 % slower) did not pay.
+#include <type_traits>
+
+#include "gemm_f32_device.h"
+
+namespace grass {
+
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef const float __attribute__((address_space(1)))* gfloat;             // global loads, whatever the compiler can tell
+typedef const unsigned char __attribute__((address_space(1)))* gbyte;
+typedef const f32x4u __attribute__((address_space(1)))* gvec;
+
+// Exponent of the leading bit of a positive fp32 number given by its bits; 128 for infinity.
+__device__ __forceinline__ int lead_exponent(uint32_t bits) {
+    return bits >= 0x800000u ? (int)(bits >> 23) - 127 : -118 - (int)__builtin_clz(bits);
+}
+__device__ __forceinline__ int clamp_exponent(int e) { return e < -126 ? -126 : e > 127 ? 127 : e; }
+
+template <int CTRL>
+__device__ __forceinline__ float swap_lanes(float x) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xF, 0xF, true));
+}
+
+constexpr int kSampleTop = 5, kExactTop = 14;      // exponents to which the largest value of a sample, of a range is scaled
+constexpr int kGuessTop = 9, kLowest = 3;          // of a tile's samples, for slots whose own are zero; lowest for those to hold
+constexpr int kTiny = 12, kFar = 18;               // binades below the largest value: quads that make a sample, a range wide
+
+// One workgroup owns a TM x TN tile of C; its WR x WC wavefronts own RB x NB blocks of 16 x 16 each.  K is consumed in groups
+// of 32 through two LDS stages.  A group travels from memory into registers one group before it is split and stored, which
+// is spread over the multiplication of the group before it; a register is loaded again as soon as it is stored.  The barrier
+// of a group sits before its last row of blocks: by then every wavefront has the fragments of this group in registers and its
+// part of the next group in LDS.
+// AKN / BKN: the operand is stored K-major (K x M resp. K x N).
+// GENERAL: with everything that is rare.  It is a function of its own that is called where the kernel gives up, because in one
+// function the ways to it cost the main loop 50 to 200 registers that had to be spilled.
+typedef unsigned char __attribute__((address_space(3)))* lds_byte;
+
+enum : int { kDone = 0, kAgain = 1, kAgainExact = 2 };
+
+// mode: kAgain, from the start; kAgainExact, with the largest values of the range (the samples' scales are in LDS and, unless
+// C accumulates, the finite sums in C).  Returns kDone or what is left to do.
+template <int RB, int NB, int WR, int WC, bool AKN, bool BKN, bool GENERAL>
+__device__ __forceinline__ int pair_tile(GemmF32Args a, lds_byte lds, int mode) {
+    unsigned char* const smem = (unsigned char*)lds;
+    constexpr int NW = WR * WC, THREADS = 64 * NW;
+    constexpr int TM = 16 * RB * WR, TN = 16 * NB * WC, SLOTS = TM + TN;
+    constexpr int CA = TM / (8 * NW), CB = TN / (8 * NW), NC = CA + CB;      // chunks of 4 fp32 per thread and group
+    static_assert(TM % (8 * NW) == 0 && TN % (8 * NW) == 0 && (!AKN || CA == 4) && (!BKN || CB == 4) && NB == 4, "loading map");
+    constexpr int kReg = SLOTS * 16, kPlane = 4 * kReg, kStage = 2 * kPlane;
+    uint32_t* const mx = reinterpret_cast<uint32_t*>(smem + 2 * kStage);      // [SLOTS] largest |x| of a slot (bits)
+    int* const ex = reinterpret_cast<int*>(mx + SLOTS);                       // [SLOTS] exponent of a slot's scale
+    uint32_t* const wd = mx + 2 * SLOTS;                                      // [SLOTS] a slot of wide range
+    uint32_t* const mt = mx + 3 * SLOTS;                                      // largest of the samples of A, of B; two votes
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave / WC, wn = wave % WC;
+    const auto [tm, tn, split] = gemm_f32_tile(a);
+    const uint64_t m0 = (uint64_t)tm * TM, n0 = (uint64_t)tn * TN;
+    a.C += split * a.split_stride_c;
+    const uint64_t ng_all = (a.K + 31) / 32;
+    const uint64_t g0 = split * ng_all / a.splits;
+    const uint32_t ng = (uint32_t)((split + 1) * ng_all / a.splits - g0);     // >= 1: splits <= ng_all
+
+    // ---- loading.  What depends on the lane is worked out where it is needed (`ln` hides the lane from the compiler, which
+    // would keep all of it in registers through the main loop).
+    struct Side {
+        gfloat mat;
+        uint64_t ld, rows, first, r0;      // first: first row of the tile; K-major: r0 = first column that is loaded
+        uint64_t k0, step;                 // first k of the range; elements from a group to the next
+        int T, slot0;                      // rows of the tile, slot of the first one
+        bool narrow;
+    };
+    auto make = [&](bool kmajor, const float* src, uint64_t ld, uint64_t rows, uint64_t first, int T, int slot0) {
+        Side o{(gfloat)src, ld, rows, first, first, g0 * 32, kmajor ? 32 * ld : 32, T, slot0, false};
+        if (kmajor) {
+            o.narrow = rows < 4;                               // too narrow for 16-byte loads
+            o.r0 = first + 4 <= rows ? first : o.narrow ? 0 : rows - 4;
+        }
+        return o;
+    };
+    const Side sa = make(AKN, a.A, a.lda, a.M, m0, TM, 0), sb = make(BKN, a.B, a.ldb, a.N, n0, TN, TM);
+    const std::integral_constant<bool, AKN> km_a;
+    const std::integral_constant<bool, BKN> km_b;
+    auto hide = [](int x) {
+        asm volatile("" : "+v"(x));
+        return x;
+    };
+    // Row-major: chunk i of a wavefront is 8 rows, 8 lanes take the 32 k of one.  Lanes past the edge repeat the last row, chunks
+    // past the edge the tile's first.  K-major: a thread takes 4 columns of 4 k, chunk i is its row i on loading and its column
+    // i on storing; columns that reach past the edge are moved back to the last 4.
+    auto column = [&](const Side& o, int ln) { return 4 * (ln >> 1) + 128 * (wave % (o.T / 128)); };
+    auto column_at = [&](const Side& o, int ln) {              // inside the tile, may be negative
+        const int c = column(o, ln);
+        return o.first + c + 4 > o.rows && !o.narrow ? (int)((int64_t)o.rows - 4 - (int64_t)o.first) : c;
+    };
+    auto first_k = [&](auto km, const Side& o, int ln) {       // k of a group: first_k..+3
+        return decltype(km)::value ? 4 * ((ln & 1) + 2 * (wave / (o.T / 128))) : 4 * (ln & 7);
+    };
+    auto chunk_row = [&](const Side& o, int i) { return (uint32_t)(wave * (o.T / NW) + 8 * i); };     // inside the tile
+    auto past = [&](const Side& o, int i) { return o.first + chunk_row(o, i) >= o.rows; };
+    auto cut = [&](const Side& o, int i) {                     // the chunk, or the first if this one is past the edge, crosses it
+        return past(o, i) ? o.rows - o.first < 8 : o.rows - o.first - chunk_row(o, i) < 8;
+    };
+    auto lane_load = [&](auto km, const Side& o, int ln) -> uint32_t {        // byte offset of the lane from a chunk's base
+        if constexpr (decltype(km)::value) {
+            return (4 * (ln & 1) * (uint32_t)o.ld + (uint32_t)(column_at(o, ln) + (int)(o.first - o.r0))) * 4;
+        } else {
+            return ((uint32_t)(ln >> 3) * (uint32_t)o.ld + 4 * (ln & 7)) * 4;
+        }
+    };
+    auto lane_load_cut = [&](auto km, const Side& o, int ln) -> uint32_t {    // the same in a row-major chunk that crosses the edge
+        if (decltype(km)::value || o.rows - o.first >= (uint64_t)o.T) return 0;
+        const uint32_t left = (uint32_t)(o.rows - o.first), last = (left < 8 ? left : left & 7) - 1, r = (uint32_t)(ln >> 3);
+        return ((r < last ? r : last) * (uint32_t)o.ld + 4 * (ln & 7)) * 4;
+    };
+    // Slot of chunk (row-major) or column (K-major) i.  Column c of 64 lies in slot 16 (c % 4) + c / 4, which spreads the
+    // stores over the banks and gives a lane 4 consecutive columns of a result.  Columns before the tile (it has fewer than 4)
+    // go to its last slot, which is past the edge.
+    auto slot_of = [&](auto km, const Side& o, int ln, int i) {
+        if constexpr (decltype(km)::value) {
+            int c = column_at(o, ln) + i;
+            c = c < 0 ? o.T - 1 : c;
+            return o.slot0 + (c & ~63) + (c & 3) * 16 + ((c >> 2) & 15);
+        } else {
+            return o.slot0 + (int)chunk_row(o, i) + (ln >> 3);
+        }
+    };
+    // LDS: [piece][k / 8][slot][8 k].  A quarter of the k's slots change places by an exclusive or, so that neither the
+    // stores (4 slots of all k, or 16 slots of 4 k, in 32 lanes) nor the 16-byte reads of fragments (16 slots of two quarters
+    // in 32 lanes) meet in a bank.
+    auto turn = [](int quarter) { return (quarter & 1) * 12 ^ (quarter >> 1) * 4; };
+    auto in_plane = [&](auto km, const Side& o, int ln, int slot) {           // byte offset of the thread's 4 k of a slot
+        const int kq = first_k(km, o, ln) / 4;
+        return (uint32_t)((kq >> 1) * kReg + (slot ^ turn(kq >> 1)) * 16 + (kq & 1) * 8);
+    };
+    auto base_of = [&](auto km, const Side& o, int i) {        // of chunk i in the first group
+        if constexpr (decltype(km)::value) return o.mat + (o.k0 + 8 * (wave / (o.T / 128)) + i) * o.ld + o.r0;
+        else return o.mat + (o.first + (past(o, i) ? 0 : chunk_row(o, i))) * o.ld + o.k0;
+    };
+    // Groups whose 32 k all exist are loaded unconditionally, so that the compiler's wait counts leave the newer loads in
+    // flight; the last group of a range goes through guarded loads.
+    uint32_t nf;
+    {
+        const uint64_t k_full = a.K / 32;
+        nf = (uint32_t)(k_full <= g0 ? 0 : k_full - g0 < ng ? k_full - g0 : ng);
+        if ((AKN && a.M < 4) || (BKN && a.N < 4)) nf = 0;
+    }
+    auto load_full = [&](gfloat p, uint64_t step, uint32_t gofs, uint32_t g) {
+        p += g * step;
+        asm volatile("" : "+s"(p));                            // stays a scalar base: no 64-bit lane addresses
+        return *(gvec)((gbyte)p + gofs);
+    };
+    auto load_part = [&](auto km, gfloat p, const Side& o, uint32_t gofs, int i, uint32_t g, int ln) {
+        constexpr bool KM = decltype(km)::value;
+        const gfloat q = (gfloat)((gbyte)(p + g * o.step) + gofs);
+        const uint64_t k = o.k0 + (uint64_t)g * 32 + first_k(km, o, ln);
+        f32x4 x;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            bool ok = k + (KM ? i : e) < a.K;
+            if (KM && o.narrow) ok = ok && column(o, ln) + e < (int)o.rows;
+            x[e] = ok ? q[e] : 0.0f;
+        }
+        return x;
+    };
+    f32x4 xa[CA], xb[CB], za[CA], zb[CB];                      // a group on its way, the first group
+    // 4 k of one slot: chunk i of a row-major operand, column i of a K-major one
+    auto values = [&](auto km, const auto& x, int i) {
+        if constexpr (decltype(km)::value) return f32x4{x[0][i], x[1][i], x[2][i], x[3][i]};
+        else return x[i];
+    };
+    auto largest = [](const f32x4& v) {
+        const float m = __builtin_fmaxf(__builtin_fabsf(v[0]), __builtin_fabsf(v[1]));
+        return __builtin_fmaxf(m, __builtin_fmaxf(__builtin_fabsf(v[2]), __builtin_fabsf(v[3])));
+    };
+
+    if ((AKN && m0 + TM > a.M) || (BKN && n0 + TN > a.N)) {    // slots past the edge that nothing is stored in
+        for (int t = threadIdx.x; t < 2 * kStage / 16; t += THREADS) reinterpret_cast<f32x4*>(smem)[t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    }
+    f32x4 acc[RB][NB];
+    int attempt = 0;
+    bool scan = GENERAL && mode == kAgainExact, reload = false, again = false;
+    for (;;) {
+        const int ln = hide(threadIdx.x & 63);
+        const uint32_t ga = lane_load(km_a, sa, ln), gb = lane_load(km_b, sb, ln);
+        gfloat pa[CA];
+        gfloat pb[CB];
+        const uint32_t ga_cut = lane_load_cut(km_a, sa, ln), gb_cut = lane_load_cut(km_b, sb, ln);
+        bool ca[CA], cb[CB];
+#pragma unroll
+        for (int i = 0; i < CA; ++i) { pa[i] = base_of(km_a, sa, i); ca[i] = !AKN && cut(sa, i); }
+#pragma unroll
+        for (int i = 0; i < CB; ++i) { pb[i] = base_of(km_b, sb, i); cb[i] = !BKN && cut(sb, i); }
+        auto load_a = [&](int i, uint32_t g) { return load_full(pa[i], sa.step, ca[i] ? ga_cut : ga, g); };
+        auto load_b = [&](int i, uint32_t g) { return load_full(pb[i], sb.step, cb[i] ? gb_cut : gb, g); };
+        auto fetch = [&](auto& ya, auto& yb, uint32_t g) {
+            if (g < nf) {                                      // uniform; in the order in which the main loop waits for them
+#pragma unroll
+                for (int i = 0; i < CA; ++i) {
+                    ya[i] = load_a(i, g);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+#pragma unroll
+                for (int i = 0; i < CB; ++i) {
+                    yb[i] = load_b(i, g);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            } else if (g < ng) {
+                const int lp = hide(threadIdx.x & 63);
+#pragma unroll
+                for (int i = 0; i < CA; ++i) ya[i] = load_part(km_a, pa[i], sa, ca[i] ? ga_cut : ga, i, g, lp);
+#pragma unroll
+                for (int i = 0; i < CB; ++i) yb[i] = load_part(km_b, pb[i], sb, cb[i] ? gb_cut : gb, i, g, lp);
+            }
+        };
+        // ---- scales: from a sample of the range, or (second attempt) from all of it
+        if (GENERAL && scan) {                                 // uniform: the largest values of the whole range
+            for (int t = threadIdx.x; t < SLOTS; t += THREADS) mx[t] = 0;
+            float qa[CA], qb[CB];
+#pragma unroll
+            for (int i = 0; i < CA; ++i) qa[i] = 0.0f;
+#pragma unroll
+            for (int i = 0; i < CB; ++i) qb[i] = 0.0f;
+            uint32_t s = 0;
+#pragma unroll 1
+            for (; s + 3 < nf; s += 3) {
+                f32x4 ya[3][CA], yb[3][CB];
+#pragma unroll
+                for (int t = 0; t < 3; ++t) {
+#pragma unroll
+                    for (int i = 0; i < CA; ++i) ya[t][i] = load_a(i, s + t);
+#pragma unroll
+                    for (int i = 0; i < CB; ++i) yb[t][i] = load_b(i, s + t);
+                }
+#pragma unroll
+                for (int t = 0; t < 3; ++t) {
+#pragma unroll
+                    for (int i = 0; i < CA; ++i) qa[i] = __builtin_fmaxf(qa[i], largest(values(km_a, ya[t], i)));
+#pragma unroll
+                    for (int i = 0; i < CB; ++i) qb[i] = __builtin_fmaxf(qb[i], largest(values(km_b, yb[t], i)));
+                }
+            }
+#pragma unroll 1
+            for (; s < ng; ++s) {
+                fetch(za, zb, s);
+#pragma unroll
+                for (int i = 0; i < CA; ++i) qa[i] = __builtin_fmaxf(qa[i], largest(values(km_a, za, i)));
+#pragma unroll
+                for (int i = 0; i < CB; ++i) qb[i] = __builtin_fmaxf(qb[i], largest(values(km_b, zb, i)));
+            }
+            __syncthreads();
+            if (threadIdx.x == 0) mt[2] = 0;
+#pragma unroll
+            for (int i = 0; i < CA; ++i) atomicMax(&mx[slot_of(km_a, sa, ln, i)], __float_as_uint(qa[i]));
+#pragma unroll
+            for (int i = 0; i < CB; ++i) atomicMax(&mx[slot_of(km_b, sb, ln, i)], __float_as_uint(qb[i]));
+            __syncthreads();
+            bool off = false;
+            for (int t = threadIdx.x; t < SLOTS; t += THREADS) {
+                const uint32_t u = mx[t];
+                if (u == 0 || u >= 0x7F800000u) continue;      // infinite: its sums are not finite, whatever the scale
+                const int e = lead_exponent(u) + ex[t];
+                off |= e > kExactTop || (e < kLowest && ex[t] < 127);
+                if (e > kSampleTop + kFar) { wd[t] = 1; mt[3] = 1; }
+            }
+            if (off) mt[2] = 1;
+            __syncthreads();
+            if (mt[2] == 0 && !(mode == kAgainExact && a.accumulate)) {               // uniform: infinities only
+                reload = mode == kAgainExact;                  // the results are stored
+                break;
+            }
+            attempt = 1;
+            fetch(za, zb, 0);
+            fetch(xa, xb, 1);
+        }
+        bool track = false;
+        if (attempt == 0) {
+            fetch(za, zb, 0);
+            for (int t = threadIdx.x; t < SLOTS; t += THREADS) mx[t] = wd[t] = 0;
+            if (threadIdx.x < 4) mt[threadIdx.x] = 0;
+            constexpr int QS = 4;                              // groups of the sample
+            float qa[QS][CA], qb[QS][CB];
+            f32x4 ya[QS][CA], yb[QS][CB];
+            const bool more = ng >= 64 && nf + 1 >= ng;        // uniform: three more groups of a long range
+            // The last one holds the diagonal, if the range does: that of a nearly diagonal matrix (an inverse) towers above the
+            // rest of its rows.
+            auto last_sample = [&](const Side& o, int i) {
+                const uint64_t d = (o.first + chunk_row(o, i)) / 32 - g0;             // wraps below the range
+                return d < nf ? (uint32_t)d : (QS - 1) * (ng / QS);
+            };
+#pragma unroll
+            for (int t = 1; t < QS; ++t) {
+#pragma unroll
+                for (int i = 0; i < CA; ++i) ya[t][i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                for (int i = 0; i < CB; ++i) yb[t][i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            }
+            if (more) {
+#pragma unroll
+                for (int t = 1; t < QS; ++t) {
+#pragma unroll
+                    for (int i = 0; i < CA; ++i) ya[t][i] = load_a(i, t < QS - 1 ? t * (ng / QS) : last_sample(sa, i));
+#pragma unroll
+                    for (int i = 0; i < CB; ++i) yb[t][i] = load_b(i, t < QS - 1 ? t * (ng / QS) : last_sample(sb, i));
+                }
+            }
+            fetch(xa, xb, 1);
+#pragma unroll
+            for (int i = 0; i < CA; ++i) ya[0][i] = za[i];
+#pragma unroll
+            for (int i = 0; i < CB; ++i) yb[0][i] = zb[i];
+#pragma unroll
+            for (int t = 0; t < QS; ++t) {
+#pragma unroll
+                for (int i = 0; i < CA; ++i) qa[t][i] = largest(values(km_a, ya[t], i));
+#pragma unroll
+                for (int i = 0; i < CB; ++i) qb[t][i] = largest(values(km_b, yb[t], i));
+            }
+            // The 8 lanes that hold a row agree on its largest value; a column is spread over wavefronts.
+            auto post = [&](auto km, const Side& o, const auto& q, int n, uint32_t* top) {
+                float all = 0.0f;
+#pragma unroll
+                for (int i = 0; i < n; ++i) {
+                    float m = __builtin_fmaxf(__builtin_fmaxf(q[0][i], q[1][i]), __builtin_fmaxf(q[2][i], q[3][i]));
+                    all = __builtin_fmaxf(all, m);
+                    if constexpr (decltype(km)::value) {
+                        atomicMax(&mx[slot_of(km, o, ln, i)], __float_as_uint(m));
+                    } else {
+                        m = __builtin_fmaxf(m, swap_lanes<0xB1>(m));                  // quad_perm 1 0 3 2
+                        m = __builtin_fmaxf(m, swap_lanes<0x4E>(m));                  // quad_perm 2 3 0 1
+                        m = __builtin_fmaxf(m, swap_lanes<0x141>(m));                 // row_half_mirror
+                        mx[slot_of(km, o, ln, i)] = __float_as_uint(m);
+                    }
+                }
+                atomicMax(top, __float_as_uint(all));
+            };
+            __syncthreads();
+            post(km_a, sa, qa, CA, &mt[0]);
+            post(km_b, sb, qb, CB, &mt[1]);
+            __syncthreads();
+            auto tiny = [&](auto km, const Side& o, const auto& q, int n) {
+#pragma unroll
+                for (int i = 0; i < n; ++i) {
+                    const int slot = slot_of(km, o, ln, i);
+                    const float small = __uint_as_float(mx[slot]) * (1.0f / (1 << kTiny));
+                    uint32_t c = 0;
+#pragma unroll
+                    for (int t = 0; t < QS; ++t) c += q[t][i] < small && q[t][i] > 0.0f;
+                    if (c) atomicAdd(&wd[slot], c);
+                }
+            };
+            tiny(km_a, sa, qa, CA);
+            tiny(km_b, sb, qb, CB);
+            __syncthreads();
+        }
+        auto inside = [&](auto km, const Side& o, int t) {     // a slot in front of the edge
+            const int s = t - o.slot0;
+            return o.first + (decltype(km)::value ? (s & ~63) + 4 * (s & 15) + ((s >> 4) & 3) : s) < o.rows;
+        };
+        bool zero = false;
+        for (int t = threadIdx.x; t < SLOTS; t += THREADS) {
+            const uint32_t u = mx[t], all = mt[t >= TM];
+            if (attempt) {
+                ex[t] = u ? clamp_exponent(kExactTop - lead_exponent(u)) : 0;
+            } else {
+                const bool wide = wd[t] >= 4;
+                wd[t] = wide;
+                if (wide) mt[3] = 1;
+                zero |= u == 0 && (t < TM ? inside(km_a, sa, t) : inside(km_b, sb, t));
+                ex[t] = u ? clamp_exponent(kSampleTop - lead_exponent(u)) : all ? clamp_exponent(kGuessTop - lead_exponent(all)) : 0;
+            }
+            mx[t] = 0;
+        }
+        if (zero) mt[2] = 1;
+        __syncthreads();
+        track = attempt == 0 && mt[2] != 0;                    // uniform
+        if (!GENERAL && track) return kAgain;
+        float fsa[CA], fsb[CB];                                // scales of the thread's slots
+        // Rows past the edge are scaled by zero: products with zero take less of the power that limits the clock.
+        auto scale_of = [&](auto km, const Side& o, int i) {
+            const uint64_t row = decltype(km)::value ? o.first + (int64_t)(column_at(o, ln) + i) : o.first + chunk_row(o, i) + (ln >> 3);
+            return row < o.rows ? __builtin_ldexpf(1.0f, ex[slot_of(km, o, ln, i)]) : 0.0f;
+        };
+#pragma unroll
+        for (int i = 0; i < CA; ++i) fsa[i] = scale_of(km_a, sa, i);
+#pragma unroll
+        for (int i = 0; i < CB; ++i) fsb[i] = scale_of(km_b, sb, i);
+        // LDS byte offset of the thread's columns; of its first row: the others are 8 slots apart, which the exclusive or may turn
+        // into 8 back (bit 7 of the offset).
+        uint32_t wa[AKN ? CA : 1], wb[BKN ? CB : 1];
+#pragma unroll
+        for (int i = 0; i < (AKN ? CA : 1); ++i) wa[i] = in_plane(km_a, sa, ln, slot_of(km_a, sa, ln, i));
+#pragma unroll
+        for (int i = 0; i < (BKN ? CB : 1); ++i) wb[i] = in_plane(km_b, sb, ln, slot_of(km_b, sb, ln, i));
+
+        // Two fp16 pieces of 4 values.  `rare`: there are slots without a sample, whose largest value is wanted.
+        auto stash = [&](auto km, auto rare, const auto& x, const Side& o, const uint32_t* w, float scale, int i, uint32_t stage) {
+            const f32x4 v = values(km, x, i);
+            u32x2 p0, p1;
+#pragma unroll
+            for (int e = 0; e < 4; e += 2) {
+                const f16x2 h = __builtin_convertvector((f32x2{v[e] * scale, v[e + 1] * scale}), f16x2);
+                p0[e / 2] = __builtin_bit_cast(uint32_t, h);
+                p1[e / 2] = __builtin_bit_cast(uint32_t, (f16x2{(_Float16)__builtin_fmaf(v[e], scale, -(float)h[0]),
+                                                                (_Float16)__builtin_fmaf(v[e + 1], scale, -(float)h[1])}));
+            }
+            unsigned char* st = smem + (decltype(km)::value ? w[i] + stage : ((w[0] + stage) ^ ((i & 1) * 128)) + (i >> 1) * 256);
+            if constexpr (decltype(rare)::value) {
+                if (track) atomicMax(&mx[slot_of(km, o, hide(threadIdx.x & 63), i)], __float_as_uint(largest(v * scale)));
+            }
+            *reinterpret_cast<u32x2*>(st) = p0;
+            *reinterpret_cast<u32x2*>(st + kPlane) = p1;
+        };
+
+        // ---- fragments: lane l holds k 8 (l / 16)..+7 of slot l % 16 of a block of 16
+        const uint32_t fofs = (ln >> 4) * kReg + ((ln & 15) ^ turn(ln >> 4)) * 16;
+        const uint32_t a_ofs = fofs + wm * RB * 256, b_ofs = fofs + (TM + wn * NB * 16) * 16;
+        struct Frag { f16x8 p[2]; };
+        auto load = [&](Frag& f, uint32_t at, int block) {
+#pragma unroll
+            for (int q = 0; q < 2; ++q) f.p[q] = *reinterpret_cast<const f16x8*>(smem + at + (q * kPlane + block * 256));
+        };
+#pragma unroll
+        for (int i = 0; i < RB; ++i)
+#pragma unroll
+            for (int j = 0; j < NB; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+
+        // ---- pipeline
+        const std::true_type yes;
+        const std::false_type no;
+        const std::integral_constant<bool, GENERAL> rare;
+#pragma unroll
+        for (int i = 0; i < CA; ++i) stash(km_a, rare, za, sa, wa, fsa[i], i, 0);
+#pragma unroll
+        for (int i = 0; i < CB; ++i) stash(km_b, rare, zb, sb, wb, fsb[i], i, 0);
+        Frag fa[2], fb[NB];
+        uint32_t cur = 0, g = 0;
+        auto group = [&](auto full, auto rare, uint32_t gi) {
+            constexpr bool FULL = decltype(full)::value;
+            const uint32_t nxt = kStage - cur;
+            const uint32_t a_cur = a_ofs + cur;
+#pragma unroll
+            for (int i = 0; i < RB; ++i) {
+                if (i + 1 < RB) {
+                    load(fa[(i + 1) & 1], a_cur, i + 1);
+#pragma unroll
+                    for (int q = 0; q < NC; ++q) {
+                        if (q * (RB - 1) / NC != i) continue;
+                        if (q < CA) {
+                            stash(km_a, rare, xa, sa, wa, fsa[q], q, nxt);
+                            if constexpr (FULL) {
+                                if (!AKN) xa[q] = load_a(q, gi + 2);
+                                else if (q == CA - 1) {
+#pragma unroll
+                                    for (int r = 0; r < CA; ++r) xa[r] = load_a(r, gi + 2);
+                                }
+                            }
+                        } else {
+                            const int r = q - CA;
+                            stash(km_b, rare, xb, sb, wb, fsb[r], r, nxt);
+                            if constexpr (FULL) {
+                                if (!BKN) xb[r] = load_b(r, gi + 2);
+                                else if (r == CB - 1) {
+#pragma unroll
+                                    for (int r2 = 0; r2 < CB; ++r2) xb[r2] = load_b(r2, gi + 2);
+                                }
+                            }
+                        }
+                    }
+                } else {
+                    if constexpr (!FULL) fetch(xa, xb, gi + 2);
+                    wait_lds();
+                    f32_barrier();
+                    load(fa[0], a_ofs + nxt, 0);
+                }
+                // products of pieces, small terms first.  The last block of rows goes column by column: the fragments of B
+                // are replaced as they fall free, so that one set of them is enough.
+                constexpr int qa[3] = {1, 0, 0}, qb[3] = {0, 1, 0};
+                auto mma = [&](int j, int t) {
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fa[i & 1].p[qa[t]], fb[j].p[qb[t]], acc[i][j], 0, 0, 0);
+                };
+                if (i + 1 < RB) {
+#pragma unroll
+                    for (int t = 0; t < 3; ++t)
+#pragma unroll
+                        for (int j = 0; j < NB; ++j) mma(j, t);
+                } else {
+#pragma unroll
+                    for (int j = 0; j < NB; j += 2) {
+#pragma unroll
+                        for (int t = 0; t < 3; ++t) { mma(j, t); mma(j + 1, t); }
+                        load(fb[j], b_ofs + nxt, j);
+                        load(fb[j + 1], b_ofs + nxt, j + 1);
+                    }
+                }
+#pragma unroll
+                for (int q = 0; q < 3 * NB / 2; ++q) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);               // two matrix instructions
+                    __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);               // vector arithmetic
+                    __builtin_amdgcn_sched_group_barrier(0x300, 1, 0);               // one LDS read or write
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            cur = nxt;
+        };
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0x0F70);                    // vmcnt == 0, or the loop's waits would also be for loads before it
+        __builtin_amdgcn_sched_barrier(0);
+        wait_lds();
+        f32_barrier();
+#pragma unroll
+        for (int j = 0; j < NB; ++j) load(fb[j], b_ofs, j);
+        load(fa[0], a_ofs, 0);
+        for (; g + 2 < nf; ++g) group(yes, rare, g);
+        for (; g < ng; ++g) group(no, rare, g);
+
+        // ---- check of the scales
+        if (attempt) break;
+        __syncthreads();
+        if (threadIdx.x == 0) mt[2] = 0;
+        __syncthreads();
+        float sum = 0.0f;                                      // a value too large for its scale: none of its sums is finite
+#pragma unroll
+        for (int i = 0; i < RB; ++i)
+#pragma unroll
+            for (int j = 0; j < NB; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) sum = __builtin_fmaf(acc[i][j][e], 0.0f, sum);
+        bool off = !(sum == 0.0f);
+        if (track)
+            for (int t = threadIdx.x; t < SLOTS; t += THREADS) off |= mx[t] != 0 && lead_exponent(mx[t]) < kLowest && ex[t] < 127;
+        if (off) mt[2] = 1;
+        __syncthreads();
+        if (mt[2] == 0) break;                                 // uniform
+        if constexpr (!GENERAL) {
+            if (a.accumulate) return kAgainExact;
+            again = true;
+            break;
+        }
+        scan = true;
+        __syncthreads();
+    }
+
+    // ---- results
+    {
+        const int ln = hide(threadIdx.x & 63), lq = ln >> 4, lc = ln & 15;
+        auto a_row = [&](int i, int r) {                       // row of A in slot r of the wavefront's block i of 16
+            const int s = wm * RB * 16 + i * 16 + r;
+            return m0 + (AKN ? (s & ~63) + 4 * (s & 15) + ((s >> 4) & 3) : s);
+        };
+        auto b_col = [&](int j) {                              // column of C in block j of the lane
+            const int s = wn * NB * 16 + j * 16 + lc;
+            return n0 + (BKN ? (s & ~63) + 4 * (s & 15) + ((s >> 4) & 3) : s);
+        };
+        const int* const ea = ex + wm * RB * 16 + 4 * lq;
+        const int* const eb = ex + TM + wn * NB * 16 + lc;
+        if (GENERAL && reload) {                               // uniform
+#pragma unroll
+            for (int i = 0; i < RB; ++i)
+#pragma unroll
+                for (int j = 0; j < NB; ++j)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const uint64_t row = a_row(i, 4 * lq + e), col = b_col(j);
+                        acc[i][j][e] = row < a.M && col < a.N ? __builtin_ldexpf(a.C[row * a.ldc + col], ea[i * 16 + e] + eb[j * 16]) : 0.0f;
+                    }
+        }
+        // Sums to be contracted again on the fp32 matrix instructions, 4 bits each (e) of the 4 blocks of a row of blocks.
+        uint32_t todo[(RB + 1) / 2];
+#pragma unroll
+        for (int i = 0; i < (RB + 1) / 2; ++i) todo[i] = 0;
+        if (GENERAL) {                                         // otherwise they are finite, or this is not the end of it
+#pragma unroll
+            for (int i = 0; i < RB; ++i)
+#pragma unroll
+                for (int j = 0; j < NB; ++j)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (!__builtin_isfinite(acc[i][j][e])) todo[i / 2] |= 1u << ((i & 1) * 16 + j * 4 + e);
+        }
+        if (mt[3] != 0) {                                      // uniform: slots of wide range
+            const uint64_t kr = (g0 + ng) * 32 < a.K ? (uint64_t)ng * 32 : a.K - g0 * 32;
+            const float low = (float)kr * (attempt ? 2.0f : 1.0f / 64.0f);        // 2^10 2^-25 kr twice 2^15, 2^8
+            const uint32_t* const wa = wd + wm * RB * 16 + 4 * lq;
+            const uint32_t* const wb = wd + TM + wn * NB * 16 + lc;
+#pragma unroll 1
+            for (int i = 0; i < RB; ++i)
+#pragma unroll 1
+                for (int j = 0; j < NB; ++j) {
+                    f32x4 x;
+#pragma unroll
+                    for (int i2 = 0; i2 < RB; ++i2)
+#pragma unroll
+                        for (int j2 = 0; j2 < NB; ++j2)
+                            if (i2 == i && j2 == j) x = acc[i2][j2];
+                    uint32_t f = 0, bad = 0;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        if (__builtin_fabsf(x[e]) < low) f |= 1u << e;
+                        const uint32_t in_row = __builtin_popcount((uint32_t)(__ballot(f >> e & 1) >> (16 * lq)) & 0xFFFFu);
+                        if (in_row >= 8 && wa[i * 16 + e] != 0) bad |= 1u << e;
+                    }
+                    int in_col = __builtin_popcount(f);
+                    in_col += __shfl_xor(in_col, 16);
+                    in_col += __shfl_xor(in_col, 32);
+                    if (in_col >= 8 && wb[j * 16] != 0) bad = 15;
+                    bad = (bad & f) << ((i & 1) * 16 + j * 4);
+#pragma unroll
+                    for (int i2 = 0; i2 < (RB + 1) / 2; ++i2)
+                        if (i2 == i / 2) todo[i2] |= bad;
+                }
+        }
+        const bool interior = m0 + TM <= a.M && n0 + TN <= a.N && !a.accumulate;         // uniform
+        const bool quads = BKN && interior && a.ldc % 4 == 0 && (reinterpret_cast<uintptr_t>(a.C) & 15) == 0;
+#pragma unroll
+        for (int i = 0; i < RB; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const uint64_t row = a_row(i, 4 * lq + e);
+                const int er = ea[i * 16 + e];
+                float v[NB];
+#pragma unroll
+                for (int j = 0; j < NB; ++j) v[j] = __builtin_ldexpf(acc[i][j][e], -(er + eb[j * 16]));
+                float* const c = a.C + row * a.ldc;
+                if (quads) {
+                    *reinterpret_cast<f32x4*>(c + b_col(0)) = f32x4{v[0], v[1], v[2], v[3]};
+                } else {
+#pragma unroll
+                    for (int j = 0; j < NB; ++j) {
+                        const uint64_t col = b_col(j);
+                        if (interior) c[col] = v[j];
+                        else if (row < a.M && col < a.N && !(a.accumulate && (todo[i / 2] >> ((i & 1) * 16 + j * 4 + e) & 1)))
+                            c[col] = a.accumulate ? c[col] + v[j] : v[j];
+                    }
+                }
+            }
+        if (again) return kAgainExact;
+        uint32_t any = 0;
+#pragma unroll
+        for (int i = 0; i < (RB + 1) / 2; ++i) any |= todo[i];
+        // Blocks with such sums are contracted again with v_mfma_f32_16x16x4_f32, straight from memory, and only those sums
+        // replaced.  A lane holds k 4 (lane / 16)..+3 of every 16 (the order inside a contraction is free).
+        if (__builtin_expect(__any(any != 0), 0)) {
+            const uint64_t k_begin = g0 * 32, k_end = (g0 + ng) * 32 < a.K ? (g0 + ng) * 32 : a.K;
+#pragma unroll 1
+            for (int t = 0; t < RB * NB; ++t) {
+                const int i = t / NB, j = t % NB;
+                uint32_t bad = 0;
+#pragma unroll
+                for (int q = 0; q < (RB + 1) / 2; ++q) bad = q == i / 2 ? todo[q] : bad;
+                bad = bad >> ((i & 1) * 16 + j * 4) & 15u;
+                uint64_t row = a_row(i, lc), col = b_col(j);
+                bool use = false;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) use |= (bad >> e & 1) && a_row(i, 4 * lq + e) < a.M && col < a.N;
+                if (!__any(use)) continue;                     // uniform
+                row = row < a.M ? row : a.M - 1;               // past the edge: never stored
+                const uint64_t colc = col < a.N ? col : a.N - 1;
+                const gfloat pa = (gfloat)(AKN ? a.A + row : a.A + row * a.lda);
+                const gfloat pb = (gfloat)(BKN ? a.B + colc : a.B + colc * a.ldb);
+                f32x4 sum{0.0f, 0.0f, 0.0f, 0.0f};
+                auto contract = [&](auto all, uint64_t k0, auto n) {                  // 16 n of k, loaded together
+                    f32x4 ya[decltype(n)::value], yb[decltype(n)::value];
+#pragma unroll
+                    for (int u = 0; u < decltype(n)::value; ++u) {
+                        const uint64_t k = k0 + 16 * u + 4 * lq;
+                        if constexpr (decltype(all)::value && !AKN) ya[u] = *(gvec)(pa + k);
+                        if constexpr (decltype(all)::value && !BKN) yb[u] = *(gvec)(pb + k);
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const bool ok = decltype(all)::value || k + q < k_end;
+                            if constexpr (!decltype(all)::value || AKN) ya[u][q] = ok ? pa[AKN ? (k + q) * a.lda : k + q] : 0.0f;
+                            if constexpr (!decltype(all)::value || BKN) yb[u][q] = ok ? pb[BKN ? (k + q) * a.ldb : k + q] : 0.0f;
+                        }
+                    }
+#pragma unroll
+                    for (int u = 0; u < decltype(n)::value; ++u)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) sum = __builtin_amdgcn_mfma_f32_16x16x4f32(ya[u][q], yb[u][q], sum, 0, 0, 0);
+                };
+                uint64_t k0 = k_begin;
+                for (; k0 + 128 <= k_end; k0 += 128) contract(std::true_type{}, k0, std::integral_constant<int, 8>{});
+                for (; k0 < k_end; k0 += 16) contract(std::false_type{}, k0, std::integral_constant<int, 1>{});
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (bad >> e & 1) {
+                        const uint64_t r = a_row(i, 4 * lq + e);
+                        if (r < a.M && col < a.N) {
+                            float* c = a.C + r * a.ldc + col;
+                            *c = a.accumulate ? *c + sum[e] : sum[e];
+                        }
+                    }
+            }
+        }
+    }
+    return kDone;
+}
+
+template <int RB, int NB, int WR, int WC, bool AKN, bool BKN>
+__device__ __attribute__((noinline)) void pair_general(GemmF32Args a, lds_byte lds, int mode) {
+    // arguments of a function that is not inlined arrive in vector registers
+    uint32_t w[sizeof(a) / 4];
+    __builtin_memcpy(w, &a, sizeof(a));
+#pragma unroll
+    for (uint32_t i = 0; i < sizeof(a) / 4; ++i) w[i] = __builtin_amdgcn_readfirstlane(w[i]);
+    __builtin_memcpy(&a, w, sizeof(a));
+    const uint32_t at = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)lds);
+    pair_tile<RB, NB, WR, WC, AKN, BKN, true>(a, (lds_byte)(uintptr_t)at, __builtin_amdgcn_readfirstlane(mode));
+}
+
+template <int RB, int NB, int WR, int WC, bool AKN, bool BKN>
+__global__ void __launch_bounds__(64 * WR * WC, 2) gemm_pair_kernel(GemmF32Args a) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int mode = pair_tile<RB, NB, WR, WC, AKN, BKN, false>(a, (lds_byte)smem, 0);
+    if (mode != kDone) {                                       // uniform
+        __syncthreads();
+        pair_general<RB, NB, WR, WC, AKN, BKN>(a, (lds_byte)smem, mode);
+    }
+}
+
+template <int RB, int NB, int WR, int WC, bool AKN, bool BKN>
+static hipError_t launch_pair(GemmF32Args a, hipStream_t st) {
+    constexpr uint64_t TM = 16 * RB * WR, TN = 16 * NB * WC;
+    constexpr uint64_t lds = 2 * 8 * (TM + TN) * 16 + (TM + TN) * 12 + 16;
+    static_assert(lds <= kLdsBytes, "LDS");
+    a.tiles_m = (uint32_t)ceil_div(a.M, TM);
+    a.tiles_n = (uint32_t)ceil_div(a.N, TN);
+    if (a.lower_only && a.tiles_m != a.tiles_n) return hipErrorInvalidValue;
+    const uint64_t total = (a.lower_only ? (uint64_t)a.tiles_m * (a.tiles_m + 1) / 2 : (uint64_t)a.tiles_m * a.tiles_n) * a.splits;
+    if (total == 0 || total > 0x7FFFFFFFull) return hipErrorInvalidValue;
+    static LdsOptIn opt_in;
+    hipError_t e = allow_large_lds(opt_in, reinterpret_cast<const void*>(gemm_pair_kernel<RB, NB, WR, WC, AKN, BKN>));
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((gemm_pair_kernel<RB, NB, WR, WC, AKN, BKN>), dim3((uint32_t)total), dim3(64 * WR * WC), lds, st, a);
+    return hipGetLastError();
+}
+
+hipError_t gemm_f32_pair(bool a_kn, bool b_kn, int tile, const GemmF32Args& a, hipStream_t st) {
+    switch (tile) {
+        case kTile256:
+            if (a_kn) return launch_pair<8, 4, 2, 4, true, true>(a, st);
+            if (b_kn) return launch_pair<8, 4, 2, 4, false, true>(a, st);
+            return launch_pair<8, 4, 2, 4, false, false>(a, st);
+        case kTile128x256:
+            if (a_kn) return hipErrorInvalidValue;
+            if (b_kn) return launch_pair<4, 4, 2, 4, false, true>(a, st);
+            return launch_pair<4, 4, 2, 4, false, false>(a, st);
+        case kTile64:
+            if (b_kn) return hipErrorInvalidValue;
+            return launch_pair<4, 4, 1, 8, false, false>(a, st);
+        default:
+            if (a_kn) return launch_pair<4, 4, 2, 2, true, true>(a, st);
+            if (b_kn) return launch_pair<4, 4, 2, 2, false, true>(a, st);
+            return launch_pair<4, 4, 2, 2, false, false>(a, st);
+    }
+}
+
+}  // namespace grass

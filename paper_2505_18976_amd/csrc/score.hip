@@ -342,7 +342,7 @@ static GaussPlan gauss_plan(uint64_t n, uint64_t p, uint32_t k, uint64_t p_chunk
     G.bf16_path = mode == 1 && n >= 128 && k >= 128;
     const uint64_t first = G.pc < p ? G.pc : p;
     G.splits = 1;
-    G.f32 = GemmPlan{kTile128, 1};
+    G.f32 = GemmPlan{kTile128, 1, false};
     if (mode == 0) { G.f32 = gemm_f32_plan(false, false, n, k, first, 0, false, 8); G.splits = G.f32.splits; }
     else if (G.bf16_path && first % 32 == 0) G.splits = gemm_dma_splits(n, k, first, 8);
     size_t o = 0;
@@ -399,8 +399,8 @@ extern "C" grass_status grass_gauss_project(const float* g, uint64_t n, uint64_t
         float* P = reinterpret_cast<float*>(base + G.off_p);
         launch_gauss_matrix(sub, p, k, p0, cur, cur, false, P, pc, hs);
         if (compute_mode == 0) {
-            GemmPlan plan = G.f32;                             // a short tail uses fewer of the K ranges
-            if (plan.splits > ceil_div(cur, 32)) plan.splits = (uint32_t)ceil_div(cur, 32);
+            GemmPlan plan = G.f32;
+            if (p0 != 0 && cur != pc) plan = gemm_f32_plan(false, false, n, k, cur, 0, false, G.splits);     // a short tail
             float* C = G.splits > 1 ? partials : out;          // one range left: into partial sum 0
             if (gemm_f32(false, false, g + p0, P, C, n, k, cur, ldg, pc, G.splits > 1 ? k : ldo, accumulate, 0, plan, partials,
                          hs) != hipSuccess)

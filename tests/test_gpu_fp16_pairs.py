@@ -1,0 +1,170 @@
+"""fp32 products as products of two fp16 pieces (contractions of 256 and more per workgroup): every tile and operand order,
+edges, and the scales of rows that a sample does not tell the truth about.
+
+Error bound of a sum: an operand is off by 2^-23 of itself (its two pieces) or by 2^-30 of the largest value of its row in
+the sample, which is at most that of the row (the end of fp16's range); the product that is left out is below 2^-22 |a b|;
+every matrix instruction adds 32 products with an error of at most one unit in the last place of a sum that never exceeds
+sum |a b|, three of them per 32 k; up to 64 K ranges are added:
+|got - exact| <= (2^-23 (3 ceil(K / 32) + 64) + 2^-21) sum |a b| + 2^-30 (max |a| sum |b| + max |b| sum |a|) + 2^-144,
+the last term because a result and the partial sums of up to 64 K ranges are whole multiples of 2^-149."""
+import pytest
+import torch
+
+import synth
+
+pytestmark = pytest.mark.gpu
+BIG = torch.finfo(torch.float32).max
+
+
+@pytest.fixture(scope="module")
+def grass():
+    import paper_2505_18976_amd as g
+    g.load_library()
+    return g
+
+
+def _dev():
+    return torch.device("cuda:0")
+
+
+def _bound(A, B, scale=True):
+    a, b = A.double().abs(), B.double().abs()
+    out = (2.0 ** -23 * (3 * -(-A.shape[1] // 32) + 64) + 2.0 ** -21) * (a @ b.T.contiguous()) + 2.0 ** -144
+    if scale:
+        out += 2.0 ** -30 * (a.amax(1)[:, None] * b.sum(1)[None] + a.sum(1)[:, None] * b.amax(1)[None])
+    return out
+
+
+def _check(got, A, B, scale=True):
+    """got = A B^T within the bound; the largest deviation over the bound."""
+    ref = A.double() @ B.double().T.contiguous()
+    ok = ref.abs() <= BIG
+    off = ((got.double() - ref).abs() / _bound(A, B, scale))[ok]
+    assert float(off.max()) <= 1.0
+    return ref
+
+
+@pytest.mark.parametrize("M,N,K", [(2_048, 8_192, 256), (2_040, 8_190, 300),          # 256 x 256
+                                   (130, 130, 4_100), (1, 1, 257), (129, 1_000, 1_023),     # 128 x 128
+                                   (100, 70_001, 288), (128, 65_536, 260),            # 128 x 256
+                                   (33, 100_000, 300), (64, 40_001, 511), (5, 33_000, 256)])   # 64 x 512
+@pytest.mark.parametrize("pad", [0, 1])
+def test_row_major(grass, M, N, K, pad):
+    te = synth.dense_normal(M, K + pad, seed=1, device=_dev())[:, :K]
+    tr = synth.dense_normal(N, K + 3 * pad, seed=2, device=_dev())[:, :K]
+    for ws in ({}, {"ws": None}):
+        got = grass.grass_score(tr, te, **ws)
+        ref = _check(got, te, tr)
+        if K <= 300:                         # seen 2.1e-7; the products of pieces left out at most 4e-8, one more lost 1e-4
+            assert float((got.double() - ref).norm() / ref.norm()) <= 3e-7
+
+
+@pytest.mark.parametrize("N,k", [(300, 4_000), (290, 4_001), (257, 4_002), (300, 4_003), (300, 130), (300, 131), (300, 257),
+                                 (300, 1), (300, 2), (299, 3), (300, 4), (300, 5), (4_000, 190), (70_001, 67)])
+def test_both_operands_k_major(grass, N, k):
+    G = synth.dense_normal(N, k, seed=3, device=_dev())
+    F = grass.grass_fim(G)
+    assert torch.equal(F, F.T)
+    _check(F * N, G.T, G.T)                  # the scaling by 1 / N and back adds two roundings, inside the bound's 64
+
+
+@pytest.mark.parametrize("m,n,p", [(3, 300, 1), (2, 257, 3), (3, 300, 5), (3, 300, 4_099), (256, 300, 65_536), (255, 299, 65_533),
+                                   (100, 290, 70_002)])
+def test_second_operand_k_major(grass, m, n, p):
+    """The backward product of a Selective-Mask step: its gradient is compared with that of double precision.  Masked scores,
+    their correlation and the row c behind them keep 1e-5 of the largest entry."""
+    G, Gt = synth.dense_normal(n, p, seed=7, device=_dev()), synth.dense_normal(m, p, seed=8, device=_dev())
+    S = synth.dense_normal(1, p, seed=9, device=_dev(), std=0.5).reshape(-1).contiguous()
+    A = synth.dense_normal(m, n, seed=10, device=_dev())
+    grad, _ = grass.grass_selective_mask_grad(G, Gt, A, S, 1e-3, 1.0)
+    sig, g, gt, a = torch.sigmoid(S.double()), G.double(), Gt.double(), A.double()
+    b = (gt * sig ** 2) @ g.T.contiguous()
+    da, db = a - a.mean(1, keepdim=True), b - b.mean(1, keepdim=True)
+    na, nb = da.norm(dim=1, keepdim=True), db.norm(dim=1, keepdim=True)
+    c = (da / (na * nb) - (da * db).sum(1, keepdim=True) / (na * nb ** 3) * db) / m
+    ds = sig * (1 - sig)
+    ref = 2 * sig * ds * (gt * (c @ g)).sum(0) - 1e-3 * ds
+    assert float((grad.double() - ref).abs().max()) <= 1e-5 * float(ref.abs().max())
+
+
+def _odd_rows(X):
+    """Rows that a sample of the first 32 k (and of three more groups in long ranges) misjudges."""
+    K = X.shape[1]
+    X[0] *= 2.0 ** -120
+    X[1] *= 2.0 ** 40
+    X[2] = 0.0
+    X[3, :K - 3] = 0.0                       # nothing but the last three, of ordinary size
+    X[4, :100] = 0.0
+    X[4, 100:] *= 2.0 ** -40                 # zero in the sample and far below the rest of the tile
+    X[5, 40] = 2.0 ** 7                      # above the sample: fits
+    X[6, 41] = 2.0 ** 12                     # does not
+    X[7, 42] = 2.0 ** 22                     # wide range
+    X[8, 43] = BIG
+    X[9, 200:] *= 2.0 ** -20
+    X[10, 3] = 2.0 ** 25                     # in the sample
+    X[11] = 2.0 ** -149 * torch.randint(-5, 6, (K,), device=X.device)
+    return X
+
+
+@pytest.mark.parametrize("M,N,K", [(40, 300, 257), (300, 40, 512), (20, 40_000, 300), (130, 70_001, 260), (2_048, 8_192, 256),
+                                   (60, 200, 5_000)])
+def test_rows_that_the_sample_misjudges(grass, M, N, K):
+    te = _odd_rows(synth.dense_normal(M, K, seed=11, device=_dev()))
+    tr = _odd_rows(synth.dense_normal(N, K, seed=12, device=_dev()))
+    for a, b in ((te, synth.dense_normal(N, K, seed=13, device=_dev())), (synth.dense_normal(M, K, seed=14, device=_dev()), tr)):
+        for ws in ({}, {"ws": None}):
+            _check(grass.grass_score(b, a, **ws), a, b)
+
+
+@pytest.mark.parametrize("spike", [2.0 ** 13, 2.0 ** 22, 2.0 ** 40, BIG])
+@pytest.mark.parametrize("M,N,K", [(40, 300, 300), (300, 5_000, 256), (60, 200, 5_000)])
+def test_large_values_that_meet_zeros(grass, spike, M, N, K):
+    """A row with one huge value where the other operand is zero, in the sample and outside: the sums are those of the rest, to
+    the bits of the rest."""
+    te, tr = synth.dense_normal(M, K, seed=15, device=_dev()), synth.dense_normal(N, K, seed=16, device=_dev())
+    tr[:, 5] = tr[:, 100] = 0.0
+    te[1, 5], te[17, 100] = spike, -spike
+    got = grass.grass_score(tr, te)
+    _check(got, te, tr, scale=False)
+    _check(grass.grass_score(te, tr), tr, te, scale=False)
+
+
+@pytest.mark.parametrize("N,k", [(300, 130), (400, 1_003)])
+def test_large_values_that_meet_zeros_k_major(grass, N, k):
+    G = synth.dense_normal(N, k, seed=17, device=_dev())
+    G[5] = G[100] = 0.0
+    G[5, 3], G[100, 77] = BIG / 4, 2.0 ** 30
+    ref = G.T.double() @ G.double()
+    got = grass.grass_fim(G).double() * N
+    ok = ref.abs() <= BIG
+    assert bool(((got - ref).abs() <= _bound(G.T, G.T, scale=False))[ok].all()) and bool(torch.isinf(got[~ok]).all())
+
+
+@pytest.mark.parametrize("M,N,K", [(70, 90, 20_001), (40, 5_000, 515), (300, 50_000, 270), (2_048, 8_192, 257)])
+def test_non_finite_operands(grass, M, N, K):
+    te, tr = synth.dense_normal(M, K, seed=31, device=_dev()), synth.dense_normal(N, K, seed=32, device=_dev())
+    for x in (te, tr):
+        x[3, 5], x[4, K - 1], x[7, 9] = float("inf"), float("nan"), float("-inf")
+        x[8, 1], x[8, K - 1] = float("inf"), float("-inf")
+        x[9, 40] = 2.0 ** 30                 # next to infinities, a scale that has to be found again
+    ref = te.double() @ tr.double().T.contiguous()
+    for ws in ({}, {"ws": None}):
+        got = grass.grass_score(tr, te, **ws).double()
+        assert torch.equal(torch.isnan(got), torch.isnan(ref)) and torch.equal(torch.isinf(got), torch.isinf(ref))
+        assert torch.equal(got[torch.isinf(ref)], ref[torch.isinf(ref)])
+        ok = torch.isfinite(ref)
+        te0, tr0 = te.nan_to_num(0.0, 0.0, 0.0), tr.nan_to_num(0.0, 0.0, 0.0)
+        assert bool(((got - ref).abs() <= _bound(te0, tr0))[ok].all())
+
+
+def test_accumulated_chunks(grass):
+    """Gaussian projection in column chunks that are added up, the last one short; infinities and a late large value."""
+    p, k = 1_300, 40
+    g = synth.dense_normal(20, p, seed=34, device=_dev())
+    g[3, 5], g[4, 600], g[7, 900], g[8, 700] = float("inf"), float("nan"), float("-inf"), 2.0 ** 20
+    P = grass.grass_gauss_matrix(0, 9, p, k, 0, p, device=_dev())
+    got = grass.grass_gauss_project(g, k, 0, 9, 512, 0).double()
+    ref = g.double() @ P.double().T.contiguous()
+    assert torch.equal(torch.isnan(got), torch.isnan(ref)) and torch.equal(torch.isinf(got), torch.isinf(ref))
+    ok = torch.isfinite(ref)
+    assert bool(((got - ref).abs() <= _bound(g.nan_to_num(0.0, 0.0, 0.0), P))[ok].all())
