@@ -24,6 +24,7 @@ namespace grass {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
@@ -175,7 +176,7 @@ __global__ void __launch_bounds__(kBf16Threads) gemm_bf16_nt_kernel(GemmBf16Args
 // 19 % faster than four stages of 64-byte rows, depending on shape and data.
 // Rows are stored unpadded; the
 // 16-byte chunk kc of row r sits at position kc ^ ((r >> 1) & 7), which makes the
-// fragment reads of 16 consecutive rows hit the 16 distinct 16-byte bank groups.
+// fragment reads of 16 rows hit the 16 distinct 16-byte bank groups.
 constexpr int kDmaStages = 2;
 constexpr int kDmaStageBytes = (TM + TN) * 128;        // 64 KB
 
@@ -193,7 +194,10 @@ __device__ __forceinline__ void bare_barrier() {
     asm volatile("" ::: "memory");
 }
 
-// v_mfma_f32_32x32x16_bf16, a slice is 32 elements.
+// v_mfma_f32_16x16x32_bf16, a slice is 32 elements.  The kernel is bound by the power that the matrix cores and the data on
+// the way to them draw, and this instruction takes less of it per operation than v_mfma_f32_32x32x16_bf16 (half the traffic
+// of the accumulators): on their own, with random data, 1,876 against 1,680 TFLOP/s.  1,024 x 65,536 x 4,096 513 -> 482 us,
+// 8,192^3 881 -> 833, 100 x 30,001 x 4,096 80 -> 76.
 struct GemmDmaArgs {
     const void* A;        // M x K
     const void* B;        // N x K
@@ -215,7 +219,7 @@ __global__ void __launch_bounds__(kBf16Threads) gemm_dma_kernel(GemmDmaArgs a) {
     constexpr int SK = 64 / ESZ;                     // elements per slice (64-byte rows)
     constexpr int TMk = SKINNY ? 128 : TM, TNk = SKINNY ? 384 : TN;                    // tile of C
     constexpr int WM = TMk / 2, WN = TNk / 4;        // wavefront tile
-    constexpr int MI = WM / 32, NJ = WN / 32;        // MFMA tiles per wavefront
+    constexpr int MI = WM / 16, NJ = WN / 16, MH = MI / 2;      // MFMA tiles per wavefront; rows of them per step
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 2, wn = wave & 3;
 
@@ -274,34 +278,38 @@ __global__ void __launch_bounds__(kBf16Threads) gemm_dma_kernel(GemmDmaArgs a) {
         }
     };
 
-    // fragment addresses: row*128 + ((2*ks + lane/32) ^ swizzle) * 16, the swizzle depends on lane only
+    // fragments: lane l holds k 8 (l / 16)..+7 of row l % 16; address row*128 + ((4*ks + lane/16) ^ swizzle) * 16, the swizzle
+    // depends on lane only
     const int fl = (lane >> 1) & 7;
-    const int a_row = (wm * WM + (lane & 31)) * 128;
-    const int b_row = (TMk + wn * WN + (lane & 31)) * 128;
-    struct RawFrags { bf16x8 a[MI], b[NJ]; };
-    auto load_frags = [&](RawFrags& f, int stage, int ks) {
-        const unsigned char* base = smem + stage * kDmaStageBytes + (((2 * ks + (lane >> 5)) ^ fl) * 16);
+    const int a_row = (wm * WM + (lane & 15)) * 128;
+    const int b_row = (TMk + wn * WN + (lane & 15)) * 128;
+    struct FragsA { bf16x8 x[MH]; };
+    struct FragsB { bf16x8 x[NJ]; };
+    auto load_a = [&](FragsA& f, int stage, int ks, int half) {
+        const unsigned char* base = smem + stage * kDmaStageBytes + (((4 * ks + (lane >> 4)) ^ fl) * 16);
 #pragma unroll
-        for (int i = 0; i < MI; ++i) f.a[i] = *reinterpret_cast<const bf16x8*>(base + a_row + i * 32 * 128);
+        for (int i = 0; i < MH; ++i) f.x[i] = *reinterpret_cast<const bf16x8*>(base + a_row + (half * MH + i) * 16 * 128);
+    };
+    auto load_b = [&](FragsB& f, int stage, int ks) {
+        const unsigned char* base = smem + stage * kDmaStageBytes + (((4 * ks + (lane >> 4)) ^ fl) * 16);
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) f.b[j] = *reinterpret_cast<const bf16x8*>(base + b_row + j * 32 * 128);
+        for (int j = 0; j < NJ; ++j) f.x[j] = *reinterpret_cast<const bf16x8*>(base + b_row + j * 16 * 128);
     };
 
-    f32x16 acc[MI][NJ];
+    f32x4 acc[MI][NJ];
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
-        for (int j = 0; j < NJ; ++j)
+        for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    auto mma = [&](const FragsA& fa, const FragsB& fb, int half) {
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
-    auto mma = [&](const RawFrags& f) {
-#pragma unroll
-        for (int i = 0; i < MI; ++i)
+        for (int i = 0; i < MH; ++i)
 #pragma unroll
             for (int j = 0; j < NJ; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[i], f.b[j], acc[i][j], 0, 0, 0);
+                acc[half * MH + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa.x[i], fb.x[j], acc[half * MH + i][j], 0, 0, 0);
     };
 
+    // A group is four multiply steps: two of 32 k, each for the upper and the lower half of the wavefront's rows.
     // Two stages.  The barrier of group g sits before its last multiply step: by then every wavefront has all
     // fragments of stage g in registers (the stage may be overwritten) and its own part of group g+1 has landed
     // (the other stage may be read).  Behind it the loads of group g+2 are issued, the first fragments of group
@@ -310,20 +318,24 @@ __global__ void __launch_bounds__(kBf16Threads) gemm_dma_kernel(GemmDmaArgs a) {
     wait_vmcnt_0();
     bare_barrier();
     if (ng > 1) dma(1, 1);
-    RawFrags f0, f1;
-    load_frags(f0, 0, 0);
+    FragsA a0, a1;
+    FragsB b0, b1;
+    load_a(a0, 0, 0, 0);
+    load_b(b0, 0, 0);
     // Groups that have two more behind them and no half tail run without a condition: with one around the middle steps and
     // around the loads the compiler kept them in separate blocks and could not move fragment reads and loads past the
-    // matrix instructions (1,024 x 65,536 x 4,096: 552 -> 510 us; 8,192^3: 965 -> 900).  The 128 x 384 tile runs two groups
+    // matrix instructions (1,024 x 65,536 x 4,096: 552 -> 510 us; 8,192^3: 965 -> 900; with 32 x 32 x 16 instructions).  Scheduling groups or barriers
+    // per step measure 2 to 4 % slower than what the compiler does by itself.  The 128 x 384 tile runs two groups
     // per turn, which makes the stage a constant (100 x 30,001 x 4,096: 90 us, 84 one group per turn, 80 two); the square
     // tile does not gain from that (8,192^3: 900 -> 913).
     auto full_group = [&](int cur, uint64_t g) {
-        load_frags(f1, cur, 1);
-        mma(f0);
-        load_frags(f0, cur, 2);
-        mma(f1);
-        load_frags(f1, cur, 3);
-        mma(f0);
+        load_a(a1, cur, 0, 1);
+        mma(a0, b0, 0);
+        load_a(a0, cur, 1, 0);
+        load_b(b1, cur, 1);
+        mma(a1, b0, 1);
+        load_a(a1, cur, 1, 1);
+        mma(a0, b1, 0);
         wait_lgkmcnt_0();
         wait_vmcnt_0();
         bare_barrier();
@@ -332,8 +344,9 @@ __global__ void __launch_bounds__(kBf16Threads) gemm_dma_kernel(GemmDmaArgs a) {
         for (int j = 0; j < 8; ++j)
             __builtin_amdgcn_global_load_lds(reinterpret_cast<const uint32_t*>(gsrc[j] + (g + 2) * gadv),
                                              reinterpret_cast<uint32_t*>(base + j * 1024), 16, 0, 0);
-        load_frags(f0, cur ^ 1, 0);
-        mma(f1);
+        load_a(a0, cur ^ 1, 0, 0);
+        load_b(b0, cur ^ 1, 0);
+        mma(a1, b1, 1);
     };
     const uint64_t ng_free = half_tail ? ng - 1 : ng;                    // groups that are whole
     uint64_t g = 0;
@@ -345,32 +358,36 @@ __global__ void __launch_bounds__(kBf16Threads) gemm_dma_kernel(GemmDmaArgs a) {
     for (; g + 2 < ng_free; ++g) full_group((int)(g & 1), g);
     for (; g < ng; ++g) {
         const int cur = (int)(g & 1);
-        load_frags(f1, cur, 1);
-        mma(f0);
+        load_a(a1, cur, 0, 1);
+        mma(a0, b0, 0);
         if (!(half_tail && g == ng - 1)) {                       // uniform
-            load_frags(f0, cur, 2);
-            mma(f1);
-            load_frags(f1, cur, 3);
-            mma(f0);
+            mma(a1, b0, 1);
+            load_a(a0, cur, 1, 0);
+            load_b(b0, cur, 1);
+            load_a(a1, cur, 1, 1);
+            mma(a0, b0, 0);
         }
         wait_lgkmcnt_0();
         wait_vmcnt_0();
         bare_barrier();
         if (g + 2 < ng) dma(g + 2, cur);
-        if (g + 1 < ng) load_frags(f0, cur ^ 1, 0);
-        mma(f1);
+        mma(a1, b0, 1);
+        if (g + 1 < ng) {
+            load_a(a0, cur ^ 1, 0, 0);
+            load_b(b0, cur ^ 1, 0);
+        }
     }
 
-    // accumulator element e of a lane: row 8*(e/4) + 4*(lane/32) + e%4, column lane%32
+    // accumulator element e of a lane: row 4*(lane/16) + e, column lane%16
     const bool interior = m0 + TMk <= a.M && n0 + TNk <= a.N;     // uniform
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-            const uint64_t col = n0 + wn * WN + j * 32 + (lane & 31);
+        for (int e = 0; e < 4; ++e) {
+            const uint64_t row = m0 + wm * WM + i * 16 + 4 * (lane >> 4) + e;
 #pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const uint64_t row = m0 + wm * WM + i * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+            for (int j = 0; j < NJ; ++j) {
+                const uint64_t col = n0 + wn * WN + j * 16 + (lane & 15);
                 if (interior && !a.accumulate) {
                     a.C[row * a.ldc + col] = acc[i][j][e];
                 } else if (row < a.M && col < a.N) {
