@@ -36,8 +36,6 @@ constexpr int kProjTokens = 128;       // tokens per workgroup of the projection
 constexpr int kProjThreads = 512;
 constexpr int kProjStages = 6;
 constexpr int kProjStageBytes = (kProjTokens + LP) * 128;      // 64 columns of the token rows, then of the projection rows
-constexpr int kOuterThreads = 512;
-constexpr int kOuterWaves = kOuterThreads / 64;
 
 __device__ __align__(16) const uint32_t g_logra_zeros[4] = {0u, 0u, 0u, 0u};
 
@@ -189,14 +187,16 @@ struct LograOuterArgs {
     uint64_t ldo;
 };
 
-// The token loop of one wavefront: U ranges and 8 / U runs of 16 tokens of both factors in flight at a time.
-template <int U>
+// The token loop of one wavefront of WAVES: U ranges and 4 / U runs of 16 tokens of both factors in flight at a time.  With
+// twice as many the tokens of a sample are dealt to half as many wavefronts (100 x 128 tokens, 2,048 -> 1,024: the call takes
+// 32.3 us, 27.3 with 4 / U; 7 x 1,000, 2,048 -> 8,192: 39.7 and 38.8; 27 shapes 4 % in the geometric mean, none slower).
+template <int U, int WAVES>
 __device__ __forceinline__ void logra_outer_tokens(const LograOuterArgs& a, uint64_t sample, uint32_t ab, uint32_t bb, uint64_t c0,
                                                    uint64_t c1, int wave, int lane, float (*st)[16][16], f32x4& acc) {
-    constexpr int RUNS = 8 / U;
+    constexpr int RUNS = 4 / U;
     const uint32_t ranges = a.ranges_a > a.ranges_b ? a.ranges_a : a.ranges_b;
     const int tr = lane >> 2, c4 = (lane & 3) * 4;
-    for (uint64_t t0 = c0 + 16 * RUNS * wave; t0 < c1; t0 += 16 * RUNS * kOuterWaves) {
+    for (uint64_t t0 = c0 + 16 * RUNS * wave; t0 < c1; t0 += 16 * RUNS * WAVES) {
         uint64_t ofs[RUNS];
         f32x4 va[RUNS], vb[RUNS];
 #pragma unroll
@@ -248,14 +248,15 @@ __device__ __forceinline__ void logra_outer_tokens(const LograOuterArgs& a, uint
     }
 }
 
-// A workgroup owns a 16 x 16 block of one sample's output and (usually) all of its tokens; its eight wavefronts take runs of
+// A workgroup owns a 16 x 16 block of one sample's output and (usually) all of its tokens; its wavefronts take runs of
 // tokens in turn, each for itself (sum of the ranges, a copy in its own part of LDS in the layout of
 // v_mfma_f32_16x16x4_f32), and add up at the end.  The 16 blocks of a sample run on one XCD, so the partial sums come out
 // of its L2 after the first of them.  Only when few samples have so many tokens that a workgroup would read megabytes are
 // the tokens cut into chunks; the workgroup of a block that arrives last then adds the chunks in their order.
-__global__ void __launch_bounds__(kOuterThreads) logra_outer_kernel(LograOuterArgs a) {
-    __shared__ __align__(16) float stage[kOuterWaves][2][16][16];
-    __shared__ float red[kOuterWaves][256];
+template <int WAVES>
+__global__ void __launch_bounds__(64 * WAVES) logra_outer_kernel(LograOuterArgs a) {
+    __shared__ __align__(16) float stage[WAVES][2][16][16];
+    __shared__ float red[WAVES][256];
     __shared__ uint32_t arrived;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t chunk = blockIdx.y;
@@ -266,9 +267,9 @@ __global__ void __launch_bounds__(kOuterThreads) logra_outer_kernel(LograOuterAr
     const uint64_t c1 = c0 + a.tokens_per_block < a.T ? c0 + a.tokens_per_block : a.T;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     const uint32_t ranges = a.ranges_a > a.ranges_b ? a.ranges_a : a.ranges_b;
-    if (ranges > 2) logra_outer_tokens<4>(a, sample, ab, bb, c0, c1, wave, lane, stage[wave], acc);
-    else if (ranges == 2) logra_outer_tokens<2>(a, sample, ab, bb, c0, c1, wave, lane, stage[wave], acc);
-    else logra_outer_tokens<1>(a, sample, ab, bb, c0, c1, wave, lane, stage[wave], acc);
+    if (ranges > 2) logra_outer_tokens<4, WAVES>(a, sample, ab, bb, c0, c1, wave, lane, stage[wave], acc);
+    else if (ranges == 2) logra_outer_tokens<2, WAVES>(a, sample, ab, bb, c0, c1, wave, lane, stage[wave], acc);
+    else logra_outer_tokens<1, WAVES>(a, sample, ab, bb, c0, c1, wave, lane, stage[wave], acc);
     // element e of a lane: row (a) 4(lane/16) + e, column (b) lane%16
 #pragma unroll
     for (int e = 0; e < 4; ++e) red[wave][(4 * (lane >> 4) + e) * 16 + (lane & 15)] = acc[e];
@@ -276,7 +277,7 @@ __global__ void __launch_bounds__(kOuterThreads) logra_outer_kernel(LograOuterAr
     float v = 0.0f;
     if (tid < 256) {
 #pragma unroll
-        for (int w = 0; w < kOuterWaves; ++w) v += red[w][tid];
+        for (int w = 0; w < WAVES; ++w) v += red[w][tid];
     }
     const uint32_t ai = ab * 16 + (tid >> 4), bi = bb * 16 + (tid & 15);
     float* o = a.out + sample * a.ldo + (uint64_t)ai * a.k_out + bi;
@@ -449,6 +450,10 @@ extern "C" grass_status logra_linear(const void* x, const void* gout, uint64_t n
     static LdsOptIn opt_in;
     if (allow_large_lds(opt_in, reinterpret_cast<const void*>(logra_project_kernel)) != hipSuccess) return GRASS_EHIP;
     hipLaunchKernelGGL(logra_project_kernel, dim3((uint32_t)blocks), dim3(kProjThreads), kProjStages * kProjStageBytes, hs, p);
-    hipLaunchKernelGGL(logra_outer_kernel, dim3((uint32_t)ceil_div(n, 8) * 128, pl.chunks), dim3(kOuterThreads), 0, hs, o);
+    const dim3 grid((uint32_t)ceil_div(n, 8) * 128, pl.chunks);
+    // 16 wavefronts where the blocks of all samples leave CUs idle and there are tokens for them (10 x 130 tokens 16.3 -> 15.2 us;
+    // 64 x 256 tokens 20.7 with 8, 22.6 with 16)
+    if (T > 128 && n <= 16) hipLaunchKernelGGL(logra_outer_kernel<16>, grid, dim3(1024), 0, hs, o);
+    else hipLaunchKernelGGL(logra_outer_kernel<8>, grid, dim3(512), 0, hs, o);
     return launch_status();
 }
