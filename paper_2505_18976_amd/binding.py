@@ -9,6 +9,7 @@ fallback: if the library is missing, loading fails loudly.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 import struct
 
@@ -165,8 +166,9 @@ def _ptr(t):
 
 
 def _ld(t: torch.Tensor) -> int:
-    assert t.dim() == 2 and t.stride(1) == 1, "row-major matrix expected"
-    return t.stride(0) if t.shape[0] > 1 else max(t.stride(0), t.shape[1])
+    s = t.stride()
+    assert len(s) == 2 and s[1] == 1, "row-major matrix expected"
+    return s[0] if t.shape[0] > 1 else max(s[0], t.shape[1])
 
 
 def _tuning(tuning):
@@ -176,6 +178,11 @@ def _tuning(tuning):
     if isinstance(tuning, dict):
         tuning = GrassTuning(**tuning)
     return ctypes.byref(tuning)
+
+
+# Workspace sizes depend on the sizes of a problem alone and are asked for on every call (0.8 us of the 9 that a small one
+# spends on the host, more where the library weighs many launch shapes); the last 256 of each kind are remembered.
+_sizes = functools.lru_cache(maxsize=256)
 
 
 def _workspace(nbytes: int, device) -> torch.Tensor | None:
@@ -236,6 +243,9 @@ def grass_sjlt_workspace_bytes(n: int, p: int, kprime_or_0: int, k: int, s: int,
     return out.value
 
 
+_sjlt_bytes = _sizes(grass_sjlt_workspace_bytes)
+
+
 def grass_sjlt(g: torch.Tensor, k: int, s: int, seed: int, stream_id: int = 1, idx: torch.Tensor | None = None,
                out: torch.Tensor | None = None, ws: torch.Tensor | None = None, tuning=None) -> torch.Tensor:
     """SJLT_k of the rows of g, or fused GraSS when idx is given."""
@@ -245,7 +255,8 @@ def grass_sjlt(g: torch.Tensor, k: int, s: int, seed: int, stream_id: int = 1, i
     if out is None:
         out = g.new_empty((n, k), dtype=torch.float32)
     if ws is None:
-        ws = _workspace(grass_sjlt_workspace_bytes(n, p, kprime, k, s, tuning), g.device)
+        ws = _workspace(_sjlt_bytes(n, p, kprime, k, s) if tuning is None
+                        else grass_sjlt_workspace_bytes(n, p, kprime, k, s, tuning), g.device)
     _check(load_library().grass_sjlt(_ptr(g), n, p, _ld(g), _ptr(idx), kprime, k, s, seed, stream_id,
                                      _ptr(out), _ld(out), _ptr(ws), 0 if ws is None else ws.numel(), _tuning(tuning),
                                      _stream()),
@@ -262,7 +273,8 @@ def grass_sjlt_bf16(g: torch.Tensor, k: int, s: int, seed: int, stream_id: int =
     if out is None:
         out = g.new_empty((n, k), dtype=torch.float32)
     if ws is None:
-        ws = _workspace(grass_sjlt_workspace_bytes(n, p, kprime, k, s, tuning), g.device)
+        ws = _workspace(_sjlt_bytes(n, p, kprime, k, s) if tuning is None
+                        else grass_sjlt_workspace_bytes(n, p, kprime, k, s, tuning), g.device)
     _check(load_library().grass_sjlt_bf16(_ptr(g), n, p, _ld(g), _ptr(idx), kprime, k, s, seed, stream_id,
                                           _ptr(out), _ld(out), _ptr(ws), 0 if ws is None else ws.numel(),
                                           _tuning(tuning), _stream()),
@@ -298,6 +310,9 @@ def factgrass_linear_workspace_bytes(n: int, T: int, kin_p: int, kout_p: int, k:
     return out.value
 
 
+_factgrass_linear_bytes = _sizes(factgrass_linear_workspace_bytes)
+
+
 def factgrass_linear(x: torch.Tensor, gout: torch.Tensor, idx_in: torch.Tensor, idx_out: torch.Tensor,
                      k: int, s: int, seed: int, stream_id: int, out: torch.Tensor | None = None,
                      ws: torch.Tensor | None = None, tuning=None) -> torch.Tensor:
@@ -309,8 +324,9 @@ def factgrass_linear(x: torch.Tensor, gout: torch.Tensor, idx_in: torch.Tensor, 
     if out is None:
         out = torch.empty((n, k), dtype=torch.float32, device=x.device)
     if ws is None:
-        ws = _workspace(factgrass_linear_workspace_bytes(n, T, idx_in.numel(), idx_out.numel(), k, s, tuning),
-                        x.device)
+        sizes = (n, T, idx_in.numel(), idx_out.numel(), k, s)
+        ws = _workspace(_factgrass_linear_bytes(*sizes) if tuning is None
+                        else factgrass_linear_workspace_bytes(*sizes, tuning), x.device)
     _check(load_library().factgrass_linear(_ptr(x), _ptr(gout), n, T, d_in, d_out, _ptr(idx_in), idx_in.numel(),
                                            _ptr(idx_out), idx_out.numel(), k, s, seed, stream_id, _ptr(out),
                                            _ld(out), _ptr(ws), 0 if ws is None else ws.numel(), _tuning(tuning),
@@ -358,6 +374,9 @@ def logra_linear_workspace_bytes(n: int, T: int, k_in: int, k_out: int) -> int:
     return out.value
 
 
+_logra_linear_bytes = _sizes(logra_linear_workspace_bytes)
+
+
 def logra_linear(x: torch.Tensor, gout: torch.Tensor, P_in: torch.Tensor, P_out: torch.Tensor,
                  out: torch.Tensor | None = None, ws: torch.Tensor | None = None) -> torch.Tensor:
     assert x.dtype == gout.dtype == P_in.dtype == P_out.dtype == torch.bfloat16
@@ -369,7 +388,7 @@ def logra_linear(x: torch.Tensor, gout: torch.Tensor, P_in: torch.Tensor, P_out:
     if out is None:
         out = x.new_empty((n, k_in * k_out), dtype=torch.float32)
     if ws is None:
-        ws = _workspace(logra_linear_workspace_bytes(n, T, k_in, k_out), x.device)
+        ws = _workspace(_logra_linear_bytes(n, T, k_in, k_out), x.device)
     _check(load_library().logra_linear(_ptr(x), _ptr(gout), n, T, d_in, d_out, _ptr(P_in), k_in, _ptr(P_out), k_out,
                                        _ptr(out), _ld(out), _ptr(ws), 0 if ws is None else ws.numel(), _stream()),
            "logra_linear")
@@ -383,6 +402,9 @@ def grass_score_workspace_bytes(N: int, M: int, K: int, compute_mode: int) -> in
     return out.value
 
 
+_score_bytes = _sizes(grass_score_workspace_bytes)
+
+
 def grass_score(train: torch.Tensor, test: torch.Tensor, compute_mode: int = 0,
                 out: torch.Tensor | None = None, ws: torch.Tensor | None | bool = True) -> torch.Tensor:
     """scores[m, i] = <test_m, train_i>.  ws: True allocates the optional workspace, None runs without one."""
@@ -393,7 +415,7 @@ def grass_score(train: torch.Tensor, test: torch.Tensor, compute_mode: int = 0,
     if out is None:
         out = torch.empty((M, N), dtype=torch.float32, device=train.device)
     if ws is True:
-        ws = _workspace(grass_score_workspace_bytes(N, M, K, compute_mode), train.device)
+        ws = _workspace(_score_bytes(N, M, K, compute_mode), train.device)
     _check(load_library().grass_score(_ptr(train), _ptr(test), compute_mode, N, M, K, _ld(train), _ld(test),
                                       _ptr(out), _ld(out), _ptr(ws), 0 if ws is None else ws.numel(), _stream()),
            "grass_score")
