@@ -1,9 +1,9 @@
 // Cache stage after compression (Sec. 2.1 steps 2 and 3 on compressed gradients, Sec. 2.2 "projected FIM",
 // damping of App. B):
-//   grass_fim          F = (1/N) G^T G                      fp32 product of gemm_split.hip, lower tiles only
+//   grass_fim          F = (1/N) G^T G                      fp32 product of gemm_pair.hip, lower tiles only
 //   grass_fim_inverse  W = (F + lambda I)^{-1}              fp64: blocked Cholesky, recursive triangular inverse,
 //                                                           W = L^{-T} L^{-1}; fp64 MFMA for every product
-//   grass_ifvp         out = G W  (row i = W g_i)           fp32 product of gemm_split.hip (W is symmetric)
+//   grass_ifvp         out = G W  (row i = W g_i)           fp32 product of gemm_pair.hip (W is symmetric)
 #include <hip/hip_runtime.h>
 #include <type_traits>
 

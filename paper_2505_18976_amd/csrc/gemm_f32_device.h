@@ -63,6 +63,19 @@ __device__ __forceinline__ GemmTile gemm_f32_tile(const GemmF32Args& a) {
     return GemmTile{tm, tn, split};
 }
 
+// What the backward product R = C G of a Selective-Mask step is for: the gradient of its columns,
+// grad[j0 + c] = 2 sigma sigma' sum_t Gt[t][j0 + c] R[t][c] - lambda sigma' with sigma = sigmoid(S[j0 + c] inv_temp).
+struct GradTail {
+    const float* Gt;
+    uint64_t ldgt, j0;
+    const float* S;
+    float inv_temp, lambda;
+    float* grad;
+};
+// The product A B (B K-major, at most 128 rows of A, not accumulated) straight to the gradient; C is scratch for tiles that
+// have to be computed again.
+hipError_t gemm_f32_pair_grad(const GemmF32Args& a, const GradTail& g, hipStream_t st);
+
 // gemm_pair.hip: tile as in GemmPlan, row distances for which gemm_f32_wide is false.
 hipError_t gemm_f32_pair(bool a_kn, bool b_kn, int tile, const GemmF32Args& a, hipStream_t st);
 

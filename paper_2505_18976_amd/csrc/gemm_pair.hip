@@ -74,10 +74,59 @@ typedef unsigned char __attribute__((address_space(3)))* lds_byte;
 
 enum : int { kDone = 0, kAgain = 1, kAgainExact = 2 };
 
+// The gradient of the columns of a tile from its R = `get(i, j, e)` (element e of block (i, j)), all rows of which it holds: a
+// lane multiplies its 4 columns with Gt and sums its rows in fp64, lanes and wavefronts are added in a fixed order.
+template <int RB, int NB, int WR, int WC, class Get>
+__device__ __forceinline__ void grad_tail(const GemmF32Args& a, const GradTail& t, double* part, uint64_t n0, Get get) {
+    constexpr int TN = 16 * NB * WC;
+    const int lane = threadIdx.x & 63, lq = lane >> 4, lc = lane & 15, wave = threadIdx.x >> 6, wm = wave / WC, wn = wave % WC;
+    const uint64_t c0 = n0 + wn * NB * 16 + 4 * lc;
+    const bool all = c0 + 4 <= a.N;
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int i = 0; i < RB; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint64_t row = (wm * RB + i) * 16 + 4 * lq + e;
+            if (row >= a.M || c0 >= a.N) continue;
+            const float* gt = t.Gt + row * t.ldgt + t.j0 + c0;
+            f32x4 x{0.0f, 0.0f, 0.0f, 0.0f};
+            if (all) {
+                x = *reinterpret_cast<const f32x4u*>(gt);
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (c0 + j < a.N) x[j] = gt[j];
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (all || c0 + j < a.N) s[j] += (double)x[j] * (double)get(i, j, e);
+        }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        s[j] += __shfl_xor(s[j], 16);
+        s[j] += __shfl_xor(s[j], 32);
+    }
+    __syncthreads();                                           // the stages are no longer read
+    if (lq == 0) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) part[wm * TN + wn * NB * 16 + 4 * lc + j] = s[j];
+    }
+    __syncthreads();
+    for (int c = threadIdx.x; c < TN && n0 + c < a.N; c += 64 * WR * WC) {
+        double sum = part[c];
+#pragma unroll
+        for (int w = 1; w < WR; ++w) sum += part[w * TN + c];
+        const uint64_t j = t.j0 + n0 + c;
+        const float sig = sigmoidf(t.S[j] * t.inv_temp), dsig = sig * (1.0f - sig) * t.inv_temp;
+        t.grad[j] = (float)(2.0 * (double)sig * (double)dsig * sum - (double)t.lambda * (double)dsig);
+    }
+}
+
 // mode: kAgain, from the start; kAgainExact, with the largest values of the range (the samples' scales are in LDS and, unless
 // C accumulates, the finite sums in C).  Returns kDone or what is left to do.
-template <int RB, int NB, int WR, int WC, bool AKN, bool BKN, bool GENERAL>
-__device__ __forceinline__ int pair_tile(GemmF32Args a, lds_byte lds, int mode) {
+template <int RB, int NB, int WR, int WC, bool AKN, bool BKN, bool GENERAL, bool GRAD = false>
+__device__ __forceinline__ int pair_tile(GemmF32Args a, lds_byte lds, int mode, const GradTail* tail = nullptr) {
     unsigned char* const smem = (unsigned char*)lds;
     constexpr int NW = WR * WC, THREADS = 64 * NW;
     constexpr int TM = 16 * RB * WR, TN = 16 * NB * WC, SLOTS = TM + TN;
@@ -646,6 +695,15 @@ __device__ __forceinline__ int pair_tile(GemmF32Args a, lds_byte lds, int mode) 
                         if (i2 == i / 2) todo[i2] |= bad;
                 }
         }
+        if constexpr (GRAD) {
+            if (!again && mt[3] == 0) {                        // uniform: none of the sums is in question
+                grad_tail<RB, NB, WR, WC>(a, *tail, reinterpret_cast<double*>(smem), n0, [&](int i, int j, int e) {
+                    return __builtin_ldexpf(acc[i][j][e], -(ea[i * 16 + e] + eb[j * 16]));
+                });
+                return kDone;
+            }
+            if (!again) return kAgain;
+        }
         const bool interior = m0 + TM <= a.M && n0 + TN <= a.N && !a.accumulate;         // uniform
         const bool quads = BKN && interior && a.ldc % 4 == 0 && (reinterpret_cast<uintptr_t>(a.C) & 15) == 0;
 #pragma unroll
@@ -754,6 +812,23 @@ __global__ void __launch_bounds__(64 * WR * WC, 2) gemm_pair_kernel(GemmF32Args 
     }
 }
 
+template <int RB, int NB, int WR, int WC>
+__global__ void __launch_bounds__(64 * WR * WC, 2) gemm_pair_grad_kernel(GemmF32Args a, GradTail t) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int mode = pair_tile<RB, NB, WR, WC, false, true, false, true>(a, (lds_byte)smem, 0, &t);
+    if (mode == kDone) return;                                 // uniform
+    __syncthreads();
+    pair_general<RB, NB, WR, WC, false, true>(a, (lds_byte)smem, mode);
+    __syncthreads();
+    // every lane reads back what it stored itself
+    const uint64_t n0 = (uint64_t)gemm_f32_tile(a).tn * (16 * NB * WC);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint64_t c0 = n0 + (wave % WC) * NB * 16 + 4 * (lane & 15);
+    grad_tail<RB, NB, WR, WC>(a, t, reinterpret_cast<double*>(smem), n0, [&](int i, int j, int e) {
+        return a.C[(uint64_t)((wave / WC * RB + i) * 16 + 4 * (lane >> 4) + e) * a.ldc + c0 + j];
+    });
+}
+
 template <int RB, int NB, int WR, int WC, bool AKN, bool BKN>
 static hipError_t launch_pair(GemmF32Args a, hipStream_t st) {
     constexpr uint64_t TM = 16 * RB * WR, TN = 16 * NB * WC;
@@ -768,6 +843,19 @@ static hipError_t launch_pair(GemmF32Args a, hipStream_t st) {
     hipError_t e = allow_large_lds(opt_in, reinterpret_cast<const void*>(gemm_pair_kernel<RB, NB, WR, WC, AKN, BKN>));
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((gemm_pair_kernel<RB, NB, WR, WC, AKN, BKN>), dim3((uint32_t)total), dim3(64 * WR * WC), lds, st, a);
+    return hipGetLastError();
+}
+
+hipError_t gemm_f32_pair_grad(const GemmF32Args& args, const GradTail& t, hipStream_t st) {
+    constexpr uint64_t TM = 128, TN = 256, lds = 2 * 8 * (TM + TN) * 16 + (TM + TN) * 12 + 16;
+    GemmF32Args a = args;
+    if (a.M > TM || a.accumulate || a.splits != 1 || gemm_f32_wide(a.lda > a.ldb ? a.lda : a.ldb)) return hipErrorInvalidValue;
+    a.tiles_m = 1;
+    a.tiles_n = (uint32_t)ceil_div(a.N, TN);
+    static LdsOptIn opt_in;
+    hipError_t e = allow_large_lds(opt_in, reinterpret_cast<const void*>(gemm_pair_grad_kernel<4, 4, 2, 4>));
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((gemm_pair_grad_kernel<4, 4, 2, 4>), dim3(a.tiles_n), dim3(512), lds, st, a, t);
     return hipGetLastError();
 }
 

@@ -38,6 +38,8 @@ __device__ __forceinline__ uint32_t bucket_of(uint64_t h, uint32_t m) {
 }
 __device__ __forceinline__ uint32_t signbit_of(uint64_t h) { return ((uint32_t)h & 1u) << 31; }
 
+__device__ __forceinline__ float sigmoidf(float x) { return 1.0f / (1.0f + expf(-x)); }
+
 inline hipStream_t as_stream(grass_stream s) { return reinterpret_cast<hipStream_t>(s); }
 
 inline grass_status launch_status() {

@@ -3,21 +3,19 @@
 //   A[t][i] = <gt_t, g_i>  (handed in),      B[t][i] = sum_j sigma_j^2 gt_t[j] g_i[j].
 // Chain rule: with da, db the centred rows of A and B, c_t = da/(|da||db|) - corr_t db/|db|^2,
 //   dL/dS_j = 2 sigma_j sigma_j' * (1/m) sum_t gt_t[j] (c_t G)[j]  -  lambda sigma_j',   sigma_j' = sigma_j (1 - sigma_j) / T.
-// Both contractions over the data are fp32 products (gemm_split.hip):
+// Both contractions over the data are fp32 products (gemm_pair.hip, gemm_split.hip):
 //   B = (Gt * sigma^2) G^T      (m x n, contraction over p)
 //   R = C G                     (m x p, contraction over n; G is read in place as a K-major operand)
 // Everything else is a row statistic (fp64, fixed order) or elementwise.
 #include <hip/hip_runtime.h>
 
-#include "gemm_f32.h"
+#include "gemm_f32_device.h"
 #include "grass.h"
 #include "grass_device.h"
 
 namespace grass {
 
 constexpr uint32_t kSmMaxSplits = 64;
-
-__device__ __forceinline__ float sigmoidf(float x) { return 1.0f / (1.0f + expf(-x)); }
 
 // Workgroup-wide sum of one double per thread (256 threads), result in every thread; fixed order.
 __device__ __forceinline__ double block_sum(double v, double* red) {
@@ -229,6 +227,14 @@ static grass_status sm_backward(const SmLayout& L, unsigned char* base, const fl
         const uint64_t pc = j0 + L.pc <= p ? L.pc : p - j0;
         // Rc (m x pc) = C G[:, j0 : j0+pc], a contraction over the n rows of G
         const GemmPlan plan = gemm_f32_plan(false, true, m, pc, n, ldg, false, 1);
+        // With one row of tiles a workgroup has all rows of its columns of R, and the gradient comes out of its registers: the
+        // round trip of R and a kernel behind every block are saved (100 rows, 327,680 columns: 379 + 53 -> 393 us; a step on 100 +
+        // 1,000 rows of 1,863,690 0.3 ms).  Rc is scratch for tiles that have to be computed again.
+        if (plan.pair && m <= 128) {
+            const GemmF32Args a{C, G + j0, Rc, m, pc, n, L.n_pad, ldg, L.pc, 0, 0, 0, 0, 1, 0};
+            if (gemm_f32_pair_grad(a, GradTail{Gt, ldgt, j0, S, inv_temp, lambda, grad}, hs) != hipSuccess) return GRASS_EHIP;
+            continue;
+        }
         if (gemm_f32(false, true, C, G + j0, Rc, m, pc, n, L.n_pad, ldg, L.pc, 0, 0, plan, nullptr, hs) != hipSuccess)
             return GRASS_EHIP;
         hipLaunchKernelGGL(sm_grad_kernel, dim3((uint32_t)ceil_div(pc, 64)), dim3(256), 0, hs, Gt, ldgt, m, Rc, L.pc, j0, pc,

@@ -87,6 +87,34 @@ def test_second_operand_k_major(grass, m, n, p):
     assert float((grad.double() - ref).abs().max()) <= 1e-5 * float(ref.abs().max())
 
 
+@pytest.mark.parametrize("m,n,p", [(1, 256, 255), (100, 300, 257), (128, 300, 1_027), (17, 259, 4_098)])
+@pytest.mark.parametrize("spoil", ["zeros", "late", "far", "infinite"])
+def test_gradient_of_columns_that_the_sample_misjudges(grass, m, n, p, spoil):
+    """The gradient out of the backward product's registers, with columns of G that send their tile through the second attempt."""
+    G, Gt = synth.dense_normal(n, p, seed=7, device=_dev()), synth.dense_normal(m, p, seed=8, device=_dev())
+    S = synth.dense_normal(1, p, seed=9, device=_dev(), std=0.5).reshape(-1).contiguous()
+    A = synth.dense_normal(m, n, seed=10, device=_dev())
+    if spoil == "zeros":                     # nothing in the sample, small behind it
+        G[:200, 5], G[200:, 5] = 0.0, G[200:, 5] * 2.0 ** -20
+        G[:, p - 1] = 0.0
+    else:                                    # too large for the sample, of wide range; test gradients are zero there
+        G[100, 7] = {"late": 2.0 ** 12, "far": 2.0 ** 30, "infinite": float("inf")}[spoil]
+        Gt[:, 7] = 0.0
+    sig, g, gt, a = torch.sigmoid(S.double()), G.double(), Gt.double(), A.double()
+    g0 = g.nan_to_num(0.0, 0.0, 0.0)
+    b = (gt * sig ** 2) @ g0.T.contiguous()
+    da, db = a - a.mean(1, keepdim=True), b - b.mean(1, keepdim=True)
+    na, nb = da.norm(dim=1, keepdim=True), db.norm(dim=1, keepdim=True)
+    c = (da / (na * nb) - (da * db).sum(1, keepdim=True) / (na * nb ** 3) * db) / m
+    ds = sig * (1 - sig)
+    ref = 2 * sig * ds * (gt * (c @ g0)).sum(0) - 1e-3 * ds
+    grad, _ = grass.grass_selective_mask_grad(G, Gt, A, S, 1e-3, 1.0)
+    if spoil == "infinite":                  # 0 times infinity in every masked score of train row 100
+        assert bool(torch.isnan(grad).all())
+        return
+    assert float((grad.double() - ref).abs().max()) <= 1e-5 * float(ref.abs().max())
+
+
 def _odd_rows(X):
     """Rows that a sample of the first 32 k (and of three more groups in long ranges) misjudges."""
     K = X.shape[1]
