@@ -22,6 +22,7 @@ struct GemmF32Args {
     int lower_only;              // symmetric product: tiles strictly above the diagonal are skipped
     uint32_t splits;             // split-K: workgroup (split, tile) contracts one of `splits` contiguous ranges of K
     uint64_t split_stride_c;     //          into C + split*split_stride_c
+    const float* weight = nullptr;      // gemm_f32_pair_weighted: K rounded up to 32 factors of the columns of A, 16-byte aligned
 };
 
 __device__ __forceinline__ void f32_barrier() {
@@ -72,6 +73,8 @@ struct GradTail {
     float inv_temp, lambda;
     float* grad;
 };
+// (A * weight) B^T for at most 128 rows of A, K ranges as in GemmPlan.
+hipError_t gemm_f32_pair_weighted(const GemmF32Args& a, hipStream_t st);
 // The product A B (B K-major, at most 128 rows of A, not accumulated) straight to the gradient; C is scratch for tiles that
 // have to be computed again.
 hipError_t gemm_f32_pair_grad(const GemmF32Args& a, const GradTail& g, hipStream_t st);

@@ -125,7 +125,7 @@ __device__ __forceinline__ void grad_tail(const GemmF32Args& a, const GradTail& 
 
 // mode: kAgain, from the start; kAgainExact, with the largest values of the range (the samples' scales are in LDS and, unless
 // C accumulates, the finite sums in C).  Returns kDone or what is left to do.
-template <int RB, int NB, int WR, int WC, bool AKN, bool BKN, bool GENERAL, bool GRAD = false>
+template <int RB, int NB, int WR, int WC, bool AKN, bool BKN, bool GENERAL, bool WEIGHT = false, bool GRAD = false>
 __device__ __forceinline__ int pair_tile(GemmF32Args a, lds_byte lds, int mode, const GradTail* tail = nullptr) {
     unsigned char* const smem = (unsigned char*)lds;
     constexpr int NW = WR * WC, THREADS = 64 * NW;
@@ -248,7 +248,16 @@ __device__ __forceinline__ int pair_tile(GemmF32Args a, lds_byte lds, int mode, 
         }
         return x;
     };
+    static_assert(!WEIGHT || !AKN, "weights");
     f32x4 xa[CA], xb[CB], za[CA], zb[CB];                      // a group on its way, the first group
+    f32x4 xw, zw;                                              // the weights of the thread's k of these
+    auto weight_at = [&](uint32_t g) {
+        if constexpr (WEIGHT) return *(gvec)((gfloat)a.weight + g0 * 32 + (uint64_t)g * 32 + 4 * (lane & 7));
+        else return f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    };
+    auto weigh = [&](f32x4& v, const f32x4& w) {               // rounded once, as a matrix of products would be
+        if constexpr (WEIGHT) v *= w;
+    };
     // 4 k of one slot: chunk i of a row-major operand, column i of a K-major one
     auto values = [&](auto km, const auto& x, int i) {
         if constexpr (decltype(km)::value) return f32x4{x[0][i], x[1][i], x[2][i], x[3][i]};
@@ -278,7 +287,8 @@ __device__ __forceinline__ int pair_tile(GemmF32Args a, lds_byte lds, int mode, 
         for (int i = 0; i < CB; ++i) { pb[i] = base_of(km_b, sb, i); cb[i] = !BKN && cut(sb, i); }
         auto load_a = [&](int i, uint32_t g) { return load_full(pa[i], sa.step, ca[i] ? ga_cut : ga, g); };
         auto load_b = [&](int i, uint32_t g) { return load_full(pb[i], sb.step, cb[i] ? gb_cut : gb, g); };
-        auto fetch = [&](auto& ya, auto& yb, uint32_t g) {
+        auto fetch = [&](auto& ya, auto& yb, f32x4& yw, uint32_t g) {
+            if (WEIGHT && g < ng) yw = weight_at(g);           // uniform
             if (g < nf) {                                      // uniform; in the order in which the main loop waits for them
 #pragma unroll
                 for (int i = 0; i < CA; ++i) {
@@ -313,7 +323,7 @@ __device__ __forceinline__ int pair_tile(GemmF32Args a, lds_byte lds, int mode, 
 #pragma unroll
                 for (int t = 0; t < 3; ++t) {
 #pragma unroll
-                    for (int i = 0; i < CA; ++i) ya[t][i] = load_a(i, s + t);
+                    for (int i = 0; i < CA; ++i) { ya[t][i] = load_a(i, s + t); weigh(ya[t][i], weight_at(s + t)); }
 #pragma unroll
                     for (int i = 0; i < CB; ++i) yb[t][i] = load_b(i, s + t);
                 }
@@ -327,9 +337,12 @@ __device__ __forceinline__ int pair_tile(GemmF32Args a, lds_byte lds, int mode, 
             }
 #pragma unroll 1
             for (; s < ng; ++s) {
-                fetch(za, zb, s);
+                fetch(za, zb, zw, s);
 #pragma unroll
-                for (int i = 0; i < CA; ++i) qa[i] = __builtin_fmaxf(qa[i], largest(values(km_a, za, i)));
+                for (int i = 0; i < CA; ++i) {
+                    weigh(za[i], zw);
+                    qa[i] = __builtin_fmaxf(qa[i], largest(values(km_a, za, i)));
+                }
 #pragma unroll
                 for (int i = 0; i < CB; ++i) qb[i] = __builtin_fmaxf(qb[i], largest(values(km_b, zb, i)));
             }
@@ -355,12 +368,12 @@ __device__ __forceinline__ int pair_tile(GemmF32Args a, lds_byte lds, int mode, 
                 break;
             }
             attempt = 1;
-            fetch(za, zb, 0);
-            fetch(xa, xb, 1);
+            fetch(za, zb, zw, 0);
+            fetch(xa, xb, xw, 1);
         }
         bool track = false;
         if (attempt == 0) {
-            fetch(za, zb, 0);
+            fetch(za, zb, zw, 0);
             for (int t = threadIdx.x; t < SLOTS; t += THREADS) mx[t] = wd[t] = 0;
             if (threadIdx.x < 4) mt[threadIdx.x] = 0;
             constexpr int QS = 4;                              // groups of the sample
@@ -384,14 +397,18 @@ __device__ __forceinline__ int pair_tile(GemmF32Args a, lds_byte lds, int mode, 
 #pragma unroll
                 for (int t = 1; t < QS; ++t) {
 #pragma unroll
-                    for (int i = 0; i < CA; ++i) ya[t][i] = load_a(i, t < QS - 1 ? t * (ng / QS) : last_sample(sa, i));
+                    for (int i = 0; i < CA; ++i) {
+                        const uint32_t at = t < QS - 1 ? t * (ng / QS) : last_sample(sa, i);
+                        ya[t][i] = load_a(i, at);
+                        weigh(ya[t][i], weight_at(at));
+                    }
 #pragma unroll
                     for (int i = 0; i < CB; ++i) yb[t][i] = load_b(i, t < QS - 1 ? t * (ng / QS) : last_sample(sb, i));
                 }
             }
-            fetch(xa, xb, 1);
+            fetch(xa, xb, xw, 1);
 #pragma unroll
-            for (int i = 0; i < CA; ++i) ya[0][i] = za[i];
+            for (int i = 0; i < CA; ++i) { ya[0][i] = za[i]; weigh(ya[0][i], zw); }
 #pragma unroll
             for (int i = 0; i < CB; ++i) yb[0][i] = zb[i];
 #pragma unroll
@@ -479,8 +496,9 @@ __device__ __forceinline__ int pair_tile(GemmF32Args a, lds_byte lds, int mode, 
         for (int i = 0; i < (BKN ? CB : 1); ++i) wb[i] = in_plane(km_b, sb, ln, slot_of(km_b, sb, ln, i));
 
         // Two fp16 pieces of 4 values.  `rare`: there are slots without a sample, whose largest value is wanted.
-        auto stash = [&](auto km, auto rare, const auto& x, const Side& o, const uint32_t* w, float scale, int i, uint32_t stage) {
-            const f32x4 v = values(km, x, i);
+        auto stash = [&](auto km, auto rare, const auto& x, const f32x4* wt, const Side& o, const uint32_t* w, float scale, int i, uint32_t stage) {
+            f32x4 v = values(km, x, i);
+            if (wt) weigh(v, *wt);
             u32x2 p0, p1;
 #pragma unroll
             for (int e = 0; e < 4; e += 2) {
@@ -515,9 +533,9 @@ __device__ __forceinline__ int pair_tile(GemmF32Args a, lds_byte lds, int mode, 
         const std::false_type no;
         const std::integral_constant<bool, GENERAL> rare;
 #pragma unroll
-        for (int i = 0; i < CA; ++i) stash(km_a, rare, za, sa, wa, fsa[i], i, 0);
+        for (int i = 0; i < CA; ++i) stash(km_a, rare, za, &zw, sa, wa, fsa[i], i, 0);
 #pragma unroll
-        for (int i = 0; i < CB; ++i) stash(km_b, rare, zb, sb, wb, fsb[i], i, 0);
+        for (int i = 0; i < CB; ++i) stash(km_b, rare, zb, nullptr, sb, wb, fsb[i], i, 0);
         Frag fa[2], fb[NB];
         uint32_t cur = 0, g = 0;
         auto group = [&](auto full, auto rare, uint32_t gi) {
@@ -532,9 +550,10 @@ __device__ __forceinline__ int pair_tile(GemmF32Args a, lds_byte lds, int mode, 
                     for (int q = 0; q < NC; ++q) {
                         if (q * (RB - 1) / NC != i) continue;
                         if (q < CA) {
-                            stash(km_a, rare, xa, sa, wa, fsa[q], q, nxt);
+                            stash(km_a, rare, xa, &xw, sa, wa, fsa[q], q, nxt);
                             if constexpr (FULL) {
                                 if (!AKN) xa[q] = load_a(q, gi + 2);
+                                if (WEIGHT && q == CA - 1) xw = weight_at(gi + 2);
                                 else if (q == CA - 1) {
 #pragma unroll
                                     for (int r = 0; r < CA; ++r) xa[r] = load_a(r, gi + 2);
@@ -542,7 +561,7 @@ __device__ __forceinline__ int pair_tile(GemmF32Args a, lds_byte lds, int mode, 
                             }
                         } else {
                             const int r = q - CA;
-                            stash(km_b, rare, xb, sb, wb, fsb[r], r, nxt);
+                            stash(km_b, rare, xb, nullptr, sb, wb, fsb[r], r, nxt);
                             if constexpr (FULL) {
                                 if (!BKN) xb[r] = load_b(r, gi + 2);
                                 else if (r == CB - 1) {
@@ -553,7 +572,7 @@ __device__ __forceinline__ int pair_tile(GemmF32Args a, lds_byte lds, int mode, 
                         }
                     }
                 } else {
-                    if constexpr (!FULL) fetch(xa, xb, gi + 2);
+                    if constexpr (!FULL) fetch(xa, xb, xw, gi + 2);
                     wait_lds();
                     f32_barrier();
                     load(fa[0], a_ofs + nxt, 0);
@@ -765,6 +784,7 @@ __device__ __forceinline__ int pair_tile(GemmF32Args a, lds_byte lds, int mode, 
                             const bool ok = decltype(all)::value || k + q < k_end;
                             if constexpr (!decltype(all)::value || AKN) ya[u][q] = ok ? pa[AKN ? (k + q) * a.lda : k + q] : 0.0f;
                             if constexpr (!decltype(all)::value || BKN) yb[u][q] = ok ? pb[BKN ? (k + q) * a.ldb : k + q] : 0.0f;
+                            if constexpr (WEIGHT) ya[u][q] *= ok ? a.weight[k + q] : 0.0f;
                         }
                     }
 #pragma unroll
@@ -790,7 +810,7 @@ __device__ __forceinline__ int pair_tile(GemmF32Args a, lds_byte lds, int mode, 
     return kDone;
 }
 
-template <int RB, int NB, int WR, int WC, bool AKN, bool BKN>
+template <int RB, int NB, int WR, int WC, bool AKN, bool BKN, bool WEIGHT = false>
 __device__ __attribute__((noinline)) void pair_general(GemmF32Args a, lds_byte lds, int mode) {
     // arguments of a function that is not inlined arrive in vector registers
     uint32_t w[sizeof(a) / 4];
@@ -799,23 +819,23 @@ __device__ __attribute__((noinline)) void pair_general(GemmF32Args a, lds_byte l
     for (uint32_t i = 0; i < sizeof(a) / 4; ++i) w[i] = __builtin_amdgcn_readfirstlane(w[i]);
     __builtin_memcpy(&a, w, sizeof(a));
     const uint32_t at = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)lds);
-    pair_tile<RB, NB, WR, WC, AKN, BKN, true>(a, (lds_byte)(uintptr_t)at, __builtin_amdgcn_readfirstlane(mode));
+    pair_tile<RB, NB, WR, WC, AKN, BKN, true, WEIGHT>(a, (lds_byte)(uintptr_t)at, __builtin_amdgcn_readfirstlane(mode));
 }
 
-template <int RB, int NB, int WR, int WC, bool AKN, bool BKN>
+template <int RB, int NB, int WR, int WC, bool AKN, bool BKN, bool WEIGHT = false>
 __global__ void __launch_bounds__(64 * WR * WC, 2) gemm_pair_kernel(GemmF32Args a) {
     extern __shared__ __align__(16) unsigned char smem[];
-    const int mode = pair_tile<RB, NB, WR, WC, AKN, BKN, false>(a, (lds_byte)smem, 0);
+    const int mode = pair_tile<RB, NB, WR, WC, AKN, BKN, false, WEIGHT>(a, (lds_byte)smem, 0);
     if (mode != kDone) {                                       // uniform
         __syncthreads();
-        pair_general<RB, NB, WR, WC, AKN, BKN>(a, (lds_byte)smem, mode);
+        pair_general<RB, NB, WR, WC, AKN, BKN, WEIGHT>(a, (lds_byte)smem, mode);
     }
 }
 
 template <int RB, int NB, int WR, int WC>
 __global__ void __launch_bounds__(64 * WR * WC, 2) gemm_pair_grad_kernel(GemmF32Args a, GradTail t) {
     extern __shared__ __align__(16) unsigned char smem[];
-    const int mode = pair_tile<RB, NB, WR, WC, false, true, false, true>(a, (lds_byte)smem, 0, &t);
+    const int mode = pair_tile<RB, NB, WR, WC, false, true, false, false, true>(a, (lds_byte)smem, 0, &t);
     if (mode == kDone) return;                                 // uniform
     __syncthreads();
     pair_general<RB, NB, WR, WC, false, true>(a, (lds_byte)smem, mode);
@@ -829,7 +849,7 @@ __global__ void __launch_bounds__(64 * WR * WC, 2) gemm_pair_grad_kernel(GemmF32
     });
 }
 
-template <int RB, int NB, int WR, int WC, bool AKN, bool BKN>
+template <int RB, int NB, int WR, int WC, bool AKN, bool BKN, bool WEIGHT = false>
 static hipError_t launch_pair(GemmF32Args a, hipStream_t st) {
     constexpr uint64_t TM = 16 * RB * WR, TN = 16 * NB * WC;
     constexpr uint64_t lds = 2 * 8 * (TM + TN) * 16 + (TM + TN) * 12 + 16;
@@ -840,10 +860,15 @@ static hipError_t launch_pair(GemmF32Args a, hipStream_t st) {
     const uint64_t total = (a.lower_only ? (uint64_t)a.tiles_m * (a.tiles_m + 1) / 2 : (uint64_t)a.tiles_m * a.tiles_n) * a.splits;
     if (total == 0 || total > 0x7FFFFFFFull) return hipErrorInvalidValue;
     static LdsOptIn opt_in;
-    hipError_t e = allow_large_lds(opt_in, reinterpret_cast<const void*>(gemm_pair_kernel<RB, NB, WR, WC, AKN, BKN>));
+    hipError_t e = allow_large_lds(opt_in, reinterpret_cast<const void*>(gemm_pair_kernel<RB, NB, WR, WC, AKN, BKN, WEIGHT>));
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((gemm_pair_kernel<RB, NB, WR, WC, AKN, BKN>), dim3((uint32_t)total), dim3(64 * WR * WC), lds, st, a);
+    hipLaunchKernelGGL((gemm_pair_kernel<RB, NB, WR, WC, AKN, BKN, WEIGHT>), dim3((uint32_t)total), dim3(64 * WR * WC), lds, st, a);
     return hipGetLastError();
+}
+
+hipError_t gemm_f32_pair_weighted(const GemmF32Args& a, hipStream_t st) {
+    if (a.M > 128 || !a.weight || !aligned(a.weight, 16) || gemm_f32_wide(a.lda > a.ldb ? a.lda : a.ldb)) return hipErrorInvalidValue;
+    return launch_pair<4, 4, 2, 4, false, false, true>(a, st);
 }
 
 hipError_t gemm_f32_pair_grad(const GemmF32Args& args, const GradTail& t, hipStream_t st) {

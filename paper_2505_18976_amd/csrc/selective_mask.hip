@@ -57,6 +57,17 @@ __global__ void __launch_bounds__(256) sm_weight_kernel(const float* __restrict_
     if (threadIdx.x == 0) sig_part[blockIdx.x] = total;
 }
 
+// sigma_j^2 for the columns of the weighted product, up to p_pad of them (zero from p on), and sums of sigma as above.
+__global__ void __launch_bounds__(256) sm_sigma_kernel(uint64_t p, uint64_t p_pad, const float* __restrict__ S, float inv_temp,
+                                                      float* __restrict__ weight, double* sig_part) {
+    __shared__ double red[256];
+    const uint64_t j = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+    const float sig = j < p ? sigmoidf(S[j] * inv_temp) : 0.0f;
+    if (j < p_pad) weight[j] = sig * sig;
+    const double total = block_sum((double)sig, red);
+    if (threadIdx.x == 0) sig_part[blockIdx.x] = total;
+}
+
 // One workgroup per test row t: Pearson correlation of A[t][:] and B[t][:] over the n train rows and the row
 // C[t][i] = (da_i / (|da||db|) - corr * db_i / |db|^2) / m; columns n..ld_c of C are zero.
 __global__ void __launch_bounds__(256) sm_corr_kernel(const float* A, uint64_t lda, const float* B, uint64_t ldb,
@@ -207,10 +218,23 @@ static grass_status sm_masked_scores(const SmLayout& L, unsigned char* base, con
                                      float* B, double* sig_part, hipStream_t hs) {
     float* Gtw = reinterpret_cast<float*>(base + L.off_gtw);
     const uint64_t ld_w = (p + 3) / 4 * 4;
-    hipLaunchKernelGGL(sm_weight_kernel, dim3((uint32_t)ceil_div(ld_w, 256), (uint32_t)(m < 16 ? m : 16)), dim3(256), 0, hs, Gt,
-                       ldgt, m, p, S, inv_temp, Gtw, ld_w, sig_part);
     const GemmPlan plan = sm_forward_plan(n, m, p);
     float* partials = reinterpret_cast<float*>(base + L.off_part);
+    // Where the product runs on tiles of 128 x 256 it weighs the test gradients on their way in, instead of a kernel that
+    // writes them weighted (100 rows of 1,863,690: 385 us).  Its vector of weights lies where those would be.
+    const uint64_t p_pad = (p + 31) / 32 * 32;
+    if (plan.pair && plan.tile == kTile128x256 && m > 64 && m <= 128 && S && !gemm_f32_wide(ldgt > ldg ? ldgt : ldg)) {
+        hipLaunchKernelGGL(sm_sigma_kernel, dim3((uint32_t)ceil_div(ld_w, 256)), dim3(256), 0, hs, p, p_pad, S, inv_temp, Gtw, sig_part);
+        GemmF32Args a{Gt, G, B, m, n, p, ldgt, ldg, L.n_pad, 0, 0, 0, 0, plan.splits, 0, Gtw};
+        if (plan.splits > 1) { a.C = partials; a.ldc = n; a.split_stride_c = m * n; }
+        if (gemm_f32_pair_weighted(a, hs) != hipSuccess) return GRASS_EHIP;
+        if (plan.splits > 1)
+            hipLaunchKernelGGL(reduce_partials_kernel, dim3((uint32_t)ceil_div(m * n, 256)), dim3(256), 0, hs, partials, m,
+                               (uint32_t)n, plan.splits, 1.0f, B, L.n_pad);
+        return GRASS_OK;
+    }
+    hipLaunchKernelGGL(sm_weight_kernel, dim3((uint32_t)ceil_div(ld_w, 256), (uint32_t)(m < 16 ? m : 16)), dim3(256), 0, hs, Gt,
+                       ldgt, m, p, S, inv_temp, Gtw, ld_w, sig_part);
     if (gemm_f32(false, false, Gtw, G, B, m, n, p, ld_w, ldg, L.n_pad, 0, 0, plan, partials, hs) != hipSuccess) return GRASS_EHIP;
     if (plan.splits > 1)
         hipLaunchKernelGGL(reduce_partials_kernel, dim3((uint32_t)ceil_div(m * n, 256)), dim3(256), 0, hs, partials, m,

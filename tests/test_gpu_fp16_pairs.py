@@ -115,6 +115,31 @@ def test_gradient_of_columns_that_the_sample_misjudges(grass, m, n, p, spoil):
     assert float((grad.double() - ref).abs().max()) <= 1e-5 * float(ref.abs().max())
 
 
+@pytest.mark.parametrize("m,n,p", [(100, 1_000, 20_001), (65, 600, 33_000), (128, 513, 8_193), (66, 300, 5_003)])
+@pytest.mark.parametrize("std", [0.5, 15.0])
+@pytest.mark.parametrize("spoil", [False, True])
+def test_weights_applied_on_the_way_in(grass, m, n, p, std, spoil):
+    """The forward product weighs the test gradients as it reads them: ragged p, weights from 1 to nothing, rows that the sample
+    misjudges.  Objective and gradient against double precision."""
+    G, Gt = synth.dense_normal(n, p, seed=7, device=_dev()), synth.dense_normal(m, p, seed=8, device=_dev())
+    S = synth.dense_normal(1, p, seed=9, device=_dev(), std=std).reshape(-1).contiguous()
+    if spoil:
+        Gt[3, 50], Gt[4, p - 1], Gt[5] = 2.0 ** 12, 2.0 ** 14, Gt[5] * 2.0 ** -60
+        Gt[6, : p // 2], S[p // 2:] = 0.0, S[p // 2:] - 12.0
+    sig, g, gt = torch.sigmoid(S.double()), G.double(), Gt.double()
+    A = (gt @ g.T.contiguous()).float()
+    b, a = (gt * sig ** 2) @ g.T.contiguous(), A.double()
+    da, db = a - a.mean(1, keepdim=True), b - b.mean(1, keepdim=True)
+    na, nb = da.norm(dim=1, keepdim=True), db.norm(dim=1, keepdim=True)
+    corr = (da * db).sum(1, keepdim=True) / (na * nb)
+    c = (da / (na * nb) - corr / nb ** 2 * db) / m
+    ds = sig * (1 - sig)
+    ref = 2 * sig * ds * (gt * (c @ g)).sum(0) - 1e-6 * ds
+    grad, obj = grass.grass_selective_mask_grad(G, Gt, A, S, 1e-6, 1.0)
+    assert abs(float(obj) - float(corr.mean() - 1e-6 * sig.sum())) <= 1e-5
+    assert float((grad.double() - ref).abs().max()) <= 1e-5 * float(ref.abs().max())
+
+
 def _odd_rows(X):
     """Rows that a sample of the first 32 k (and of three more groups in long ranges) misjudges."""
     K = X.shape[1]
