@@ -34,7 +34,7 @@
 //   100 x 1,000 x 1,863,690, A B^T, unaligned rows    3.3  -> 1.85
 //   100 x 327,680 x 1,000, A B                        0.50 -> 0.38
 // Two groups on their way instead of one (150 us for 64 x 65,536 x 2,048 either way) and vector instructions that are not
-// spread over the matrix instructions (4 % slower) did not pay.
+// spread over the matrix instructions (1 to 2 % slower) did not pay.
 #include <type_traits>
 
 #include "gemm_f32_device.h"
@@ -251,7 +251,7 @@ __device__ __forceinline__ int pair_tile(GemmF32Args a, lds_byte lds, int mode, 
     static_assert(!WEIGHT || !AKN, "weights");
     f32x4 xa[CA], xb[CB], za[CA], zb[CB];                      // a group on its way, the first group
     f32x4 xw, zw;                                              // the weights of the thread's k of these
-    auto weight_at = [&](uint32_t g) {
+    auto weight_at = [&](uint32_t g) -> f32x4 {
         if constexpr (WEIGHT) return *(gvec)((gfloat)a.weight + g0 * 32 + (uint64_t)g * 32 + 4 * (lane & 7));
         else return f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     };
