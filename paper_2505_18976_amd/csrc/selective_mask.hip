@@ -250,7 +250,7 @@ static grass_status sm_backward(const SmLayout& L, unsigned char* base, const fl
     for (uint64_t j0 = 0; j0 < p; j0 += L.pc) {
         const uint64_t pc = j0 + L.pc <= p ? L.pc : p - j0;
         // Rc (m x pc) = C G[:, j0 : j0+pc], a contraction over the n rows of G
-        const GemmPlan plan = gemm_f32_plan(false, true, m, pc, n, ldg, false, 1);
+        const GemmPlan plan = gemm_f32_plan(false, true, m, pc, n, ldg > L.n_pad ? ldg : L.n_pad, false, 1);      // rows of C, of G
         // With one row of tiles a workgroup has all rows of its columns of R, and the gradient comes out of its registers: the
         // round trip of R and a kernel behind every block are saved (100 rows, 327,680 columns: 379 + 53 -> 393 us; a step on 100 +
         // 1,000 rows of 1,863,690 0.3 ms).  Rc is scratch for tiles that have to be computed again.

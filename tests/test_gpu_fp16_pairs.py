@@ -115,6 +115,26 @@ def test_gradient_of_columns_that_the_sample_misjudges(grass, m, n, p, spoil):
     assert float((grad.double() - ref).abs().max()) <= 1e-5 * float(ref.abs().max())
 
 
+def test_gradient_of_more_train_rows_than_32_bit_offsets_reach(grass):
+    """2^26 train rows: the rows of the backward product's first operand are too far apart for the kernel that has the gradient
+    in its registers.  All train rows but 400 are zero, so the error bound of a sum is that of 400 terms."""
+    n, m, p, rows = 1 << 26, 2, 4, 400
+    G, A = torch.zeros(n, p, device=_dev()), torch.zeros(m, n, device=_dev())
+    at = torch.arange(rows, device=_dev()) * 167_771
+    G[at], A[:, at] = synth.dense_normal(rows, p, seed=7, device=_dev()), synth.dense_normal(m, rows, seed=10, device=_dev())
+    Gt, S = synth.dense_normal(m, p, seed=8, device=_dev()), synth.dense_normal(1, p, seed=9, device=_dev()).reshape(-1)
+    grad, _ = grass.grass_selective_mask_grad(G, Gt, A, S.contiguous(), 1e-3, 1.0)
+    sig, g, gt, a = torch.sigmoid(S.double()), G[at].double(), Gt.double(), A[:, at].double()
+    b = (gt * sig ** 2) @ g.T.contiguous()
+    ma, mb = a.sum(1, keepdim=True) / n, b.sum(1, keepdim=True) / n
+    na, nb = ((a ** 2).sum(1, keepdim=True) - n * ma ** 2).sqrt(), ((b ** 2).sum(1, keepdim=True) - n * mb ** 2).sqrt()
+    corr = ((a * b).sum(1, keepdim=True) - n * ma * mb) / (na * nb)
+    c = ((a - ma) / (na * nb) - corr / nb ** 2 * (b - mb)) / m
+    ds = sig * (1 - sig)
+    ref = 2 * sig * ds * (gt * (c @ g)).sum(0) - 1e-3 * ds
+    assert float((grad.double() - ref).abs().max()) <= 1e-5 * float(ref.abs().max())
+
+
 @pytest.mark.parametrize("m,n,p", [(100, 1_000, 20_001), (65, 600, 33_000), (128, 513, 8_193), (66, 300, 5_003)])
 @pytest.mark.parametrize("std", [0.5, 15.0])
 @pytest.mark.parametrize("spoil", [False, True])
