@@ -246,19 +246,20 @@ static grass_status sm_masked_scores(const SmLayout& L, unsigned char* base, con
 static grass_status sm_backward(const SmLayout& L, unsigned char* base, const float* G, uint64_t n, uint64_t ldg,
                                 const float* Gt, uint64_t m, uint64_t ldgt, uint64_t p, const float* S, float inv_temp,
                                 float lambda, const float* C, float* grad, hipStream_t hs) {
+    const uint64_t ld_max = ldg > L.n_pad ? ldg : L.n_pad;     // rows of G, of C
+    // With one row of tiles a workgroup has all rows of its columns of R = C G, and the gradient comes out of its registers: the
+    // round trip of R and a kernel behind every block are saved (100 rows, 327,680 columns: 379 + 53 -> 393 us).  As nothing has to
+    // stay in a cache all columns are one launch (100 + 1,000 rows of 1,863,690, two steps: 9.83 -> 9.78 ms for six a step).  Tiles
+    // that have to be computed again use the memory of the weighted test gradients.
+    if (m <= 128 && gemm_f32_plan(false, true, m, p, n, ld_max, false, 1).pair) {
+        const GemmF32Args a{C, G, reinterpret_cast<float*>(base + L.off_gtw), m, p, n, L.n_pad, ldg, (p + 3) / 4 * 4, 0, 0, 0, 0, 1, 0};
+        return gemm_f32_pair_grad(a, GradTail{Gt, ldgt, 0, S, inv_temp, lambda, grad}, hs) == hipSuccess ? GRASS_OK : GRASS_EHIP;
+    }
     float* Rc = reinterpret_cast<float*>(base + L.off_r);
     for (uint64_t j0 = 0; j0 < p; j0 += L.pc) {
         const uint64_t pc = j0 + L.pc <= p ? L.pc : p - j0;
         // Rc (m x pc) = C G[:, j0 : j0+pc], a contraction over the n rows of G
-        const GemmPlan plan = gemm_f32_plan(false, true, m, pc, n, ldg > L.n_pad ? ldg : L.n_pad, false, 1);      // rows of C, of G
-        // With one row of tiles a workgroup has all rows of its columns of R, and the gradient comes out of its registers: the
-        // round trip of R and a kernel behind every block are saved (100 rows, 327,680 columns: 379 + 53 -> 393 us; a step on 100 +
-        // 1,000 rows of 1,863,690 0.3 ms).  Rc is scratch for tiles that have to be computed again.
-        if (plan.pair && m <= 128) {
-            const GemmF32Args a{C, G + j0, Rc, m, pc, n, L.n_pad, ldg, L.pc, 0, 0, 0, 0, 1, 0};
-            if (gemm_f32_pair_grad(a, GradTail{Gt, ldgt, j0, S, inv_temp, lambda, grad}, hs) != hipSuccess) return GRASS_EHIP;
-            continue;
-        }
+        const GemmPlan plan = gemm_f32_plan(false, true, m, pc, n, ld_max, false, 1);
         if (gemm_f32(false, true, C, G + j0, Rc, m, pc, n, L.n_pad, ldg, L.pc, 0, 0, plan, nullptr, hs) != hipSuccess)
             return GRASS_EHIP;
         hipLaunchKernelGGL(sm_grad_kernel, dim3((uint32_t)ceil_div(pc, 64)), dim3(256), 0, hs, Gt, ldgt, m, Rc, L.pc, j0, pc,
