@@ -65,10 +65,10 @@ __device__ __forceinline__ GemmTile gemm_f32_tile(const GemmF32Args& a) {
 }
 
 // What the backward product R = C G of a Selective-Mask step is for: the gradient of its columns,
-// grad[j0 + c] = 2 sigma sigma' sum_t Gt[t][j0 + c] R[t][c] - lambda sigma' with sigma = sigmoid(S[j0 + c] inv_temp).
+// grad[c] = 2 sigma sigma' sum_t Gt[t][c] R[t][c] - lambda sigma' with sigma = sigmoid(S[c] inv_temp).
 struct GradTail {
     const float* Gt;
-    uint64_t ldgt, j0;
+    uint64_t ldgt;
     const float* S;
     float inv_temp, lambda;
     float* grad;

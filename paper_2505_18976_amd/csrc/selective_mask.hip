@@ -253,7 +253,7 @@ static grass_status sm_backward(const SmLayout& L, unsigned char* base, const fl
     // that have to be computed again use the memory of the weighted test gradients.
     if (m <= 128 && gemm_f32_plan(false, true, m, p, n, ld_max, false, 1).pair) {
         const GemmF32Args a{C, G, reinterpret_cast<float*>(base + L.off_gtw), m, p, n, L.n_pad, ldg, (p + 3) / 4 * 4, 0, 0, 0, 0, 1, 0};
-        return gemm_f32_pair_grad(a, GradTail{Gt, ldgt, 0, S, inv_temp, lambda, grad}, hs) == hipSuccess ? GRASS_OK : GRASS_EHIP;
+        return gemm_f32_pair_grad(a, GradTail{Gt, ldgt, S, inv_temp, lambda, grad}, hs) == hipSuccess ? GRASS_OK : GRASS_EHIP;
     }
     float* Rc = reinterpret_cast<float*>(base + L.off_r);
     for (uint64_t j0 = 0; j0 < p; j0 += L.pc) {

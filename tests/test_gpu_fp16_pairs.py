@@ -87,7 +87,8 @@ def test_second_operand_k_major(grass, m, n, p):
     assert float((grad.double() - ref).abs().max()) <= 1e-5 * float(ref.abs().max())
 
 
-@pytest.mark.parametrize("m,n,p", [(1, 256, 255), (100, 300, 257), (128, 300, 1_027), (17, 259, 4_098)])
+@pytest.mark.parametrize("m,n,p", [(1, 256, 255), (100, 300, 257), (128, 300, 1_027), (17, 259, 4_098), (64, 300, 129),
+                                   (65, 300, 127), (33, 1_000, 128)])
 @pytest.mark.parametrize("spoil", ["zeros", "late", "far", "infinite"])
 def test_gradient_of_columns_that_the_sample_misjudges(grass, m, n, p, spoil):
     """The gradient out of the backward product's registers, with columns of G that send their tile through the second attempt."""
