@@ -26,7 +26,7 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0            # MI355X published HBM3E bandwidth
-MFMA_PEAK_F32_TFLOPS = 2500.0 / 6     # an fp32 product is six bf16 products of the operands' pieces (csrc/gemm_split.hip)
+MFMA_PEAK_F32_TFLOPS = 2500.0 / 3     # an fp32 product is three fp16 products of the operands' pieces (csrc/gemm_pair.hip)
 MFMA_PEAK_BF16_TFLOPS = 2500.0
 
 # HBM traffic per launch of the headline kernel comes from the rocprofv3 --pmc summary under profiles/ (FETCH_SIZE and
