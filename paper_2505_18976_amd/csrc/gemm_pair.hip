@@ -552,8 +552,8 @@ __device__ __forceinline__ int pair_tile(GemmF32Args a, lds_byte lds, int mode, 
                         if (q < CA) {
                             stash(km_a, rare, xa, &xw, sa, wa, fsa[q], q, nxt);
                             if constexpr (FULL) {
-                                if (!AKN) xa[q] = load_a(q, gi + 2);
                                 if (WEIGHT && q == CA - 1) xw = weight_at(gi + 2);
+                                if (!AKN) xa[q] = load_a(q, gi + 2);
                                 else if (q == CA - 1) {
 #pragma unroll
                                     for (int r = 0; r < CA; ++r) xa[r] = load_a(r, gi + 2);
