@@ -1,26 +1,22 @@
-// fp32 products on the fp16 matrix cores: C[M x N] = or += A * B^T with fp32 operands, fp32 accumulation and an error that is
-// not larger than that of the products of three bf16 pieces (gemm_split.hip), for workgroups that contract at least 256 k.
+// fp32 products on the fp16 matrix cores: C[M x N] = or += A * B^T with fp32 operands and fp32 accumulation, for workgroups that
+// contract at least 256 k.  Sums are within the bound of the products of three bf16 pieces (gemm_split.hip), |error| <= 2^-23 (6
+// ceil(k / 16) + 65) sum |a b|, and on ordinary data closer than those.
 //
 // Every row of an operand ("slot") is scaled by a power of two and split into two fp16 numbers, a = a0 + a1 with a0 = fp16(a)
 // and a1 = fp16(a - a0), both rounded to nearest: 23 of the 24 significant bits, the last one with an error of one unit at
-// most.  Three of the four products of two such sums are accumulated by v_mfma_f32_16x16x32_f16; a1 b1 is below 2^-22 |a b|,
-// 2^-24.8 in the root mean square.  The sums take half as many roundings as six products of bf16 pieces do, which more than
-// makes up for the bit.  Error against fp64, 2-norm, one K range, normal data (three bf16 pieces in brackets): K = 64 1.1e-7
-// (1.1e-7), 256 1.9e-7 (2.4e-7), 1,024 3.6e-7 (4.9e-7), 4,096 7.1e-7 (1.0e-6); 100 x 1,000 x 1,863,690 in 64 ranges 5.9e-6
+// most (Markidis, Der Chien, Laure, Peng and Vetter, "NVIDIA tensor core programmability, performance & precision", 2018, split
+// fp32 operands so).  Three of the four products of two such sums are accumulated by v_mfma_f32_16x16x32_f16; a1 b1 is below
+// 2^-22 |a b|, 2^-24.8 in the root mean square.  The sums take half as many roundings as six products of bf16 pieces do, which
+// more than makes up for the bit.  Error against fp64, 2-norm, one K range, normal data (three bf16 pieces in brackets): K = 64
+// 1.1e-7 (1.1e-7), 256 1.9e-7 (2.4e-7), 1,024 3.6e-7 (4.9e-7), 4,096 7.1e-7 (1.0e-6); 100 x 1,000 x 1,863,690 in 64 ranges 5.9e-6
 // (1.1e-5); FIM of 65,536 x 4,096 rows 4.0e-7 (2.8e-6); largest deviations likewise.  Below 256 k there is next to nothing to
 // gain (launches start 8 us later, the bit shows), so shorter ranges stay with gemm_split.hip.
 //
-// Scales.  fp16 reaches from 2^-24 to 2^16.  A workgroup takes the largest |x| of 32 or 128 values of every slot (a group of
-// 32 k, with three more spread over ranges of 2,048 k and more) and scales it to 2^5..2^6: values up to 2^9 times the sample's
-// largest fit, smaller ones lose nothing above 2^-7 of it and are off by 2^-30 of it below.  A value that is too large
-// becomes infinite and makes every sum of its slot infinite or NaN, so the finished sums tell.  Slots whose sample is zero are
-// scaled like the largest of the tile, and their largest value is recorded on the way.  Where either does not fit, the tile
-// runs again with the largest values of the whole range (pair_general); where only infinities and NaNs were found, their
-// sums are contracted again by v_mfma_f32_16x16x4_f32.
-// A slot is of wide range if an eighth of the quads of its sample are 2^12 below its largest value or the largest value of
-// the range is 2^18 above that of the sample.  What is small beside that value is then known to few bits, which shows where
-// the other operand is zero at the large ones.  Such sums are found by their size, below 2^10 times the bound of what the
-// scale took from them (2^-25 a k), and contracted again if half of those of a row or column of 16 x 16 are so small.
+// Scales.  fp16 reaches from 2^-24 to 2^16.  A workgroup takes the largest |x| of a sample of every slot (a group of 32 k, another
+// one, two more in ranges of 2,048 k and more) and scales it to 2^9..2^10: values up to 2^6 times the sample's largest fit,
+// smaller ones lose nothing above 2^-11 of it and are off by 2^-34 of it below.  What that takes from a sum is judged by the
+// sample and by the size of the sum alone, once the sums are there.  The few that do not pass are summed again one by one in
+// fp64; where they are more, or a slot's sample is zero, the tile is computed again with three bf16 pieces.
 //
 // Bound: the power that the matrix cores and the data on the way to them draw.  1,024 x 65,536 x 4,096 takes 1.45 ms = 1,140
 // TFLOP/s of fp16 products at 1.5 GHz, matrix cores 74 % busy; without loads and splitting it would be 1.15 ms, a loop of
@@ -37,7 +33,7 @@
 // spread over the matrix instructions (1 to 2 % slower) did not pay.
 #include <type_traits>
 
-#include "gemm_f32_device.h"
+#include "gemm_split_device.h"
 
 namespace grass {
 
@@ -58,31 +54,23 @@ __device__ __forceinline__ float swap_lanes(float x) {
     return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xF, 0xF, true));
 }
 
-constexpr int kSampleTop = 5, kExactTop = 14;      // exponents to which the largest value of a sample, of a range is scaled
-constexpr int kGuessTop = 9, kLowest = 3;          // of a tile's samples, for slots whose own are zero; lowest for those to hold
-constexpr int kTiny = 12, kFar = 18;               // binades below the largest value: quads that make a sample, a range wide
+constexpr uint32_t kDone = 0, kExact = ~0u;
+constexpr int kSampleTop = 9;                      // exponent to which the largest value of a sample is scaled
 
-// One workgroup owns a TM x TN tile of C; its WR x WC wavefronts own RB x NB blocks of 16 x 16 each.  K is consumed in groups
-// of 32 through two LDS stages.  A group travels from memory into registers one group before it is split and stored, which
-// is spread over the multiplication of the group before it; a register is loaded again as soon as it is stored.  The barrier
-// of a group sits before its last row of blocks: by then every wavefront has the fragments of this group in registers and its
-// part of the next group in LDS.
-// AKN / BKN: the operand is stored K-major (K x M resp. K x N).
-// GENERAL: with everything that is rare.  It is a function of its own that is called where the kernel gives up, because in one
-// function the ways to it cost the main loop 50 to 200 registers that had to be spilled.
 typedef unsigned char __attribute__((address_space(3)))* lds_byte;
-
-enum : int { kDone = 0, kAgain = 1, kAgainExact = 2 };
 
 // The gradient of the columns of a tile from its R = `get(i, j, e)` (element e of block (i, j)), all rows of which it holds: a
 // lane multiplies its 4 columns with Gt and sums its rows in fp64, lanes and wavefronts are added in a fixed order.
-template <int RB, int NB, int WR, int WC, class Get>
-__device__ __forceinline__ void grad_tail(const GemmF32Args& a, const GradTail& t, double* part, uint64_t n0, Get get) {
+// CHECK: an R below <lost(i, e), col(j)> may have lost bits to the scales.  Where the sum over the rows of |Gt R| is not above that
+// of |Gt| times this, false is returned and nothing stored.
+template <int RB, int NB, int WR, int WC, bool CHECK, class Get, class Lost, class Col>
+__device__ __forceinline__ bool grad_tail(const GemmF32Args& a, const GradTail& t, double* part, uint64_t n0, Get get, Lost lost, Col col) {
     constexpr int TN = 16 * NB * WC;
     const int lane = threadIdx.x & 63, lq = lane >> 4, lc = lane & 15, wave = threadIdx.x >> 6, wm = wave / WC, wn = wave % WC;
     const uint64_t c0 = n0 + wn * NB * 16 + 4 * lc;
     const bool all = c0 + 4 <= a.N;
     double s[4] = {0.0, 0.0, 0.0, 0.0};
+    float size[4] = {0.0f, 0.0f, 0.0f, 0.0f}, lx[4] = {0.0f, 0.0f, 0.0f, 0.0f}, ly[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int i = 0; i < RB; ++i)
 #pragma unroll
@@ -98,21 +86,53 @@ __device__ __forceinline__ void grad_tail(const GemmF32Args& a, const GradTail& 
                 for (int j = 0; j < 4; ++j)
                     if (c0 + j < a.N) x[j] = gt[j];
             }
+            f32x2 l;
+            if constexpr (CHECK) l = lost(i, e);
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                if (all || c0 + j < a.N) s[j] += (double)x[j] * (double)get(i, j, e);
+                if (all || c0 + j < a.N) {
+                    const float r = get(i, j, e);
+                    s[j] += (double)x[j] * (double)r;
+                    if constexpr (CHECK) {
+                        size[j] = __builtin_fmaf(__builtin_fabsf(x[j]), __builtin_fabsf(r), size[j]);
+                        lx[j] = __builtin_fmaf(__builtin_fabsf(x[j]), l[0], lx[j]);
+                        ly[j] = __builtin_fmaf(__builtin_fabsf(x[j]), l[1], ly[j]);
+                    }
+                }
         }
+    float* const check = reinterpret_cast<float*>(part + WR * TN);
+    int* const vote = reinterpret_cast<int*>(check + WR * TN);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         s[j] += __shfl_xor(s[j], 16);
         s[j] += __shfl_xor(s[j], 32);
+        if constexpr (CHECK) {
+            const f32x2 c = col(j);
+            size[j] -= lx[j] * c[0] + ly[j] * c[1];
+            size[j] += __shfl_xor(size[j], 16);
+            size[j] += __shfl_xor(size[j], 32);
+        }
     }
-    __syncthreads();                                           // the stages are no longer read
+    __syncthreads();                                           // the memory of `part` is free
+    if (CHECK && threadIdx.x == 0) *vote = 0;
     if (lq == 0) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) part[wm * TN + wn * NB * 16 + 4 * lc + j] = s[j];
+        for (int j = 0; j < 4; ++j) {
+            part[wm * TN + wn * NB * 16 + 4 * lc + j] = s[j];
+            if constexpr (CHECK) check[wm * TN + wn * NB * 16 + 4 * lc + j] = size[j];
+        }
     }
     __syncthreads();
+    if constexpr (CHECK) {
+        for (int c = threadIdx.x; c < TN && n0 + c < a.N; c += 64 * WR * WC) {
+            float sum = check[c];
+#pragma unroll
+            for (int w = 1; w < WR; ++w) sum += check[w * TN + c];
+            if (!(sum >= 0.0f && sum < __builtin_inff())) *vote = 1;
+        }
+        __syncthreads();
+        if (*vote != 0) return false;                          // uniform
+    }
     for (int c = threadIdx.x; c < TN && n0 + c < a.N; c += 64 * WR * WC) {
         double sum = part[c];
 #pragma unroll
@@ -121,22 +141,111 @@ __device__ __forceinline__ void grad_tail(const GemmF32Args& a, const GradTail& 
         const float sig = sigmoidf(t.S[j] * t.inv_temp), dsig = sig * (1.0f - sig) * t.inv_temp;
         t.grad[j] = (float)(2.0 * (double)sig * (double)dsig * sum - (double)t.lambda * (double)dsig);
     }
+    return true;
 }
 
-// mode: kAgain, from the start; kAgainExact, with the largest values of the range (the samples' scales are in LDS and, unless
-// C accumulates, the finite sums in C).  Returns kDone or what is left to do.
-template <int RB, int NB, int WR, int WC, bool AKN, bool BKN, bool GENERAL, bool WEIGHT = false, bool GRAD = false>
-__device__ __forceinline__ int pair_tile(GemmF32Args a, lds_byte lds, int mode, const GradTail* tail = nullptr) {
+// What a function that is not inlined is handed arrives in vector registers; this puts it back.
+template <class T>
+__device__ __forceinline__ T uniform(T x) {
+    uint32_t w[sizeof(T) / 4];
+    __builtin_memcpy(w, &x, sizeof(T));
+#pragma unroll
+    for (uint32_t i = 0; i < sizeof(T) / 4; ++i) w[i] = __builtin_amdgcn_readfirstlane(w[i]);
+    __builtin_memcpy(&x, w, sizeof(T));
+    return x;
+}
+__device__ __forceinline__ unsigned char* uniform_lds(lds_byte p) { return (unsigned char*)(lds_byte)(uintptr_t)uniform((uint32_t)(uintptr_t)p); }
+
+// The rare ends of a tile are functions of their own: in one function they cost the main loop registers that it has to spill.
+template <int RB, int NB, int WR, int WC, bool AKN, bool BKN, bool WEIGHT>
+__device__ __attribute__((noinline)) void sum_again(GemmF32Args a, lds_byte lds, uint32_t total) {
+    constexpr uint32_t NW = WR * WC, THREADS = 64 * NW;
+    static_assert((NW == 4 || NW == 8) && 128 * NW * (4 + 8 * NW) <= 2 * 8 * 16 * 16 * (RB * WR + NB * WC), "LDS of the stages");
+    a = uniform(a);
+    total = uniform(total);
+    unsigned char* const smem = uniform_lds(lds);
+    const uint32_t* const list = reinterpret_cast<const uint32_t*>(smem);        // [128 NW]
+    double* const parts = reinterpret_cast<double*>(smem + 128 * NW * 4);
+    const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const auto [tm, tn, split] = gemm_f32_tile(a);
+    a.C += split * a.split_stride_c;
+    const uint64_t m0 = (uint64_t)tm * (16 * RB * WR), n0 = (uint64_t)tn * (16 * NB * WC);
+    const uint64_t ng_all = (a.K + 31) / 32, k_begin = split * ng_all / a.splits * 32, k_last = (split + 1) * ng_all / a.splits * 32;
+    const uint64_t k_end = k_last < a.K ? k_last : a.K;
+    const float kr = (float)(k_end - k_begin);
+            // The sums that did not pass, in fp64 straight from memory; of long ranges by several wavefronts, whose parts are added in
+            // their order.
+            const uint32_t share = total >= NW || kr < 2048.0f ? 1 : kr < 4096.0f ? 2 : kr < 8192.0f || NW == 4 ? 4 : 8, part_no = wave % share;
+                            #pragma unroll 1
+            for (uint32_t t = wave / share; t < total; t += NW / share) {
+                const uint32_t at = __builtin_amdgcn_readfirstlane(list[t]);
+                const uint64_t row = m0 + (at >> 16), col = n0 + (at & 0xFFFFu);
+                const gfloat pa = (gfloat)(AKN ? a.A + row : a.A + row * a.lda), pb = (gfloat)(BKN ? a.B + col : a.B + col * a.ldb);
+                double sum = 0.0;
+                auto dot = [&](auto full, uint64_t k0) {           // 256 k a turn, 4 a lane
+                    constexpr int U = decltype(full)::value ? 4 : 1;
+                    f32x4 ya[U], yb[U];
+    #pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const uint64_t k = k0 + 256 * u + 4 * lane;
+                        if constexpr (decltype(full)::value && !AKN) ya[u] = *(gvec)(pa + k);
+                        if constexpr (decltype(full)::value && !BKN) yb[u] = *(gvec)(pb + k);
+    #pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const bool ok = decltype(full)::value || k + q < k_end;
+                            if constexpr (!decltype(full)::value || AKN) ya[u][q] = ok ? pa[AKN ? (k + q) * a.lda : k + q] : 0.0f;
+                            if constexpr (!decltype(full)::value || BKN) yb[u][q] = ok ? pb[BKN ? (k + q) * a.ldb : k + q] : 0.0f;
+                            if constexpr (WEIGHT) ya[u][q] *= ok ? a.weight[k + q] : 0.0f;
+                        }
+                    }
+    #pragma unroll
+                    for (int u = 0; u < U; ++u)
+    #pragma unroll
+                        for (int q = 0; q < 4; ++q) sum = __builtin_fma((double)ya[u][q], (double)yb[u][q], sum);
+                };
+                uint64_t k0 = k_begin + 1024 * part_no;
+    #pragma unroll 1
+                for (; k0 + 1024 <= k_end; k0 += 1024 * share) dot(std::true_type{}, k0);
+                const uint64_t k1 = k0 + 1024 < k_end ? k0 + 1024 : k_end;                // of at most one of them
+    #pragma unroll 1
+                for (; k0 < k1; k0 += 256) dot(std::false_type{}, k0);
+    #pragma unroll
+                for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+                if (lane == 0) parts[t * share + part_no] = sum;
+            }
+                    __syncthreads();
+            for (uint32_t t = threadIdx.x; t < total; t += THREADS) {
+                double sum = parts[t * share];
+                for (uint32_t q = 1; q < share; ++q) sum += parts[t * share + q];
+                float* const c = a.C + (m0 + (list[t] >> 16)) * a.ldc + n0 + (list[t] & 0xFFFFu);
+                *c = a.accumulate ? *c + (float)sum : (float)sum;
+            }
+}
+
+// One workgroup owns a TM x TN tile of C; its WR x WC wavefronts own RB x NB blocks of 16 x 16 each.  K is consumed in groups
+// of 32 through two LDS stages.  A group travels from memory into registers one group before it is split and stored, which
+// is spread over the multiplication of the group before it; a register is loaded again as soon as it is stored.  The barrier
+// of a group sits before its last row of blocks: by then every wavefront has the fragments of this group in registers and its
+// part of the next group in LDS.
+// AKN / BKN: the operand is stored K-major (K x M resp. K x N).
+// Returns kDone, kExact (the tile's data do not suit two fp16 pieces; nothing has been stored) or how many sums are left for
+// sum_again.
+template <int RB, int NB, int WR, int WC, bool AKN, bool BKN, bool WEIGHT = false, bool GRAD = false>
+__device__ __forceinline__ uint32_t pair_tile(GemmF32Args a, lds_byte lds, const GradTail* tail = nullptr) {
     unsigned char* const smem = (unsigned char*)lds;
     constexpr int NW = WR * WC, THREADS = 64 * NW;
     constexpr int TM = 16 * RB * WR, TN = 16 * NB * WC, SLOTS = TM + TN;
     constexpr int CA = TM / (8 * NW), CB = TN / (8 * NW), NC = CA + CB;      // chunks of 4 fp32 per thread and group
     static_assert(TM % (8 * NW) == 0 && TN % (8 * NW) == 0 && (!AKN || CA == 4) && (!BKN || CB == 4) && NB == 4, "loading map");
     constexpr int kReg = SLOTS * 16, kPlane = 4 * kReg, kStage = 2 * kPlane;
-    uint32_t* const mx = reinterpret_cast<uint32_t*>(smem + 2 * kStage);      // [SLOTS] largest |x| of a slot (bits)
+    uint32_t* const mx = reinterpret_cast<uint32_t*>(smem + 2 * kStage);      // [SLOTS] largest |x| of a slot's sample (bits), then
+    float* const nrm = reinterpret_cast<float*>(mx);                          //         its squares, then the slot's 2-norm (scaled)
     int* const ex = reinterpret_cast<int*>(mx + SLOTS);                       // [SLOTS] exponent of a slot's scale
-    uint32_t* const wd = mx + 2 * SLOTS;                                      // [SLOTS] a slot of wide range
-    uint32_t* const mt = mx + 3 * SLOTS;                                      // largest of the samples of A, of B; two votes
+    uint32_t* const few = mx + 2 * SLOTS;                                     // [SLOTS] values of the sample that the scale leaves few bits,
+    float* const gam = reinterpret_cast<float*>(few);                         //         then what that means for the slot
+    int* const bias = reinterpret_cast<int*>(mx + 3 * SLOTS);                 // [SLOTS] sum of what they lose, away from zero, in 2^-33,
+    float* const odd = reinterpret_cast<float*>(bias);                        //         then the share of gam against an ordinary row, < 0: odd row
+    uint32_t* const mt = mx + 4 * SLOTS;                                      // a vote, a count
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave / WC, wn = wave % WC;
     const auto [tm, tn, split] = gemm_f32_tile(a);
@@ -271,10 +380,25 @@ __device__ __forceinline__ int pair_tile(GemmF32Args a, lds_byte lds, int mode, 
     if ((AKN && m0 + TM > a.M) || (BKN && n0 + TN > a.N)) {    // slots past the edge that nothing is stored in
         for (int t = threadIdx.x; t < 2 * kStage / 16; t += THREADS) reinterpret_cast<f32x4*>(smem)[t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     }
+    // What the scales may take from a sum.  The pieces are off by 2^-23 of a value, and of values below 2^-2 (scaled) by up to 2^-25.
+    // Products of three bf16 pieces are within 2^-23 (6 ceil(k / 16) + 65) sum |a b|, those of two fp16 pieces, but for values below
+    // 2^-2, within 2^-23 (3 ceil(k / 32) + 64) + 2^-21.  In between there is room for an error of 2^-25 / unit times sum |a b|.  Values
+    // from 4 unit on take half of it at most.  n smaller ones in a row a take at most 2^-25 sqrt(n) |b|_2, and likewise for b; the
+    // other half has room for that if the sum, which is at most sum |a b|, is not below 2 unit (gam_a |b|_2 + gam_b |a|_2), gam =
+    // sqrt(n).  That much is lost if all errors have one sign.  Otherwise they add up to 2^-25 sqrt(f / 3) |b|_2 in the root mean
+    // square, f = n / k, whatever n is, and seven times that is gam = 4 sqrt(f).  f is twice what the sample says.  The mean of the
+    // errors in the sample, as far as it is more than chance makes it (1.2 / sqrt(c) for c of them), is the part that has one sign,
+    // as equal values have; half where the sample has too few to tell.  gam is 2 at least, for up to four such values that the sample
+    // does not show.  |a|_2 is sqrt(2) times what the sample says, and a value of 2^12 that it does not show.
+    // A row is ordinary if 24 of 32 values in the sample are 4 and more.  Two of them meet at enough k for sum |a b| to be above that
+    // whatever the sum is (0.5 of their sums per tile of 1,000 x 50,001 x 4,096 would not pass, and cost 5 us at the end of a
+    // launch).  What the n small values of an odd row meet in an ordinary one is rather n / k of it: min(1, 2 sqrt(f)), at least
+    // 1/4, of gam counts.
+    // Values too large for their scale, infinities and NaNs leave sums that are not finite.
+    const uint64_t k_begin = g0 * 32, k_end = (g0 + ng) * 32 < a.K ? (g0 + ng) * 32 : a.K;
+    const float kr = (float)(k_end - k_begin), unit = 0.25f / (0.28125f * kr - 3.0f);
     f32x4 acc[RB][NB];
-    int attempt = 0;
-    bool scan = GENERAL && mode == kAgainExact, reload = false, again = false;
-    for (;;) {
+    {
         const int ln = hide(threadIdx.x & 63);
         const uint32_t ga = lane_load(km_a, sa, ln), gb = lane_load(km_b, sb, ln);
         gfloat pa[CA];
@@ -308,78 +432,14 @@ __device__ __forceinline__ int pair_tile(GemmF32Args a, lds_byte lds, int mode, 
                 for (int i = 0; i < CB; ++i) yb[i] = load_part(km_b, pb[i], sb, cb[i] ? gb_cut : gb, i, g, lp);
             }
         };
-        // ---- scales: from a sample of the range, or (second attempt) from all of it
-        if (GENERAL && scan) {                                 // uniform: the largest values of the whole range
-            for (int t = threadIdx.x; t < SLOTS; t += THREADS) mx[t] = 0;
-            float qa[CA], qb[CB];
-#pragma unroll
-            for (int i = 0; i < CA; ++i) qa[i] = 0.0f;
-#pragma unroll
-            for (int i = 0; i < CB; ++i) qb[i] = 0.0f;
-            uint32_t s = 0;
-#pragma unroll 1
-            for (; s + 3 < nf; s += 3) {
-                f32x4 ya[3][CA], yb[3][CB];
-#pragma unroll
-                for (int t = 0; t < 3; ++t) {
-#pragma unroll
-                    for (int i = 0; i < CA; ++i) { ya[t][i] = load_a(i, s + t); weigh(ya[t][i], weight_at(s + t)); }
-#pragma unroll
-                    for (int i = 0; i < CB; ++i) yb[t][i] = load_b(i, s + t);
-                }
-#pragma unroll
-                for (int t = 0; t < 3; ++t) {
-#pragma unroll
-                    for (int i = 0; i < CA; ++i) qa[i] = __builtin_fmaxf(qa[i], largest(values(km_a, ya[t], i)));
-#pragma unroll
-                    for (int i = 0; i < CB; ++i) qb[i] = __builtin_fmaxf(qb[i], largest(values(km_b, yb[t], i)));
-                }
-            }
-#pragma unroll 1
-            for (; s < ng; ++s) {
-                fetch(za, zb, zw, s);
-#pragma unroll
-                for (int i = 0; i < CA; ++i) {
-                    weigh(za[i], zw);
-                    qa[i] = __builtin_fmaxf(qa[i], largest(values(km_a, za, i)));
-                }
-#pragma unroll
-                for (int i = 0; i < CB; ++i) qb[i] = __builtin_fmaxf(qb[i], largest(values(km_b, zb, i)));
-            }
-            __syncthreads();
-            if (threadIdx.x == 0) mt[2] = 0;
-#pragma unroll
-            for (int i = 0; i < CA; ++i) atomicMax(&mx[slot_of(km_a, sa, ln, i)], __float_as_uint(qa[i]));
-#pragma unroll
-            for (int i = 0; i < CB; ++i) atomicMax(&mx[slot_of(km_b, sb, ln, i)], __float_as_uint(qb[i]));
-            __syncthreads();
-            bool off = false;
-            for (int t = threadIdx.x; t < SLOTS; t += THREADS) {
-                const uint32_t u = mx[t];
-                if (u == 0 || u >= 0x7F800000u) continue;      // infinite: its sums are not finite, whatever the scale
-                const int e = lead_exponent(u) + ex[t];
-                off |= e > kExactTop || (e < kLowest && ex[t] < 127);
-                if (e > kSampleTop + kFar) { wd[t] = 1; mt[3] = 1; }
-            }
-            if (off) mt[2] = 1;
-            __syncthreads();
-            if (mt[2] == 0 && !(mode == kAgainExact && a.accumulate)) {               // uniform: infinities only
-                reload = mode == kAgainExact;                  // the results are stored
-                break;
-            }
-            attempt = 1;
-            fetch(za, zb, zw, 0);
-            fetch(xa, xb, xw, 1);
-        }
-        bool track = false;
-        if (attempt == 0) {
-            fetch(za, zb, zw, 0);
-            for (int t = threadIdx.x; t < SLOTS; t += THREADS) mx[t] = wd[t] = 0;
-            if (threadIdx.x < 4) mt[threadIdx.x] = 0;
+        // ---- scales, from a sample of the range
+        {
             constexpr int QS = 4;                              // groups of the sample
-            float qa[QS][CA], qb[QS][CB];
+            fetch(za, zb, zw, 0);
+            for (int t = threadIdx.x; t < SLOTS; t += THREADS) mx[t] = few[t] = bias[t] = 0;
+            if (threadIdx.x < 2) mt[threadIdx.x] = 0;
             f32x4 ya[QS][CA], yb[QS][CB];
-            const bool more = ng >= 64 && nf + 1 >= ng;        // uniform: three more groups of a long range
+            const bool more = ng >= 64 && nf + 1 >= ng;        // uniform: three more groups of a long range, one of a short one
             // The last one holds the diagonal, if the range does: that of a nearly diagonal matrix (an inverse) towers above the
             // rest of its rows.
             auto last_sample = [&](const Side& o, int i) {
@@ -393,9 +453,9 @@ __device__ __forceinline__ int pair_tile(GemmF32Args a, lds_byte lds, int mode, 
 #pragma unroll
                 for (int i = 0; i < CB; ++i) yb[t][i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
             }
-            if (more) {
 #pragma unroll
-                for (int t = 1; t < QS; ++t) {
+            for (int t = 1; t < QS; ++t)
+                if (more || (t == QS - 1 && nf + 1 >= ng)) {
 #pragma unroll
                     for (int i = 0; i < CA; ++i) {
                         const uint32_t at = t < QS - 1 ? t * (ng / QS) : last_sample(sa, i);
@@ -405,26 +465,18 @@ __device__ __forceinline__ int pair_tile(GemmF32Args a, lds_byte lds, int mode, 
 #pragma unroll
                     for (int i = 0; i < CB; ++i) yb[t][i] = load_b(i, t < QS - 1 ? t * (ng / QS) : last_sample(sb, i));
                 }
-            }
             fetch(xa, xb, xw, 1);
 #pragma unroll
             for (int i = 0; i < CA; ++i) { ya[0][i] = za[i]; weigh(ya[0][i], zw); }
 #pragma unroll
             for (int i = 0; i < CB; ++i) yb[0][i] = zb[i];
-#pragma unroll
-            for (int t = 0; t < QS; ++t) {
-#pragma unroll
-                for (int i = 0; i < CA; ++i) qa[t][i] = largest(values(km_a, ya[t], i));
-#pragma unroll
-                for (int i = 0; i < CB; ++i) qb[t][i] = largest(values(km_b, yb[t], i));
-            }
             // The 8 lanes that hold a row agree on its largest value; a column is spread over wavefronts.
-            auto post = [&](auto km, const Side& o, const auto& q, int n, uint32_t* top) {
-                float all = 0.0f;
+            auto post = [&](auto km, const Side& o, const auto& y, int n) {
 #pragma unroll
                 for (int i = 0; i < n; ++i) {
-                    float m = __builtin_fmaxf(__builtin_fmaxf(q[0][i], q[1][i]), __builtin_fmaxf(q[2][i], q[3][i]));
-                    all = __builtin_fmaxf(all, m);
+                    float m = 0.0f;
+#pragma unroll
+                    for (int t = 0; t < QS; ++t) m = __builtin_fmaxf(m, largest(values(km, y[t], i)));
                     if constexpr (decltype(km)::value) {
                         atomicMax(&mx[slot_of(km, o, ln, i)], __float_as_uint(m));
                     } else {
@@ -434,49 +486,81 @@ __device__ __forceinline__ int pair_tile(GemmF32Args a, lds_byte lds, int mode, 
                         mx[slot_of(km, o, ln, i)] = __float_as_uint(m);
                     }
                 }
-                atomicMax(top, __float_as_uint(all));
             };
             __syncthreads();
-            post(km_a, sa, qa, CA, &mt[0]);
-            post(km_b, sb, qb, CB, &mt[1]);
+            post(km_a, sa, ya, CA);
+            post(km_b, sb, yb, CB);
             __syncthreads();
-            auto tiny = [&](auto km, const Side& o, const auto& q, int n) {
+            auto inside = [&](auto km, const Side& o, int t) { // a slot in front of the edge
+                const int s = t - o.slot0;
+                return o.first + (decltype(km)::value ? (s & ~63) + 4 * (s & 15) + ((s >> 4) & 3) : s) < o.rows;
+            };
+            bool zero = false;
+            for (int t = threadIdx.x; t < SLOTS; t += THREADS) {
+                const uint32_t u = mx[t];
+                zero |= u == 0 && (t < TM ? inside(km_a, sa, t) : inside(km_b, sb, t));
+                ex[t] = u ? clamp_exponent(kSampleTop - lead_exponent(u)) : 0;
+                mx[t] = 0;
+            }
+            if (zero) mt[0] = 1;
+            __syncthreads();
+            if (mt[0] != 0) return kExact;                     // uniform: nothing to scale a slot by
+            // What one of the groups, 32 values of a slot, says about the others
+            auto count = [&](auto km, const Side& o, const auto& y, int n) {
+                const uint32_t top = (__float_as_uint(4.0f * unit) << 1) - 1;
 #pragma unroll
                 for (int i = 0; i < n; ++i) {
                     const int slot = slot_of(km, o, ln, i);
-                    const float small = __uint_as_float(mx[slot]) * (1.0f / (1 << kTiny));
-                    uint32_t c = 0;
+                    const f32x4 v = values(km, y, i) * __builtin_ldexpf(1.0f, ex[slot]);
+                    float q = 0.0f;
+                    uint32_t least = ~0u, c = 0;
 #pragma unroll
-                    for (int t = 0; t < QS; ++t) c += q[t][i] < small && q[t][i] > 0.0f;
-                    if (c) atomicAdd(&wd[slot], c);
+                    for (int e = 0; e < 4; ++e) {
+                        const uint32_t u = (__float_as_uint(v[e]) << 1) - 1;          // order of |v|, zero above all
+                        q = __builtin_fmaf(v[e], v[e], q);
+                        least = u < least ? u : least;
+                        c += __builtin_fabsf(v[e]) >= 4.0f;
+                    }
+                    atomicAdd(&mx[slot], (uint32_t)q);         // at most 2^25 in all
+                    c <<= 16;
+                    if (__any(least < top)) {                  // uniform
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) c += (__float_as_uint(v[e]) << 1) - 1 < top;
+                    }
+                    atomicAdd(&few[slot], c);
                 }
             };
-            tiny(km_a, sa, qa, CA);
-            tiny(km_b, sb, qb, CB);
+            count(km_a, sa, ya[QS - 1], CA);
+            count(km_b, sb, yb[QS - 1], CB);
             __syncthreads();
-        }
-        auto inside = [&](auto km, const Side& o, int t) {     // a slot in front of the edge
-            const int s = t - o.slot0;
-            return o.first + (decltype(km)::value ? (s & ~63) + 4 * (s & 15) + ((s >> 4) & 3) : s) < o.rows;
-        };
-        bool zero = false;
-        for (int t = threadIdx.x; t < SLOTS; t += THREADS) {
-            const uint32_t u = mx[t], all = mt[t >= TM];
-            if (attempt) {
-                ex[t] = u ? clamp_exponent(kExactTop - lead_exponent(u)) : 0;
-            } else {
-                const bool wide = wd[t] >= 4;
-                wd[t] = wide;
-                if (wide) mt[3] = 1;
-                zero |= u == 0 && (t < TM ? inside(km_a, sa, t) : inside(km_b, sb, t));
-                ex[t] = u ? clamp_exponent(kSampleTop - lead_exponent(u)) : all ? clamp_exponent(kGuessTop - lead_exponent(all)) : 0;
+            auto lose = [&](auto km, const Side& o, const auto& y, int n) {
+#pragma unroll
+                for (int i = 0; i < n; ++i) {
+                    const int slot = slot_of(km, o, ln, i);
+                    if (!__any((few[slot] & 0xFFFFu) >= 4)) continue;                 // uniform
+                    const f32x4 v = values(km, y, i) * __builtin_ldexpf(1.0f, ex[slot]);
+                    int r = 0;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float x = __builtin_fabsf(v[e]), h = (float)(_Float16)x;
+                        if (x < 4.0f * unit) r += (int)(((x - h) - (float)(_Float16)(x - h)) * 8589934592.0f);
+                    }
+                    if (r) atomicAdd(&bias[slot], r);
+                }
+            };
+            lose(km_a, sa, ya[QS - 1], CA);
+            lose(km_b, sb, yb[QS - 1], CB);
+            __syncthreads();
+            for (int t = threadIdx.x; t < SLOTS; t += THREADS) {
+                const bool in = t < TM ? inside(km_a, sa, t) : inside(km_b, sb, t);
+                const float c = (float)(few[t] & 0xFFFFu), f = (2.0f * c + (c > 0.0f)) * (1.0f / 32.0f);
+                const float lean = c < 4.0f ? 0.5f : __builtin_fabsf((float)bias[t]) / (256.0f * c) - 1.2f * __builtin_amdgcn_rsqf(c);
+                const float share = __builtin_fmaxf(0.25f, __builtin_fminf(1.0f, 2.0f * __builtin_sqrtf(f)));
+                odd[t] = few[t] >> 16 < 24 ? -share : share;
+                nrm[t] = in ? __builtin_sqrtf((float)mx[t] * (kr / 16.0f) + 16777216.0f) : 0.0f;
+                gam[t] = in ? __builtin_fmaxf(2.0f, __builtin_sqrtf(f) * __builtin_fmaxf(4.0f, lean * __builtin_sqrtf(kr))) : 0.0f;
             }
-            mx[t] = 0;
         }
-        if (zero) mt[2] = 1;
-        __syncthreads();
-        track = attempt == 0 && mt[2] != 0;                    // uniform
-        if (!GENERAL && track) return kAgain;
         float fsa[CA], fsb[CB];                                // scales of the thread's slots
         // Rows past the edge are scaled by zero: products with zero take less of the power that limits the clock.
         auto scale_of = [&](auto km, const Side& o, int i) {
@@ -495,8 +579,8 @@ __device__ __forceinline__ int pair_tile(GemmF32Args a, lds_byte lds, int mode, 
 #pragma unroll
         for (int i = 0; i < (BKN ? CB : 1); ++i) wb[i] = in_plane(km_b, sb, ln, slot_of(km_b, sb, ln, i));
 
-        // Two fp16 pieces of 4 values.  `rare`: there are slots without a sample, whose largest value is wanted.
-        auto stash = [&](auto km, auto rare, const auto& x, const f32x4* wt, const Side& o, const uint32_t* w, float scale, int i, uint32_t stage) {
+        // Two fp16 pieces of 4 values.
+        auto stash = [&](auto km, const auto& x, const f32x4* wt, const uint32_t* w, float scale, int i, uint32_t stage) {
             f32x4 v = values(km, x, i);
             if (wt) weigh(v, *wt);
             u32x2 p0, p1;
@@ -508,9 +592,6 @@ __device__ __forceinline__ int pair_tile(GemmF32Args a, lds_byte lds, int mode, 
                                                                 (_Float16)__builtin_fmaf(v[e + 1], scale, -(float)h[1])}));
             }
             unsigned char* st = smem + (decltype(km)::value ? w[i] + stage : ((w[0] + stage) ^ ((i & 1) * 128)) + (i >> 1) * 256);
-            if constexpr (decltype(rare)::value) {
-                if (track) atomicMax(&mx[slot_of(km, o, hide(threadIdx.x & 63), i)], __float_as_uint(largest(v * scale)));
-            }
             *reinterpret_cast<u32x2*>(st) = p0;
             *reinterpret_cast<u32x2*>(st + kPlane) = p1;
         };
@@ -531,14 +612,13 @@ __device__ __forceinline__ int pair_tile(GemmF32Args a, lds_byte lds, int mode, 
         // ---- pipeline
         const std::true_type yes;
         const std::false_type no;
-        const std::integral_constant<bool, GENERAL> rare;
 #pragma unroll
-        for (int i = 0; i < CA; ++i) stash(km_a, rare, za, &zw, sa, wa, fsa[i], i, 0);
+        for (int i = 0; i < CA; ++i) stash(km_a, za, &zw, wa, fsa[i], i, 0);
 #pragma unroll
-        for (int i = 0; i < CB; ++i) stash(km_b, rare, zb, nullptr, sb, wb, fsb[i], i, 0);
+        for (int i = 0; i < CB; ++i) stash(km_b, zb, nullptr, wb, fsb[i], i, 0);
         Frag fa[2], fb[NB];
         uint32_t cur = 0, g = 0;
-        auto group = [&](auto full, auto rare, uint32_t gi) {
+        auto group = [&](auto full, uint32_t gi) {
             constexpr bool FULL = decltype(full)::value;
             const uint32_t nxt = kStage - cur;
             const uint32_t a_cur = a_ofs + cur;
@@ -550,7 +630,7 @@ __device__ __forceinline__ int pair_tile(GemmF32Args a, lds_byte lds, int mode, 
                     for (int q = 0; q < NC; ++q) {
                         if (q * (RB - 1) / NC != i) continue;
                         if (q < CA) {
-                            stash(km_a, rare, xa, &xw, sa, wa, fsa[q], q, nxt);
+                            stash(km_a, xa, &xw, wa, fsa[q], q, nxt);
                             if constexpr (FULL) {
                                 if (WEIGHT && q == CA - 1) xw = weight_at(gi + 2);
                                 if (!AKN) xa[q] = load_a(q, gi + 2);
@@ -561,7 +641,7 @@ __device__ __forceinline__ int pair_tile(GemmF32Args a, lds_byte lds, int mode, 
                             }
                         } else {
                             const int r = q - CA;
-                            stash(km_b, rare, xb, nullptr, sb, wb, fsb[r], r, nxt);
+                            stash(km_b, xb, nullptr, wb, fsb[r], r, nxt);
                             if constexpr (FULL) {
                                 if (!BKN) xb[r] = load_b(r, gi + 2);
                                 else if (r == CB - 1) {
@@ -579,9 +659,9 @@ __device__ __forceinline__ int pair_tile(GemmF32Args a, lds_byte lds, int mode, 
                 }
                 // products of pieces, small terms first.  The last block of rows goes column by column: the fragments of B
                 // are replaced as they fall free, so that one set of them is enough.
-                constexpr int qa[3] = {1, 0, 0}, qb[3] = {0, 1, 0};
+                constexpr int ka[3] = {1, 0, 0}, kb[3] = {0, 1, 0};
                 auto mma = [&](int j, int t) {
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fa[i & 1].p[qa[t]], fb[j].p[qb[t]], acc[i][j], 0, 0, 0);
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fa[i & 1].p[ka[t]], fb[j].p[kb[t]], acc[i][j], 0, 0, 0);
                 };
                 if (i + 1 < RB) {
 #pragma unroll
@@ -615,116 +695,93 @@ __device__ __forceinline__ int pair_tile(GemmF32Args a, lds_byte lds, int mode, 
 #pragma unroll
         for (int j = 0; j < NB; ++j) load(fb[j], b_ofs, j);
         load(fa[0], a_ofs, 0);
-        for (; g + 2 < nf; ++g) group(yes, rare, g);
-        for (; g < ng; ++g) group(no, rare, g);
+        for (; g + 2 < nf; ++g) group(yes, g);
+        for (; g < ng; ++g) group(no, g);
 
-        // ---- check of the scales
-        if (attempt) break;
-        __syncthreads();
-        if (threadIdx.x == 0) mt[2] = 0;
-        __syncthreads();
-        float sum = 0.0f;                                      // a value too large for its scale: none of its sums is finite
-#pragma unroll
-        for (int i = 0; i < RB; ++i)
-#pragma unroll
-            for (int j = 0; j < NB; ++j)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) sum = __builtin_fmaf(acc[i][j][e], 0.0f, sum);
-        bool off = !(sum == 0.0f);
-        if (track)
-            for (int t = threadIdx.x; t < SLOTS; t += THREADS) off |= mx[t] != 0 && lead_exponent(mx[t]) < kLowest && ex[t] < 127;
-        if (off) mt[2] = 1;
-        __syncthreads();
-        if (mt[2] == 0) break;                                 // uniform
-        if constexpr (!GENERAL) {
-            if (a.accumulate) return kAgainExact;
-            again = true;
-            break;
-        }
-        scan = true;
-        __syncthreads();
     }
 
-    // ---- results
-    {
-        const int ln = hide(threadIdx.x & 63), lq = ln >> 4, lc = ln & 15;
-        auto a_row = [&](int i, int r) {                       // row of A in slot r of the wavefront's block i of 16
-            const int s = wm * RB * 16 + i * 16 + r;
-            return m0 + (AKN ? (s & ~63) + 4 * (s & 15) + ((s >> 4) & 3) : s);
+    // ---- check of the sums; the stages are no longer read
+    uint32_t* const list = reinterpret_cast<uint32_t*>(smem);
+    const int ln = hide(threadIdx.x & 63), lq = ln >> 4, lc = ln & 15;
+    __syncthreads();
+    auto a_row = [&](int i, int r) {                           // row of A in slot r of the wavefront's block i of 16
+        const int s = wm * RB * 16 + i * 16 + r;
+        return m0 + (AKN ? (s & ~63) + 4 * (s & 15) + ((s >> 4) & 3) : s);
+    };
+    auto b_col = [&](int j) {                                  // column of C in block j of the lane
+        const int s = wn * NB * 16 + j * 16 + lc;
+        return n0 + (BKN ? (s & ~63) + 4 * (s & 15) + ((s >> 4) & 3) : s);
+    };
+    const int* const ea = ex + wm * RB * 16 + 4 * lq;
+    const int* const eb = ex + TM + wn * NB * 16 + lc;
+    const float* const na = nrm + wm * RB * 16 + 4 * lq;
+    const float* const nb = nrm + TM + wn * NB * 16 + lc;
+    const float* const ga = gam + wm * RB * 16 + 4 * lq;
+    const float* const gb = gam + TM + wn * NB * 16 + lc;
+    const float* const oa = odd + wm * RB * 16 + 4 * lq;
+    const float* const ob = odd + TM + wn * NB * 16 + lc;
+    if constexpr (GRAD) {
+        auto r = [&](int i, int j, int e) { return __builtin_ldexpf(acc[i][j][e], -(ea[i * 16 + e] + eb[j * 16])); };
+        auto lost = [&](int i, int e) {
+            const float x = __builtin_ldexpf(2.0f * unit, -ea[i * 16 + e]);
+            return f32x2{x * na[i * 16 + e], x * ga[i * 16 + e]};
         };
-        auto b_col = [&](int j) {                              // column of C in block j of the lane
-            const int s = wn * NB * 16 + j * 16 + lc;
-            return n0 + (BKN ? (s & ~63) + 4 * (s & 15) + ((s >> 4) & 3) : s);
-        };
-        const int* const ea = ex + wm * RB * 16 + 4 * lq;
-        const int* const eb = ex + TM + wn * NB * 16 + lc;
-        if (GENERAL && reload) {                               // uniform
-#pragma unroll
-            for (int i = 0; i < RB; ++i)
-#pragma unroll
-                for (int j = 0; j < NB; ++j)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const uint64_t row = a_row(i, 4 * lq + e), col = b_col(j);
-                        acc[i][j][e] = row < a.M && col < a.N ? __builtin_ldexpf(a.C[row * a.ldc + col], ea[i * 16 + e] + eb[j * 16]) : 0.0f;
-                    }
-        }
-        // Sums to be contracted again on the fp32 matrix instructions, 4 bits each (e) of the 4 blocks of a row of blocks.
-        uint32_t todo[(RB + 1) / 2];
+        auto col = [&](int j) { return f32x2{__builtin_ldexpf(gb[j * 16], -eb[j * 16]), __builtin_ldexpf(nb[j * 16], -eb[j * 16])}; };
+        return grad_tail<RB, NB, WR, WC, true>(a, *tail, reinterpret_cast<double*>(smem), n0, r, lost, col) ? kDone : kExact;
+    } else {
+        // Sums that do not pass, 4 bits each (e) of the 4 blocks of a row of blocks.  Slots without a value other than zero have
+        // nothing to lose.
+        const bool interior = m0 + TM <= a.M && n0 + TN <= a.N;                       // uniform
+        uint32_t todo[(RB + 1) / 2], n = 0;
 #pragma unroll
         for (int i = 0; i < (RB + 1) / 2; ++i) todo[i] = 0;
-        if (GENERAL) {                                         // otherwise they are finite, or this is not the end of it
 #pragma unroll
-            for (int i = 0; i < RB; ++i)
+        for (int i = 0; i < RB; ++i) {
+            float worst = 0.0f, sum = 0.0f;                    // cheaply first: 128 sums a lane
 #pragma unroll
-                for (int j = 0; j < NB; ++j)
+            for (int e = 0; e < 4; ++e) {
+                const float x = 2.0f * unit * na[i * 16 + e], g = 2.0f * unit * ga[i * 16 + e];
 #pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (!__builtin_isfinite(acc[i][j][e])) todo[i / 2] |= 1u << ((i & 1) * 16 + j * 4 + e);
-        }
-        if (mt[3] != 0) {                                      // uniform: slots of wide range
-            const uint64_t kr = (g0 + ng) * 32 < a.K ? (uint64_t)ng * 32 : a.K - g0 * 32;
-            const float low = (float)kr * (attempt ? 2.0f : 1.0f / 64.0f);        // 2^10 2^-25 kr twice 2^15, 2^8
-            const uint32_t* const wa = wd + wm * RB * 16 + 4 * lq;
-            const uint32_t* const wb = wd + TM + wn * NB * 16 + lc;
-#pragma unroll 1
-            for (int i = 0; i < RB; ++i)
-#pragma unroll 1
                 for (int j = 0; j < NB; ++j) {
-                    f32x4 x;
+                    worst = __builtin_fmaxf(worst, __builtin_fmaf(x, gb[j * 16], __builtin_fmaf(g, nb[j * 16], -__builtin_fabsf(acc[i][j][e]))));
+                    sum = __builtin_fmaf(acc[i][j][e], 0.0f, sum);
+                }
+            }
+            if (!__any(!(worst <= 0.0f && sum == 0.0f))) continue;                    // uniform
 #pragma unroll
-                    for (int i2 = 0; i2 < RB; ++i2)
+            for (int e = 0; e < 4; ++e) {
+                const float x = 2.0f * unit * na[i * 16 + e], g = 2.0f * unit * ga[i * 16 + e];
+                const bool in = interior || a_row(i, 4 * lq + e) < a.M;
 #pragma unroll
-                        for (int j2 = 0; j2 < NB; ++j2)
-                            if (i2 == i && j2 == j) x = acc[i2][j2];
-                    uint32_t f = 0, bad = 0;
+                for (int j = 0; j < NB; ++j) {
+                    const float p = oa[i * 16 + e], q = ob[j * 16];
+                    const float low = p > 0.0f && q > 0.0f ? 0.0f : x * gb[j * 16] * (p < 0.0f ? 1.0f : __builtin_fabsf(q)) +
+                                                                    g * nb[j * 16] * (q < 0.0f ? 1.0f : __builtin_fabsf(p));
+                    const float v = __builtin_fabsf(acc[i][j][e]);
+                    if (!(v >= low && v < __builtin_inff()) && in && (interior || b_col(j) < a.N)) todo[i / 2] |= 1u << ((i & 1) * 16 + j * 4 + e);
+                }
+            }
+        }
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        if (__builtin_fabsf(x[e]) < low) f |= 1u << e;
-                        const uint32_t in_row = __builtin_popcount((uint32_t)(__ballot(f >> e & 1) >> (16 * lq)) & 0xFFFFu);
-                        if (in_row >= 8 && wa[i * 16 + e] != 0) bad |= 1u << e;
-                    }
-                    int in_col = __builtin_popcount(f);
-                    in_col += __shfl_xor(in_col, 16);
-                    in_col += __shfl_xor(in_col, 32);
-                    if (in_col >= 8 && wb[j * 16] != 0) bad = 15;
-                    bad = (bad & f) << ((i & 1) * 16 + j * 4);
+        for (int i = 0; i < (RB + 1) / 2; ++i) n += __builtin_popcount(todo[i]);
+        // As many of them as can be summed one by one in half the time that the tile takes with three bf16 pieces (1,000 x 50,001 x
+        // 4,096: 2 us each for a wavefront; a column of a K-major operand is a line of 128 bytes per value, 50 us for 9,362 of them).
+        const uint32_t limit = AKN ? 2 * NW : BKN ? 4 * NW : NW * (kr < 2048.0f ? (uint32_t)kr / 16 : 128);
+        if (n != 0) {
+            uint32_t at = atomicAdd(&mt[1], n);
 #pragma unroll
-                    for (int i2 = 0; i2 < (RB + 1) / 2; ++i2)
-                        if (i2 == i / 2) todo[i2] |= bad;
+            for (int q = 0; q < (RB + 1) / 2; ++q)
+                for (uint32_t w = todo[q]; w != 0; w &= w - 1, ++at) {
+                    const int bit = __builtin_ctz(w), i = 2 * q + (bit >> 4), j = bit >> 2 & 3, e = bit & 3;
+                    if (at < limit) list[at] = (uint32_t)(a_row(i, 4 * lq + e) - m0) << 16 | (uint32_t)(b_col(j) - n0);
                 }
         }
-        if constexpr (GRAD) {
-            if (!again && mt[3] == 0) {                        // uniform: none of the sums is in question
-                grad_tail<RB, NB, WR, WC>(a, *tail, reinterpret_cast<double*>(smem), n0, [&](int i, int j, int e) {
-                    return __builtin_ldexpf(acc[i][j][e], -(ea[i * 16 + e] + eb[j * 16]));
-                });
-                return kDone;
-            }
-            if (!again) return kAgain;
-        }
-        const bool interior = m0 + TM <= a.M && n0 + TN <= a.N && !a.accumulate;         // uniform
-        const bool quads = BKN && interior && a.ldc % 4 == 0 && (reinterpret_cast<uintptr_t>(a.C) & 15) == 0;
+        __syncthreads();
+        const uint32_t total = mt[1];
+        if (total > limit) return kExact;                      // uniform
+
+        // ---- results
+        const bool quads = BKN && interior && !a.accumulate && a.ldc % 4 == 0 && (reinterpret_cast<uintptr_t>(a.C) & 15) == 0;
 #pragma unroll
         for (int i = 0; i < RB; ++i)
 #pragma unroll
@@ -741,118 +798,71 @@ __device__ __forceinline__ int pair_tile(GemmF32Args a, lds_byte lds, int mode, 
 #pragma unroll
                     for (int j = 0; j < NB; ++j) {
                         const uint64_t col = b_col(j);
-                        if (interior) c[col] = v[j];
+                        if (interior && !a.accumulate) c[col] = v[j];
                         else if (row < a.M && col < a.N && !(a.accumulate && (todo[i / 2] >> ((i & 1) * 16 + j * 4 + e) & 1)))
                             c[col] = a.accumulate ? c[col] + v[j] : v[j];
                     }
                 }
             }
-        if (again) return kAgainExact;
-        uint32_t any = 0;
-#pragma unroll
-        for (int i = 0; i < (RB + 1) / 2; ++i) any |= todo[i];
-        // Blocks with such sums are contracted again with v_mfma_f32_16x16x4_f32, straight from memory, and only those sums
-        // replaced.  A lane holds k 4 (lane / 16)..+3 of every 16 (the order inside a contraction is free).
-        if (__builtin_expect(__any(any != 0), 0)) {
-            const uint64_t k_begin = g0 * 32, k_end = (g0 + ng) * 32 < a.K ? (g0 + ng) * 32 : a.K;
-#pragma unroll 1
-            for (int t = 0; t < RB * NB; ++t) {
-                const int i = t / NB, j = t % NB;
-                uint32_t bad = 0;
-#pragma unroll
-                for (int q = 0; q < (RB + 1) / 2; ++q) bad = q == i / 2 ? todo[q] : bad;
-                bad = bad >> ((i & 1) * 16 + j * 4) & 15u;
-                uint64_t row = a_row(i, lc), col = b_col(j);
-                bool use = false;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) use |= (bad >> e & 1) && a_row(i, 4 * lq + e) < a.M && col < a.N;
-                if (!__any(use)) continue;                     // uniform
-                row = row < a.M ? row : a.M - 1;               // past the edge: never stored
-                const uint64_t colc = col < a.N ? col : a.N - 1;
-                const gfloat pa = (gfloat)(AKN ? a.A + row : a.A + row * a.lda);
-                const gfloat pb = (gfloat)(BKN ? a.B + colc : a.B + colc * a.ldb);
-                f32x4 sum{0.0f, 0.0f, 0.0f, 0.0f};
-                auto contract = [&](auto all, uint64_t k0, auto n) {                  // 16 n of k, loaded together
-                    f32x4 ya[decltype(n)::value], yb[decltype(n)::value];
-#pragma unroll
-                    for (int u = 0; u < decltype(n)::value; ++u) {
-                        const uint64_t k = k0 + 16 * u + 4 * lq;
-                        if constexpr (decltype(all)::value && !AKN) ya[u] = *(gvec)(pa + k);
-                        if constexpr (decltype(all)::value && !BKN) yb[u] = *(gvec)(pb + k);
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            const bool ok = decltype(all)::value || k + q < k_end;
-                            if constexpr (!decltype(all)::value || AKN) ya[u][q] = ok ? pa[AKN ? (k + q) * a.lda : k + q] : 0.0f;
-                            if constexpr (!decltype(all)::value || BKN) yb[u][q] = ok ? pb[BKN ? (k + q) * a.ldb : k + q] : 0.0f;
-                            if constexpr (WEIGHT) ya[u][q] *= ok ? a.weight[k + q] : 0.0f;
-                        }
-                    }
-#pragma unroll
-                    for (int u = 0; u < decltype(n)::value; ++u)
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) sum = __builtin_amdgcn_mfma_f32_16x16x4f32(ya[u][q], yb[u][q], sum, 0, 0, 0);
-                };
-                uint64_t k0 = k_begin;
-                for (; k0 + 128 <= k_end; k0 += 128) contract(std::true_type{}, k0, std::integral_constant<int, 8>{});
-                for (; k0 < k_end; k0 += 16) contract(std::false_type{}, k0, std::integral_constant<int, 1>{});
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (bad >> e & 1) {
-                        const uint64_t r = a_row(i, 4 * lq + e);
-                        if (r < a.M && col < a.N) {
-                            float* c = a.C + r * a.ldc + col;
-                            *c = a.accumulate ? *c + sum[e] : sum[e];
-                        }
-                    }
-            }
-        }
+        return total;
     }
-    return kDone;
 }
 
-template <int RB, int NB, int WR, int WC, bool AKN, bool BKN, bool WEIGHT = false>
-__device__ __attribute__((noinline)) void pair_general(GemmF32Args a, lds_byte lds, int mode) {
-    // arguments of a function that is not inlined arrive in vector registers
-    uint32_t w[sizeof(a) / 4];
-    __builtin_memcpy(w, &a, sizeof(a));
-#pragma unroll
-    for (uint32_t i = 0; i < sizeof(a) / 4; ++i) w[i] = __builtin_amdgcn_readfirstlane(w[i]);
-    __builtin_memcpy(&a, w, sizeof(a));
-    const uint32_t at = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)lds);
-    pair_tile<RB, NB, WR, WC, AKN, BKN, true, WEIGHT>(a, (lds_byte)(uintptr_t)at, __builtin_amdgcn_readfirstlane(mode));
+// A tile that pair_tile gives up, on three bf16 pieces.
+template <int RB, int NB, int WR, int WC, bool AKN, bool BKN, bool WEIGHT>
+__device__ __attribute__((noinline)) void exact_tile(GemmF32Args a, lds_byte lds) {
+    constexpr int TM = 16 * RB * WR, TN = 16 * NB * WC;
+    a = uniform(a);
+    unsigned char* const smem = uniform_lds(lds);
+    const auto [tm, tn, split] = gemm_f32_tile(a);
+    a.C += split * a.split_stride_c;
+    const uint64_t ng_all = (a.K + 31) / 32, g0 = split * ng_all / a.splits, ng = (split + 1) * ng_all / a.splits - g0;
+    const uint64_t m0 = (uint64_t)tm * TM, n0 = (uint64_t)tn * TN;
+    constexpr uint32_t lds_bytes = 2 * 8 * (TM + TN) * 16;     // the stages of pair_tile
+    if constexpr (RB == 8) {
+        static_assert(split_lds<4, 2, 2, 4>() <= lds_bytes && TM == 256 && TN == 256, "256 x 256");
+        split_tile<4, 2, 2, 4, AKN, BKN, false, WEIGHT>(a, smem, threadIdx.x, m0, n0, g0, ng);
+    } else if constexpr (WC == 8) {
+        static_assert(split_lds<2, 2, 1, 8>() <= lds_bytes && TM == 64 && TN == 512, "64 x 512");
+        split_tile<2, 2, 1, 8, AKN, BKN, false, WEIGHT>(a, smem, threadIdx.x, m0, n0, g0, ng);
+    } else {                                                   // halves of 128 x 128, 4 wavefronts each; TM == 64 has no rows 64..127
+        constexpr uint32_t half = split_lds<2, 2, 2, 2>();
+        static_assert(half * (TN / 128) <= lds_bytes && TM <= 128 && TN / 128 * 4 == WR * WC, "128 x 128");
+        const uint32_t h = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
+        split_tile<2, 2, 2, 2, AKN, BKN, false, WEIGHT>(a, smem + h * half, threadIdx.x & 255, m0, n0 + h * 128, g0, ng);
+    }
 }
 
 template <int RB, int NB, int WR, int WC, bool AKN, bool BKN, bool WEIGHT = false>
 __global__ void __launch_bounds__(64 * WR * WC, 2) gemm_pair_kernel(GemmF32Args a) {
     extern __shared__ __align__(16) unsigned char smem[];
-    const int mode = pair_tile<RB, NB, WR, WC, AKN, BKN, false, WEIGHT>(a, (lds_byte)smem, 0);
-    if (mode != kDone) {                                       // uniform
-        __syncthreads();
-        pair_general<RB, NB, WR, WC, AKN, BKN, WEIGHT>(a, (lds_byte)smem, mode);
-    }
+    const uint32_t left = pair_tile<RB, NB, WR, WC, AKN, BKN, WEIGHT>(a, (lds_byte)smem);
+    if (left == kDone) return;                                 // uniform
+    __builtin_amdgcn_s_waitcnt(0x0F70);                        // vmcnt == 0: what is stored is there
+    __syncthreads();
+    if (left == kExact) exact_tile<RB, NB, WR, WC, AKN, BKN, WEIGHT>(a, (lds_byte)smem);
+    else sum_again<RB, NB, WR, WC, AKN, BKN, WEIGHT>(a, (lds_byte)smem, left);
 }
 
 template <int RB, int NB, int WR, int WC>
 __global__ void __launch_bounds__(64 * WR * WC, 2) gemm_pair_grad_kernel(GemmF32Args a, GradTail t) {
     extern __shared__ __align__(16) unsigned char smem[];
-    const int mode = pair_tile<RB, NB, WR, WC, false, true, false, false, true>(a, (lds_byte)smem, 0, &t);
-    if (mode == kDone) return;                                 // uniform
+    if (pair_tile<RB, NB, WR, WC, false, true, false, true>(a, (lds_byte)smem, &t) == kDone) return;         // uniform
     __syncthreads();
-    pair_general<RB, NB, WR, WC, false, true>(a, (lds_byte)smem, mode);
+    exact_tile<RB, NB, WR, WC, false, true, false>(a, (lds_byte)smem);
+    __builtin_amdgcn_s_waitcnt(0x0F70);                        // vmcnt == 0: R is stored
     __syncthreads();
-    // every lane reads back what it stored itself
     const uint64_t n0 = (uint64_t)gemm_f32_tile(a).tn * (16 * NB * WC);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const uint64_t c0 = n0 + (wave % WC) * NB * 16 + 4 * (lane & 15);
-    grad_tail<RB, NB, WR, WC>(a, t, reinterpret_cast<double*>(smem), n0, [&](int i, int j, int e) {
-        return a.C[(uint64_t)((wave / WC * RB + i) * 16 + 4 * (lane >> 4) + e) * a.ldc + c0 + j];
-    });
+    auto r = [&](int i, int j, int e) { return a.C[(uint64_t)((wave / WC * RB + i) * 16 + 4 * (lane >> 4) + e) * a.ldc + c0 + j]; };
+    grad_tail<RB, NB, WR, WC, false>(a, t, reinterpret_cast<double*>(smem), n0, r, [](int, int) { return f32x2{}; }, [](int) { return f32x2{}; });
 }
 
 template <int RB, int NB, int WR, int WC, bool AKN, bool BKN, bool WEIGHT = false>
 static hipError_t launch_pair(GemmF32Args a, hipStream_t st) {
     constexpr uint64_t TM = 16 * RB * WR, TN = 16 * NB * WC;
-    constexpr uint64_t lds = 2 * 8 * (TM + TN) * 16 + (TM + TN) * 12 + 16;
+    constexpr uint64_t lds = 2 * 8 * (TM + TN) * 16 + (TM + TN) * 16 + 16;
     static_assert(lds <= kLdsBytes, "LDS");
     a.tiles_m = (uint32_t)ceil_div(a.M, TM);
     a.tiles_n = (uint32_t)ceil_div(a.N, TN);
@@ -874,7 +884,7 @@ hipError_t gemm_f32_pair_weighted(const GemmF32Args& a, hipStream_t st) {
 template <int RB, int NB, int WR, int WC>
 static hipError_t launch_pair_grad(GemmF32Args a, const GradTail& t, hipStream_t st) {
     constexpr uint64_t TM = 16 * RB * WR, TN = 16 * NB * WC;
-    constexpr uint64_t lds = 2 * 8 * (TM + TN) * 16 + (TM + TN) * 12 + 16;
+    constexpr uint64_t lds = 2 * 8 * (TM + TN) * 16 + (TM + TN) * 16 + 16;
     a.tiles_m = 1;
     a.tiles_n = (uint32_t)ceil_div(a.N, TN);
     static LdsOptIn opt_in;

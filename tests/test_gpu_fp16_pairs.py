@@ -214,6 +214,66 @@ def test_large_values_that_meet_zeros_k_major(grass, N, k):
     assert bool(((got - ref).abs() <= _bound(G.T, G.T, scale=False))[ok].all()) and bool(torch.isinf(got[~ok]).all())
 
 
+def _strict(got, A, B):
+    """got = A B^T within the bound of products of three bf16 pieces, |got - exact| <= 2^-23 (6 ceil(K / 16) + 65) sum |a b|: nothing
+    is allowed for values that are small beside others of their row."""
+    a, b = A.double(), B.double()
+    bound = (6 * -(-A.shape[1] // 16) + 65) * 2.0 ** -23 * (a.abs() @ b.abs().T.contiguous())
+    off = (got.double() - a @ b.T.contiguous()).abs() > bound
+    assert not bool(off.any()), (int(off.sum()), off.nonzero()[:5].tolist())
+
+
+@pytest.mark.parametrize("M,N,K", [(60, 200, 5_000), (1_000, 4_000, 1_000),           # 128 x 128 (the first without a workspace)
+                                   (128, 33_000, 1_000), (2_048, 8_192, 1_000)])      # 128 x 256, 256 x 256
+@pytest.mark.parametrize("spike", [2.0 ** 13, 2.0 ** 22, 2.0 ** 30])
+@pytest.mark.parametrize("at", [5, 700])
+def test_sums_that_miss_the_large_value_of_their_row(grass, M, N, K, spike, at):
+    """A test row has one large value; 0 to 12 of every 16 train rows are zero there, the others are not.  Their sums are those of
+    the rest of the row, to the bits of the rest, whatever the neighbouring sums are."""
+    te, tr = synth.dense_normal(M, K, seed=41, device=_dev()), synth.dense_normal(N, K, seed=42, device=_dev())
+    te[[3, 17, M - 1], at] = spike
+    block, inside = torch.arange(N, device=_dev()) // 16, torch.arange(N, device=_dev()) % 16
+    zero = inside < torch.tensor([0, 1, 4, 7, 8, 12], device=_dev())[block % 6]
+    tr[zero, at] = 0.0
+    for ws in ({}, {"ws": None}):
+        _strict(grass.grass_score(tr, te, **ws), te, tr)
+    if N <= 4_000:
+        _strict(grass.grass_score(te, tr), tr, te)
+
+
+@pytest.mark.parametrize("M,N,K", [(60, 200, 5_000), (1_000, 4_000, 1_000), (128, 33_000, 1_000), (2_048, 8_192, 1_000)])
+@pytest.mark.parametrize("fall", [12, 20, 24, 27])
+def test_rows_whose_first_values_tower_above_the_rest(grass, M, N, K, fall):
+    te, tr = synth.dense_normal(M, K, seed=43, device=_dev()), synth.dense_normal(N, K, seed=44, device=_dev())
+    te[:40, 20:] *= 2.0 ** -fall
+    tr[1::3, :20] = 0.0
+    tr[5::48, :K - 40] = 0.0                 # and rows with few values
+    for ws in ({}, {"ws": None}):
+        _strict(grass.grass_score(tr, te, **ws), te, tr)
+
+
+@pytest.mark.parametrize("N,k", [(5_000, 1_024), (500, 4_000), (501, 3_999)])         # 128 x 128, 256 x 256, both K-major
+@pytest.mark.parametrize("spike", [2.0 ** 13, 2.0 ** 22, 2.0 ** 30])
+def test_columns_that_miss_the_large_value_of_another(grass, N, k, spike):
+    G = synth.dense_normal(N, k, seed=45, device=_dev())
+    col = torch.arange(k, device=_dev())
+    for row in (3, N - 1):
+        G[row, col % 16 < (col // 16) % 13] = 0.0
+        G[row, 40 + row % 16] = spike
+    G[20:, 100] *= 2.0 ** -20                # the first values tower above the rest,
+    G[:20, col % 48 == 7] = 0.0              # where others are zero
+    _strict(grass.grass_fim(G) * N, G.T, G.T)
+
+
+def test_rows_with_one_value(grass):
+    """The sums are single products of values that are small beside the largest of their row."""
+    te, tr = synth.dense_normal(300, 1_000, seed=46, device=_dev()), torch.zeros(5_000, 1_000, device=_dev())
+    tr[torch.arange(5_000), torch.arange(5_000) % 1_000] = synth.dense_normal(1, 5_000, seed=47, device=_dev())[0]
+    for ws in ({}, {"ws": None}):
+        _strict(grass.grass_score(tr, te, **ws), te, tr)
+        _strict(grass.grass_score(te, tr, **ws), tr, te)
+
+
 @pytest.mark.parametrize("M,N,K", [(70, 90, 20_001), (40, 5_000, 515), (300, 50_000, 270), (2_048, 8_192, 257)])
 def test_non_finite_operands(grass, M, N, K):
     te, tr = synth.dense_normal(M, K, seed=31, device=_dev()), synth.dense_normal(N, K, seed=32, device=_dev())
