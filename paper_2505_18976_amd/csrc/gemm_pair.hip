@@ -12,11 +12,11 @@
 // (1.1e-5); FIM of 65,536 x 4,096 rows 4.0e-7 (2.8e-6); largest deviations likewise.  Below 256 k there is next to nothing to
 // gain (launches start 8 us later, the bit shows), so shorter ranges stay with gemm_split.hip.
 //
-// Scales.  fp16 reaches from 2^-24 to 2^16.  A workgroup takes the largest |x| of a sample of every slot (a group of 32 k, another
-// one, two more in ranges of 2,048 k and more) and scales it to 2^9..2^10: values up to 2^6 times the sample's largest fit,
-// smaller ones lose nothing above 2^-11 of it and are off by 2^-34 of it below.  What that takes from a sum is judged by the
-// sample and by the size of the sum alone, once the sums are there.  The few that do not pass are summed again one by one in
-// fp64; where they are more, or a slot's sample is zero, the tile is computed again with three bf16 pieces.
+// Scales.  fp16 reaches from 2^-24 to 2^16.  A workgroup takes the largest |x| of a sample of every slot, 64 values or more, and scales it
+// to 2^9..2^10: values up to 2^6 times the sample's largest fit, smaller ones lose nothing above 2^-11 of it and are off by 2^-34
+// of it below.  What that takes from a sum is judged by the sample and by the size of the sum alone, once the sums are there.
+// The few that do not pass are summed again one by one in fp64; where they are more, the tile is computed again with three
+// bf16 pieces.  Tiles of scattered values go there at once.
 //
 // Bound: the power that the matrix cores and the data on the way to them draw.  1,024 x 65,536 x 4,096 takes 1.45 ms = 1,140
 // TFLOP/s of fp16 products at 1.5 GHz, matrix cores 74 % busy; without loads and splitting it would be 1.15 ms, a loop of
@@ -49,9 +49,16 @@ __device__ __forceinline__ int lead_exponent(uint32_t bits) {
 }
 __device__ __forceinline__ int clamp_exponent(int e) { return e < -126 ? -126 : e > 127 ? 127 : e; }
 
-template <int CTRL>
-__device__ __forceinline__ float swap_lanes(float x) {
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xF, 0xF, true));
+template <int CTRL, class T>
+__device__ __forceinline__ T swap_lanes(T x) {
+    return __builtin_bit_cast(T, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), CTRL, 0xF, 0xF, true));
+}
+// `f` over 8 neighbouring lanes, in all of them: quad_perm 1 0 3 2, quad_perm 2 3 0 1, row_half_mirror.
+template <class T, class F>
+__device__ __forceinline__ T over_8_lanes(T x, F f) {
+    x = f(x, swap_lanes<0xB1>(x));
+    x = f(x, swap_lanes<0x4E>(x));
+    return f(x, swap_lanes<0x141>(x));
 }
 
 constexpr uint32_t kDone = 0, kExact = ~0u;
@@ -156,7 +163,8 @@ __device__ __forceinline__ T uniform(T x) {
 }
 __device__ __forceinline__ unsigned char* uniform_lds(lds_byte p) { return (unsigned char*)(lds_byte)(uintptr_t)uniform((uint32_t)(uintptr_t)p); }
 
-// The rare ends of a tile are functions of their own: in one function they cost the main loop registers that it has to spill.
+// The sums of a tile that did not pass, in fp64 straight from memory.  The rare ends of a tile are functions of their own: in one
+// function they cost the main loop registers that it has to spill.
 template <int RB, int NB, int WR, int WC, bool AKN, bool BKN, bool WEIGHT>
 __device__ __attribute__((noinline)) void sum_again(GemmF32Args a, lds_byte lds, uint32_t total) {
     constexpr uint32_t NW = WR * WC, THREADS = 64 * NW;
@@ -173,53 +181,57 @@ __device__ __attribute__((noinline)) void sum_again(GemmF32Args a, lds_byte lds,
     const uint64_t ng_all = (a.K + 31) / 32, k_begin = split * ng_all / a.splits * 32, k_last = (split + 1) * ng_all / a.splits * 32;
     const uint64_t k_end = k_last < a.K ? k_last : a.K;
     const float kr = (float)(k_end - k_begin);
-            // The sums that did not pass, in fp64 straight from memory; of long ranges by several wavefronts, whose parts are added in
-            // their order.
-            const uint32_t share = total >= NW || kr < 2048.0f ? 1 : kr < 4096.0f ? 2 : kr < 8192.0f || NW == 4 ? 4 : 8, part_no = wave % share;
-                            #pragma unroll 1
-            for (uint32_t t = wave / share; t < total; t += NW / share) {
-                const uint32_t at = __builtin_amdgcn_readfirstlane(list[t]);
-                const uint64_t row = m0 + (at >> 16), col = n0 + (at & 0xFFFFu);
-                const gfloat pa = (gfloat)(AKN ? a.A + row : a.A + row * a.lda), pb = (gfloat)(BKN ? a.B + col : a.B + col * a.ldb);
-                double sum = 0.0;
-                auto dot = [&](auto full, uint64_t k0) {           // 256 k a turn, 4 a lane
-                    constexpr int U = decltype(full)::value ? 4 : 1;
-                    f32x4 ya[U], yb[U];
-    #pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        const uint64_t k = k0 + 256 * u + 4 * lane;
-                        if constexpr (decltype(full)::value && !AKN) ya[u] = *(gvec)(pa + k);
-                        if constexpr (decltype(full)::value && !BKN) yb[u] = *(gvec)(pb + k);
-    #pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            const bool ok = decltype(full)::value || k + q < k_end;
-                            if constexpr (!decltype(full)::value || AKN) ya[u][q] = ok ? pa[AKN ? (k + q) * a.lda : k + q] : 0.0f;
-                            if constexpr (!decltype(full)::value || BKN) yb[u][q] = ok ? pb[BKN ? (k + q) * a.ldb : k + q] : 0.0f;
-                            if constexpr (WEIGHT) ya[u][q] *= ok ? a.weight[k + q] : 0.0f;
-                        }
-                    }
-    #pragma unroll
-                    for (int u = 0; u < U; ++u)
-    #pragma unroll
-                        for (int q = 0; q < 4; ++q) sum = __builtin_fma((double)ya[u][q], (double)yb[u][q], sum);
-                };
-                uint64_t k0 = k_begin + 1024 * part_no;
-    #pragma unroll 1
-                for (; k0 + 1024 <= k_end; k0 += 1024 * share) dot(std::true_type{}, k0);
-                const uint64_t k1 = k0 + 1024 < k_end ? k0 + 1024 : k_end;                // of at most one of them
-    #pragma unroll 1
-                for (; k0 < k1; k0 += 256) dot(std::false_type{}, k0);
-    #pragma unroll
-                for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
-                if (lane == 0) parts[t * share + part_no] = sum;
+    // of long ranges by several wavefronts, whose parts are added in their order
+    const uint32_t share = total >= NW || kr < 4096.0f ? 1 : kr < 8192.0f ? 2 : kr < 16384.0f || NW == 4 ? 4 : 8, part = wave % share;
+#pragma unroll 1
+    for (uint32_t t = wave / share; t < total; t += NW / share) {
+        const uint32_t at = __builtin_amdgcn_readfirstlane(list[t]);
+        const uint64_t row = m0 + (at >> 16), col = n0 + (at & 0xFFFFu);
+        const gfloat pa = (gfloat)(AKN ? a.A + row : a.A + row * a.lda), pb = (gfloat)(BKN ? a.B + col : a.B + col * a.ldb);
+        double sum = 0.0;
+        uint64_t k0 = k_begin + 2048 * part;
+        auto dot = [&](auto full, auto n) {                    // 256 n of k, 4 in a row for a lane, requested together
+            constexpr bool FULL = decltype(full)::value;
+            constexpr int U = decltype(n)::value;
+            f32x4 ya[U], yb[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint64_t k = k0 + 256 * u + 4 * lane;
+                if constexpr (FULL && !AKN) ya[u] = *(gvec)(pa + k);
+                if constexpr (FULL && !BKN) yb[u] = *(gvec)(pb + k);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const bool ok = FULL || k + q < k_end;
+                    if constexpr (!FULL || AKN) ya[u][q] = ok ? pa[AKN ? (k + q) * a.lda : k + q] : 0.0f;
+                    if constexpr (!FULL || BKN) yb[u][q] = ok ? pb[BKN ? (k + q) * a.ldb : k + q] : 0.0f;
+                    if constexpr (WEIGHT) ya[u][q] *= ok ? a.weight[k + q] : 0.0f;
+                }
             }
-                    __syncthreads();
-            for (uint32_t t = threadIdx.x; t < total; t += THREADS) {
-                double sum = parts[t * share];
-                for (uint32_t q = 1; q < share; ++q) sum += parts[t * share + q];
-                float* const c = a.C + (m0 + (list[t] >> 16)) * a.ldc + n0 + (list[t] & 0xFFFFu);
-                *c = a.accumulate ? *c + (float)sum : (float)sum;
-            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) sum = __builtin_fma((double)ya[u][q], (double)yb[u][q], sum);
+        };
+        const std::true_type full;
+        const std::false_type rest;
+#pragma unroll 1
+        for (; k0 + 2048 <= k_end; k0 += 2048 * share) dot(full, std::integral_constant<int, 8>{});
+        if (k0 < k_end) {                                      // uniform; of one part at most
+            if (k0 + 1024 <= k_end) { dot(full, std::integral_constant<int, 4>{}); k0 += 1024; }
+            if (k0 + 512 <= k_end) { dot(full, std::integral_constant<int, 2>{}); k0 += 512; }
+            dot(rest, std::integral_constant<int, 2>{});
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+        if (lane == 0) parts[t * share + part] = sum;
+    }
+    __syncthreads();
+    for (uint32_t t = threadIdx.x; t < total; t += THREADS) {
+        double sum = parts[t * share];
+        for (uint32_t q = 1; q < share; ++q) sum += parts[t * share + q];
+        float* const c = a.C + (m0 + (list[t] >> 16)) * a.ldc + n0 + (list[t] & 0xFFFFu);
+        *c = a.accumulate ? *c + (float)sum : (float)sum;
+    }
 }
 
 // One workgroup owns a TM x TN tile of C; its WR x WC wavefronts own RB x NB blocks of 16 x 16 each.  K is consumed in groups
@@ -245,7 +257,7 @@ __device__ __forceinline__ uint32_t pair_tile(GemmF32Args a, lds_byte lds, const
     float* const gam = reinterpret_cast<float*>(few);                         //         then what that means for the slot
     int* const bias = reinterpret_cast<int*>(mx + 3 * SLOTS);                 // [SLOTS] sum of what they lose, away from zero, in 2^-33,
     float* const odd = reinterpret_cast<float*>(bias);                        //         then the share of gam against an ordinary row, < 0: odd row
-    uint32_t* const mt = mx + 4 * SLOTS;                                      // a vote, a count
+    uint32_t* const mt = mx + 4 * SLOTS;                                      // rows, columns of the tile; a count; the largest weight
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave / WC, wn = wave % WC;
     const auto [tm, tn, split] = gemm_f32_tile(a);
@@ -383,14 +395,14 @@ __device__ __forceinline__ uint32_t pair_tile(GemmF32Args a, lds_byte lds, const
     // What the scales may take from a sum.  The pieces are off by 2^-23 of a value, and of values below 2^-2 (scaled) by up to 2^-25.
     // Products of three bf16 pieces are within 2^-23 (6 ceil(k / 16) + 65) sum |a b|, those of two fp16 pieces, but for values below
     // 2^-2, within 2^-23 (3 ceil(k / 32) + 64) + 2^-21.  In between there is room for an error of 2^-25 / unit times sum |a b|.  Values
-    // from 4 unit on take half of it at most.  n smaller ones in a row a take at most 2^-25 sqrt(n) |b|_2, and likewise for b; the
-    // other half has room for that if the sum, which is at most sum |a b|, is not below 2 unit (gam_a |b|_2 + gam_b |a|_2), gam =
+    // from 8 unit on take a quarter of it at most.  n smaller ones in a row a take at most 2^-25 sqrt(n) |b|_2, and likewise for b;
+    // the rest has room for that if the sum, which is at most sum |a b|, is not below 4/3 unit (gam_a |b|_2 + gam_b |a|_2), gam =
     // sqrt(n).  That much is lost if all errors have one sign.  Otherwise they add up to 2^-25 sqrt(f / 3) |b|_2 in the root mean
     // square, f = n / k, whatever n is, and seven times that is gam = 4 sqrt(f).  f is twice what the sample says.  The mean of the
     // errors in the sample, as far as it is more than chance makes it (1.2 / sqrt(c) for c of them), is the part that has one sign,
-    // as equal values have; half where the sample has too few to tell.  gam is 2 at least, for up to four such values that the sample
-    // does not show.  |a|_2 is sqrt(2) times what the sample says, and a value of 2^12 that it does not show.
-    // A row is ordinary if 24 of 32 values in the sample are 4 and more.  Two of them meet at enough k for sum |a b| to be above that
+    // as equal values have; a quarter where the sample has too few to tell.  gam is 2 at least, for up to four such values that the sample
+    // does not show.  |a|_2 is sqrt(2) times what the sample says, and a value of 2^11 that it does not show.
+    // A row is ordinary if 24 of 32 values in the sample are 1 and more.  Two of them meet at enough k for sum |a b| to be above that
     // whatever the sum is (0.5 of their sums per tile of 1,000 x 50,001 x 4,096 would not pass, and cost 5 us at the end of a
     // launch).  What the n small values of an odd row meet in an ordinary one is rather n / k of it: min(1, 2 sqrt(f)), at least
     // 1/4, of gam counts.
@@ -432,85 +444,138 @@ __device__ __forceinline__ uint32_t pair_tile(GemmF32Args a, lds_byte lds, const
                 for (int i = 0; i < CB; ++i) yb[i] = load_part(km_b, pb[i], sb, cb[i] ? gb_cut : gb, i, g, lp);
             }
         };
-        // ---- scales, from a sample of the range
+        // ---- scales, from a sample of the range: the first group of 32 k and one to three more, those of a K-major operand from 32 or 96
+        // places.
         {
-            constexpr int QS = 4;                              // groups of the sample
+            constexpr int QS = 4;
             fetch(za, zb, zw, 0);
             for (int t = threadIdx.x; t < SLOTS; t += THREADS) mx[t] = few[t] = bias[t] = 0;
-            if (threadIdx.x < 2) mt[threadIdx.x] = 0;
-            f32x4 ya[QS][CA], yb[QS][CB];
-            const bool more = ng >= 64 && nf + 1 >= ng;        // uniform: three more groups of a long range, one of a short one
-            // The last one holds the diagonal, if the range does: that of a nearly diagonal matrix (an inverse) towers above the
-            // rest of its rows.
-            auto last_sample = [&](const Side& o, int i) {
-                const uint64_t d = (o.first + chunk_row(o, i)) / 32 - g0;             // wraps below the range
-                return d < nf ? (uint32_t)d : (QS - 1) * (ng / QS);
+            if (threadIdx.x < 4) mt[threadIdx.x] = 0;
+            auto place = [&](int at, float of) { return (uint32_t)(((float)at + 0.5f) * ((float)nf * of)); };       // below nf
+            const bool more = ng >= 64;                        // uniform: short ranges are sampled in two groups
+            // The last group of a row holds the diagonal, if the range does: that of a nearly diagonal matrix (an inverse) towers above
+            // the rest of the row.
+            auto diagonal = [&](const Side& o, int i) { return (o.first + chunk_row(o, i)) / 32 - g0; };              // wraps below the range
+            auto look = [&](auto km, const Side& o, gfloat p, uint32_t gofs, int t, int i) {
+                uint32_t g;
+                if constexpr (decltype(km)::value) {
+                    g = place(((t - 1) * 4 + i) * 8 + first_k(km, o, ln) / 4, more ? 1.0f / 96.0f : 1.0f / 32.0f);
+                    if (nf == 0 || (t != 1 && !more)) return f32x4{0.0f, 0.0f, 0.0f, 0.0f};                           // uniform
+                } else {
+                    const bool d = t == QS - 1 && diagonal(o, i) < nf;
+                    g = d ? (uint32_t)diagonal(o, i) : place(t - 1, more ? 1.0f / 3.0f : 1.0f);
+                    if (nf == 0 || (t != 1 && !more && !d)) return f32x4{0.0f, 0.0f, 0.0f, 0.0f};                     // uniform
+                }
+                return f32x4(*(gvec)((gbyte)p + gofs + (uint64_t)g * (4 * o.step)));
             };
+            f32x4 ya[QS][CA], yb[QS][CB], yw;                  // weights of the second part of the sample
 #pragma unroll
             for (int t = 1; t < QS; ++t) {
 #pragma unroll
-                for (int i = 0; i < CA; ++i) ya[t][i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+                for (int i = 0; i < CA; ++i) ya[t][i] = look(km_a, sa, pa[i], ca[i] ? ga_cut : ga, t, i);
 #pragma unroll
-                for (int i = 0; i < CB; ++i) yb[t][i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+                for (int i = 0; i < CB; ++i) yb[t][i] = look(km_b, sb, pb[i], cb[i] ? gb_cut : gb, t, i);
             }
-#pragma unroll
-            for (int t = 1; t < QS; ++t)
-                if (more || (t == QS - 1 && nf + 1 >= ng)) {
-#pragma unroll
-                    for (int i = 0; i < CA; ++i) {
-                        const uint32_t at = t < QS - 1 ? t * (ng / QS) : last_sample(sa, i);
-                        ya[t][i] = load_a(i, at);
-                        weigh(ya[t][i], weight_at(at));
-                    }
-#pragma unroll
-                    for (int i = 0; i < CB; ++i) yb[t][i] = load_b(i, t < QS - 1 ? t * (ng / QS) : last_sample(sb, i));
-                }
+            // Weights are at most one, and in a trained mask a few are one and the others next to nothing, which a sample would miss:
+            // rows are scaled by their own largest value and the largest weight of the range.
+            float wm = 0.0f;
+            if constexpr (WEIGHT) {
+                yw = *(gvec)((gfloat)a.weight + g0 * 32 + (uint64_t)place(0, more ? 1.0f / 3.0f : 1.0f) * 32 + 4 * (ln & 7));
+                for (uint64_t j = 4 * threadIdx.x; j < (uint64_t)ng * 32; j += 4 * THREADS) wm = __builtin_fmaxf(wm, largest(f32x4(*(gvec)((gfloat)a.weight + g0 * 32 + j))));
+            }
             fetch(xa, xb, xw, 1);
 #pragma unroll
-            for (int i = 0; i < CA; ++i) { ya[0][i] = za[i]; weigh(ya[0][i], zw); }
+            for (int i = 0; i < CA; ++i) ya[0][i] = za[i];
 #pragma unroll
             for (int i = 0; i < CB; ++i) yb[0][i] = zb[i];
-            // The 8 lanes that hold a row agree on its largest value; a column is spread over wavefronts.
-            auto post = [&](auto km, const Side& o, const auto& y, int n) {
+            // Columns past the edge are loaded from the last ones again, which count once.
+            auto counts = [&](auto km, const Side& o, int i) { return !decltype(km)::value || column_at(o, ln) + i >= column(o, ln); };
+            // The 8 lanes that hold a row agree on what is in it; a column is spread over wavefronts.
+            auto top = [](float x, float y) { return __builtin_fmaxf(x, y); };
+            auto add = [](auto x, auto y) { return x + y; };
+            auto post = [&](auto km, const Side& o, const auto& y, const gfloat* p, const bool* c, uint32_t gofs, uint32_t gofs_cut, auto n) {
+                constexpr int N = decltype(n)::value;
+                float m[N];
+                bool uneven = false;
 #pragma unroll
-                for (int i = 0; i < n; ++i) {
-                    float m = 0.0f;
+                for (int i = 0; i < N; ++i) {
+                    uint32_t quads = 0;                        // that are not zero
+                    float l[QS];
 #pragma unroll
-                    for (int t = 0; t < QS; ++t) m = __builtin_fmaxf(m, largest(values(km, y[t], i)));
-                    if constexpr (decltype(km)::value) {
-                        atomicMax(&mx[slot_of(km, o, ln, i)], __float_as_uint(m));
-                    } else {
-                        m = __builtin_fmaxf(m, swap_lanes<0xB1>(m));                  // quad_perm 1 0 3 2
-                        m = __builtin_fmaxf(m, swap_lanes<0x4E>(m));                  // quad_perm 2 3 0 1
-                        m = __builtin_fmaxf(m, swap_lanes<0x141>(m));                 // row_half_mirror
-                        mx[slot_of(km, o, ln, i)] = __float_as_uint(m);
+                    for (int t = 0; t < QS; ++t) {
+                        l[t] = largest(values(km, y[t], i));
+                        quads += l[t] != 0.0f;
+                        if constexpr (!decltype(km)::value) l[t] = over_8_lanes(l[t], top);
                     }
+                    m[i] = top(top(l[0], l[1]), l[2]);
+                    uneven |= __builtin_fminf(__builtin_fminf(l[0], l[1]), more ? l[2] : l[1]) * 64.0f <= m[i];
+                    m[i] = top(m[i], l[3]);
+                    if constexpr (decltype(km)::value) {
+                        if (quads != 0 && counts(km, o, i)) atomicAdd(&few[slot_of(km, o, ln, i)], quads);
+                    } else {
+                        few[slot_of(km, o, ln, i)] = over_8_lanes(quads, add);
+                    }
+                }
+                if constexpr (!decltype(km)::value) {
+                    // Rows whose groups are of different sizes or zero (half of the neurons dead) are looked at in 24 more places, one
+                    // per lane.  For all rows that would be eight times the lines (64 x 65,536 x 2,048: 140 -> 156 us).
+                    if (nf != 0 && __any(uneven)) {            // uniform
+#pragma unroll 1
+                        for (int t = 0; t < 3; ++t) {
+                            const uint64_t g = place(t * 8 + (ln & 7), 1.0f / 24.0f);
+                            f32x4 z[N];
+#pragma unroll
+                            for (int i = 0; i < N; ++i) z[i] = *(gvec)((gbyte)p[i] + (c[i] ? gofs_cut : gofs) + g * (4 * o.step));
+#pragma unroll
+                            for (int i = 0; i < N; ++i) m[i] = __builtin_fmaxf(m[i], largest(z[i]));
+                        }
+#pragma unroll
+                        for (int i = 0; i < N; ++i) m[i] = over_8_lanes(m[i], top);
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < N; ++i) {
+                    if constexpr (decltype(km)::value) atomicMax(&mx[slot_of(km, o, ln, i)], __float_as_uint(m[i]));
+                    else mx[slot_of(km, o, ln, i)] = __float_as_uint(m[i]);
                 }
             };
             __syncthreads();
-            post(km_a, sa, ya, CA);
-            post(km_b, sb, yb, CB);
+            post(km_a, sa, ya, pa, ca, ga, ga_cut, std::integral_constant<int, CA>{});
+            post(km_b, sb, yb, pb, cb, gb, gb_cut, std::integral_constant<int, CB>{});
+            if (WEIGHT) atomicMax(&mt[3], __float_as_uint(wm));
             __syncthreads();
             auto inside = [&](auto km, const Side& o, int t) { // a slot in front of the edge
                 const int s = t - o.slot0;
                 return o.first + (decltype(km)::value ? (s & ~63) + 4 * (s & 15) + ((s >> 4) & 3) : s) < o.rows;
             };
-            bool zero = false;
+            // Slots without a value other than zero get the largest scale: a value that the sample does not show is too large for it,
+            // or one of very few bits.  Where more than an eighth of the others have values in 1 to 5 of 32 quads of the sample (scattered
+            // ones, not runs), too many samples are empty by chance, and sums of nothing (which do not pass) are frequent.
             for (int t = threadIdx.x; t < SLOTS; t += THREADS) {
-                const uint32_t u = mx[t];
-                zero |= u == 0 && (t < TM ? inside(km_a, sa, t) : inside(km_b, sb, t));
-                ex[t] = u ? clamp_exponent(kSampleTop - lead_exponent(u)) : 0;
+                const bool side = t >= TM;                     // uniform
+                uint32_t u = mx[t];
+                if (WEIGHT && !side) u = __float_as_uint(__uint_as_float(u) * __uint_as_float(mt[3]));
+                ex[t] = u ? clamp_exponent(kSampleTop - lead_exponent(u)) : 127;
+                const bool live = u != 0 && (side ? inside(km_b, sb, t) : inside(km_a, sa, t));
+                const uint32_t n = __builtin_popcountll(__ballot(live)), rare = __builtin_popcountll(__ballot(live && few[t] - 1 < 5));
+                if ((t & 63) == 0) atomicAdd(&mt[side ? 2 : 0], n << 16 | rare);
                 mx[t] = 0;
+                few[t] = live ? 0 : ~0u;
             }
-            if (zero) mt[0] = 1;
             __syncthreads();
-            if (mt[0] != 0) return kExact;                     // uniform: nothing to scale a slot by
-            // What one of the groups, 32 values of a slot, says about the others
+            const uint32_t va = mt[0], vb = mt[2];
+            if (nf != 0 && ((va & 0xFFFFu) * 8 > va >> 16 || (vb & 0xFFFFu) * 8 > vb >> 16)) return kExact;          // uniform
+            if constexpr (WEIGHT) {
+#pragma unroll
+                for (int i = 0; i < CA; ++i) weigh(ya[1][i], yw);
+            }
+            // What the second part of the sample, 32 values of a slot, says about the range
             auto count = [&](auto km, const Side& o, const auto& y, int n) {
-                const uint32_t top = (__float_as_uint(4.0f * unit) << 1) - 1;
+                const uint32_t small = (__float_as_uint(8.0f * unit) << 1) - 1;
 #pragma unroll
                 for (int i = 0; i < n; ++i) {
                     const int slot = slot_of(km, o, ln, i);
+                    const bool use = counts(km, o, i) && few[slot] != ~0u;
                     const f32x4 v = values(km, y, i) * __builtin_ldexpf(1.0f, ex[slot]);
                     float q = 0.0f;
                     uint32_t least = ~0u, c = 0;
@@ -519,45 +584,53 @@ __device__ __forceinline__ uint32_t pair_tile(GemmF32Args a, lds_byte lds, const
                         const uint32_t u = (__float_as_uint(v[e]) << 1) - 1;          // order of |v|, zero above all
                         q = __builtin_fmaf(v[e], v[e], q);
                         least = u < least ? u : least;
-                        c += __builtin_fabsf(v[e]) >= 4.0f;
+                        c += __builtin_fabsf(v[e]) >= 1.0f;
                     }
-                    atomicAdd(&mx[slot], (uint32_t)q);         // at most 2^25 in all
                     c <<= 16;
-                    if (__any(least < top)) {                  // uniform
+                    if (least < small) {
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) c += (__float_as_uint(v[e]) << 1) - 1 < top;
+                        for (int e = 0; e < 4; ++e) c += (__float_as_uint(v[e]) << 1) - 1 < small;
                     }
-                    atomicAdd(&few[slot], c);
+                    if constexpr (decltype(km)::value) {
+                        if (use) {
+                            atomicAdd(&mx[slot], (uint32_t)q); // at most 2^25 in all
+                            atomicAdd(&few[slot], c);
+                        }
+                    } else {
+                        q = over_8_lanes(q, add);
+                        c = over_8_lanes(c, add);
+                        if (use) { mx[slot] = (uint32_t)q; few[slot] = c; }
+                    }
                 }
             };
-            count(km_a, sa, ya[QS - 1], CA);
-            count(km_b, sb, yb[QS - 1], CB);
+            count(km_a, sa, ya[1], CA);
+            count(km_b, sb, yb[1], CB);
             __syncthreads();
             auto lose = [&](auto km, const Side& o, const auto& y, int n) {
 #pragma unroll
                 for (int i = 0; i < n; ++i) {
                     const int slot = slot_of(km, o, ln, i);
-                    if (!__any((few[slot] & 0xFFFFu) >= 4)) continue;                 // uniform
+                    if (!counts(km, o, i) || few[slot] == ~0u || (few[slot] & 0xFFFFu) < 4) continue;
                     const f32x4 v = values(km, y, i) * __builtin_ldexpf(1.0f, ex[slot]);
                     int r = 0;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         const float x = __builtin_fabsf(v[e]), h = (float)(_Float16)x;
-                        if (x < 4.0f * unit) r += (int)(((x - h) - (float)(_Float16)(x - h)) * 8589934592.0f);
+                        if (x < 8.0f * unit) r += (int)(((x - h) - (float)(_Float16)(x - h)) * 8589934592.0f);
                     }
                     if (r) atomicAdd(&bias[slot], r);
                 }
             };
-            lose(km_a, sa, ya[QS - 1], CA);
-            lose(km_b, sb, yb[QS - 1], CB);
+            lose(km_a, sa, ya[1], CA);
+            lose(km_b, sb, yb[1], CB);
             __syncthreads();
             for (int t = threadIdx.x; t < SLOTS; t += THREADS) {
-                const bool in = t < TM ? inside(km_a, sa, t) : inside(km_b, sb, t);
+                const bool in = few[t] != ~0u;
                 const float c = (float)(few[t] & 0xFFFFu), f = (2.0f * c + (c > 0.0f)) * (1.0f / 32.0f);
-                const float lean = c < 4.0f ? 0.5f : __builtin_fabsf((float)bias[t]) / (256.0f * c) - 1.2f * __builtin_amdgcn_rsqf(c);
+                const float lean = c < 4.0f ? 0.25f : __builtin_fabsf((float)bias[t]) / (256.0f * c) - 1.2f * __builtin_amdgcn_rsqf(c);
                 const float share = __builtin_fmaxf(0.25f, __builtin_fminf(1.0f, 2.0f * __builtin_sqrtf(f)));
                 odd[t] = few[t] >> 16 < 24 ? -share : share;
-                nrm[t] = in ? __builtin_sqrtf((float)mx[t] * (kr / 16.0f) + 16777216.0f) : 0.0f;
+                nrm[t] = in ? __builtin_sqrtf((float)mx[t] * (kr / 16.0f) + 4194304.0f) : 0.0f;
                 gam[t] = in ? __builtin_fmaxf(2.0f, __builtin_sqrtf(f) * __builtin_fmaxf(4.0f, lean * __builtin_sqrtf(kr))) : 0.0f;
             }
         }
@@ -723,7 +796,7 @@ __device__ __forceinline__ uint32_t pair_tile(GemmF32Args a, lds_byte lds, const
     if constexpr (GRAD) {
         auto r = [&](int i, int j, int e) { return __builtin_ldexpf(acc[i][j][e], -(ea[i * 16 + e] + eb[j * 16])); };
         auto lost = [&](int i, int e) {
-            const float x = __builtin_ldexpf(2.0f * unit, -ea[i * 16 + e]);
+            const float x = __builtin_ldexpf(4.0f / 3.0f * unit, -ea[i * 16 + e]);
             return f32x2{x * na[i * 16 + e], x * ga[i * 16 + e]};
         };
         auto col = [&](int j) { return f32x2{__builtin_ldexpf(gb[j * 16], -eb[j * 16]), __builtin_ldexpf(nb[j * 16], -eb[j * 16])}; };
@@ -740,7 +813,7 @@ __device__ __forceinline__ uint32_t pair_tile(GemmF32Args a, lds_byte lds, const
             float worst = 0.0f, sum = 0.0f;                    // cheaply first: 128 sums a lane
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const float x = 2.0f * unit * na[i * 16 + e], g = 2.0f * unit * ga[i * 16 + e];
+                const float x = 4.0f / 3.0f * unit * na[i * 16 + e], g = 4.0f / 3.0f * unit * ga[i * 16 + e];
 #pragma unroll
                 for (int j = 0; j < NB; ++j) {
                     worst = __builtin_fmaxf(worst, __builtin_fmaf(x, gb[j * 16], __builtin_fmaf(g, nb[j * 16], -__builtin_fabsf(acc[i][j][e]))));
@@ -750,7 +823,7 @@ __device__ __forceinline__ uint32_t pair_tile(GemmF32Args a, lds_byte lds, const
             if (!__any(!(worst <= 0.0f && sum == 0.0f))) continue;                    // uniform
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const float x = 2.0f * unit * na[i * 16 + e], g = 2.0f * unit * ga[i * 16 + e];
+                const float x = 4.0f / 3.0f * unit * na[i * 16 + e], g = 4.0f / 3.0f * unit * ga[i * 16 + e];
                 const bool in = interior || a_row(i, 4 * lq + e) < a.M;
 #pragma unroll
                 for (int j = 0; j < NB; ++j) {
@@ -764,9 +837,9 @@ __device__ __forceinline__ uint32_t pair_tile(GemmF32Args a, lds_byte lds, const
         }
 #pragma unroll
         for (int i = 0; i < (RB + 1) / 2; ++i) n += __builtin_popcount(todo[i]);
-        // As many of them as can be summed one by one in half the time that the tile takes with three bf16 pieces (1,000 x 50,001 x
-        // 4,096: 2 us each for a wavefront; a column of a K-major operand is a line of 128 bytes per value, 50 us for 9,362 of them).
-        const uint32_t limit = AKN ? 2 * NW : BKN ? 4 * NW : NW * (kr < 2048.0f ? (uint32_t)kr / 16 : 128);
+        // As many of them as can be summed one by one in less time than the tile takes with three bf16 pieces (1,000 + 100 rows of
+        // 1,863,690 in 64 ranges: 13 us each, 1.9 ms).  A column of a K-major operand is a line of 128 bytes per value (50 us for 9,362 of them).
+        const uint32_t limit = AKN ? 2 * NW : BKN ? 4 * NW : kr < 4.0f * SLOTS / NW ? NW * (uint32_t)kr / 16 : SLOTS / 4;
         if (n != 0) {
             uint32_t at = atomicAdd(&mt[1], n);
 #pragma unroll
