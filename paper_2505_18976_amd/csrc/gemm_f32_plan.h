@@ -8,7 +8,7 @@ namespace grass {
 constexpr uint64_t kGemmCUs = 256;       // MI355X
 inline uint64_t gemm_div(uint64_t a, uint64_t b) { return (a + b - 1) / b; }
 
-// 256 x 256, 128 x 128, 64 x 512, 128 x 256 (only with two fp16 pieces, A row-major)
+// 256 x 256, 128 x 128, 64 x 512 (only with three bf16 pieces), 128 x 256 (only with two fp16 pieces, A row-major)
 enum : int { kTile256 = 0, kTile128 = 1, kTile64 = 2, kTile128x256 = 3 };
 struct GemmPlan {
     int tile;
@@ -41,7 +41,7 @@ constexpr uint64_t kPairMinK = 256;      // k per workgroup from which on two fp
 // the time of the best plan with three bf16 pieces in the geometric mean, and 1.06 at most.
 struct TileCost { uint64_t tm, tn, per_cu; double full, part; uint64_t part_wgs; };
 inline const TileCost kTiles[2][4] = {{{256, 256, 1, 2.1, 1.95, 192}, {128, 128, 2, 1.31, 1.05, 256}, {64, 512, 1, 2.15, 1.5, 128}},
-                                      {{256, 256, 1, 1.32, 1.1, 192}, {128, 128, 2, 0.87, 0.5, 256}, {64, 512, 1, 1.75, 1.4, 128}, {128, 256, 1, 0.84, 0.62, 128}}};
+                                      {{256, 256, 1, 1.32, 1.1, 192}, {128, 128, 2, 0.87, 0.5, 256}, {}, {128, 256, 1, 0.84, 0.62, 128}}};
 constexpr double kPairStart = 8.0;       // us more than a launch on three bf16 pieces
 
 inline GemmPlan gemm_f32_plan(bool a_kn, bool b_kn, uint64_t M, uint64_t N, uint64_t K, uint64_t ld_max, bool lower_only,
@@ -54,7 +54,7 @@ inline GemmPlan gemm_f32_plan(bool a_kn, bool b_kn, uint64_t M, uint64_t N, uint
             const TileCost& T = kTiles[pair][t];
             if (wide && t != kTile128) continue;
             if (t == kTile128x256 && a_kn) continue;
-            if (t == kTile64 && (a_kn || b_kn || lower_only || M > 64)) continue;
+            if (t == kTile64 && (pair || a_kn || b_kn || lower_only || M > 64)) continue;
             const uint64_t side = gemm_div(M, T.tm);
             const uint64_t n = lower_only ? side * (side + 1) / 2 : side * gemm_div(N, T.tn);
             for (uint32_t s = 1; s <= max_splits && (s == 1 || groups / s >= 2); ++s) {
@@ -88,7 +88,7 @@ inline GemmCut gemm_f32_cut(uint64_t M, uint64_t N, uint64_t K, uint64_t ld_max,
     const bool pair = K >= kPairMinK;
     for (int t = 0; t < (pair ? 4 : 3); ++t) {
         const TileCost& T = kTiles[pair][t];
-        if (t == kTile64 && M > 64) continue;
+        if (t == kTile64 && (pair || M > 64)) continue;
         const uint64_t side = gemm_div(M, T.tm), cap = T.per_cu * kGemmCUs;
         const uint64_t rounds = side * (N / T.tn) / cap;
         for (uint64_t q = rounds; q > 0 && q + 2 > rounds; --q) {                // all full rounds, or one less

@@ -895,9 +895,6 @@ __device__ __attribute__((noinline)) void exact_tile(GemmF32Args a, lds_byte lds
     if constexpr (RB == 8) {
         static_assert(split_lds<4, 2, 2, 4>() <= lds_bytes && TM == 256 && TN == 256, "256 x 256");
         split_tile<4, 2, 2, 4, AKN, BKN, false, WEIGHT>(a, smem, threadIdx.x, m0, n0, g0, ng);
-    } else if constexpr (WC == 8) {
-        static_assert(split_lds<2, 2, 1, 8>() <= lds_bytes && TM == 64 && TN == 512, "64 x 512");
-        split_tile<2, 2, 1, 8, AKN, BKN, false, WEIGHT>(a, smem, threadIdx.x, m0, n0, g0, ng);
     } else {                                                   // halves of 128 x 128, 4 wavefronts each; TM == 64 has no rows 64..127
         constexpr uint32_t half = split_lds<2, 2, 2, 2>();
         static_assert(half * (TN / 128) <= lds_bytes && TM <= 128 && TN / 128 * 4 == WR * WC, "128 x 128");
@@ -987,8 +984,7 @@ hipError_t gemm_f32_pair(bool a_kn, bool b_kn, int tile, const GemmF32Args& a, h
             if (b_kn) return launch_pair<4, 4, 2, 4, false, true>(a, st);
             return launch_pair<4, 4, 2, 4, false, false>(a, st);
         case kTile64:
-            if (b_kn) return hipErrorInvalidValue;
-            return launch_pair<4, 4, 1, 8, false, false>(a, st);
+            return hipErrorInvalidValue;
         default:
             if (a_kn) return launch_pair<4, 4, 2, 2, true, true>(a, st);
             if (b_kn) return launch_pair<4, 4, 2, 2, false, true>(a, st);
