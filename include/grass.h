@@ -256,9 +256,15 @@ grass_status logra_linear(const void* x, const void* gout,
  * Sec. 2.1, attribute stage: scores[m, i] = <test_m, train_i> for all pairs of
  * compressed gradients (no preconditioner).
  * train: N x K fp32 (ld_train >= K), test: M x K fp32, scores: M x N fp32.
- * compute_mode 0: fp32 products and accumulation (each operand exactly split
- * into three bf16 pieces, six products of pieces on the bf16 matrix cores; the
- * three left out are below 2^-24 of a product together).  1: inputs rounded to
+ * compute_mode 0: fp32 products and accumulation, within
+ * 2^-23 (6 ceil(K / 16) + 65) sum_k |test_mk train_ik| of the exact score: each
+ * operand exactly split into three bf16 pieces, six products of pieces (the three
+ * left out are below 2^-24 of a product together); or, where a workgroup
+ * contracts 256 k and more, scaled per row and split into two fp16 pieces that
+ * hold 23 of its 24 bits, three products of pieces (the one left out is below
+ * 2^-22 of a product).  Scores that the scales would take more from than the
+ * bound has room for, as a sample of their rows and their own size tell, are
+ * computed again in fp64 or with three bf16 pieces.  1: inputs rounded to
  * bf16 (nearest-even), bf16 MFMA with fp32 accumulation.
  * Workspace (optional, from grass_score_workspace_bytes): with it, mode 1
  * rounds both operands once into the workspace and runs the direct-to-LDS bf16
@@ -327,7 +333,8 @@ grass_status grass_gauss_project(const float* g, uint64_t n, uint64_t p, uint64_
  * 2 * kp^2 * 8 bytes with kp = k rounded up to 64.
  *
  * grass_ifvp: out (N x k fp32, ldo >= k), row i = W g_i for the rows g_i of G
- * (N x k).  W must be symmetric (as grass_fim_inverse writes it).  fp32 products.
+ * (N x k).  W must be symmetric (as grass_fim_inverse writes it).  fp32 products
+ * as in grass_score mode 0.
  * Scores with the preconditioner are then grass_score(out_train, test) =
  * <g_test, (F + lambda I)^{-1} g_i>.
  * Errors: GRASS_EINVAL for null pointers, k = 0, N = 0 in grass_fim, short

@@ -187,7 +187,8 @@ static SmLayout sm_layout(uint64_t n, uint64_t m, uint64_t p, uint64_t p2 = 0) {
     L.n_pad = (n + 15) / 16 * 16;
     // columns of R at a time: a 128 MiB block stays in the last-level cache for the kernel that reads it next; at least
     // 4,096 columns; whole rounds of the backward product's tiles where a block holds more than one (100 x 1,000 x 335,488
-    // columns are 5.1 rounds and took 570 us, 327,680 are 5 and take 495)
+    // columns are 5.1 rounds and took 570 us, 327,680 are 5 and take 495).  Up to 128 rows need the block only for rows too far
+    // apart for 32-bit offsets, slices of a longer gradient for instance, which the sizes here do not tell.
     uint64_t pc = (1ull << 25) / m;
     if (pc < 4096) pc = 4096;
     pc = pc / 64 * 64;
