@@ -16,7 +16,8 @@
 // to 2^9..2^10: values up to 2^6 times the sample's largest fit, smaller ones lose nothing above 2^-11 of it and are off by 2^-34
 // of it below.  What that takes from a sum is judged by the sample and by the size of the sum alone, once the sums are there.
 // The few that do not pass are summed again one by one in fp64; where they are more, the tile is computed again with three
-// bf16 pieces.  Tiles of scattered values go there at once.
+// bf16 pieces.  Tiles of scattered values go there at once.  The diagonal of a matrix whose rows are its columns (an inverse) is
+// known to be large: it is scaled to 2^14..2^15 at most and the rest of the row as if it was not there.
 //
 // Bound: the power that the matrix cores and the data on the way to them draw.  1,024 x 65,536 x 4,096 takes 1.45 ms = 1,140
 // TFLOP/s of fp16 products at 1.5 GHz, matrix cores 74 % busy; without loads and splitting it would be 1.15 ms, a loop of
@@ -62,15 +63,16 @@ __device__ __forceinline__ T over_8_lanes(T x, F f) {
 }
 
 constexpr uint32_t kDone = 0, kExact = ~0u;
-constexpr int kSampleTop = 9;                      // exponent to which the largest value of a sample is scaled
+constexpr int kSampleTop = 9, kDiagonalTop = 14;   // exponents to which the largest value of a sample is scaled, a diagonal at most
 
 typedef unsigned char __attribute__((address_space(3)))* lds_byte;
 
 // The gradient of the columns of a tile from its R = `get(i, j, e)` (element e of block (i, j)), all rows of which it holds: a
 // lane multiplies its 4 columns with Gt and sums its rows in fp64, lanes and wavefronts are added in a fixed order.
-// CHECK: an R below <lost(i, e), col(j)> may have lost bits to the scales.  Where the sum over the rows of |Gt R| is not above that
-// of |Gt| times this, false is returned and nothing stored.
-template <int RB, int NB, int WR, int WC, bool CHECK, class Get, class Lost, class Col>
+// CHECK: where the sum over the rows of |Gt R| is not finite or, for kSize, not above that of |Gt| <lost(i, e), col(j)>, below which
+// the scales may have taken bits from an R, false is returned and nothing stored.
+enum : int { kNothing = 0, kFinite = 1, kSize = 2 };
+template <int RB, int NB, int WR, int WC, int CHECK, class Get, class Lost, class Col>
 __device__ __forceinline__ bool grad_tail(const GemmF32Args& a, const GradTail& t, double* part, uint64_t n0, Get get, Lost lost, Col col) {
     constexpr int TN = 16 * NB * WC;
     const int lane = threadIdx.x & 63, lq = lane >> 4, lc = lane & 15, wave = threadIdx.x >> 6, wm = wave / WC, wn = wave % WC;
@@ -94,14 +96,14 @@ __device__ __forceinline__ bool grad_tail(const GemmF32Args& a, const GradTail& 
                     if (c0 + j < a.N) x[j] = gt[j];
             }
             f32x2 l;
-            if constexpr (CHECK) l = lost(i, e);
+            if constexpr (CHECK == kSize) l = lost(i, e);
 #pragma unroll
             for (int j = 0; j < 4; ++j)
                 if (all || c0 + j < a.N) {
                     const float r = get(i, j, e);
                     s[j] += (double)x[j] * (double)r;
-                    if constexpr (CHECK) {
-                        size[j] = __builtin_fmaf(__builtin_fabsf(x[j]), __builtin_fabsf(r), size[j]);
+                    if constexpr (CHECK != kNothing) size[j] = __builtin_fmaf(__builtin_fabsf(x[j]), __builtin_fabsf(r), size[j]);
+                    if constexpr (CHECK == kSize) {
                         lx[j] = __builtin_fmaf(__builtin_fabsf(x[j]), l[0], lx[j]);
                         ly[j] = __builtin_fmaf(__builtin_fabsf(x[j]), l[1], ly[j]);
                     }
@@ -113,24 +115,26 @@ __device__ __forceinline__ bool grad_tail(const GemmF32Args& a, const GradTail& 
     for (int j = 0; j < 4; ++j) {
         s[j] += __shfl_xor(s[j], 16);
         s[j] += __shfl_xor(s[j], 32);
-        if constexpr (CHECK) {
+        if constexpr (CHECK == kSize) {
             const f32x2 c = col(j);
             size[j] -= lx[j] * c[0] + ly[j] * c[1];
+        }
+        if constexpr (CHECK != kNothing) {
             size[j] += __shfl_xor(size[j], 16);
             size[j] += __shfl_xor(size[j], 32);
         }
     }
     __syncthreads();                                           // the memory of `part` is free
-    if (CHECK && threadIdx.x == 0) *vote = 0;
+    if (CHECK != kNothing && threadIdx.x == 0) *vote = 0;
     if (lq == 0) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             part[wm * TN + wn * NB * 16 + 4 * lc + j] = s[j];
-            if constexpr (CHECK) check[wm * TN + wn * NB * 16 + 4 * lc + j] = size[j];
+            if constexpr (CHECK != kNothing) check[wm * TN + wn * NB * 16 + 4 * lc + j] = size[j];
         }
     }
     __syncthreads();
-    if constexpr (CHECK) {
+    if constexpr (CHECK != kNothing) {
         for (int c = threadIdx.x; c < TN && n0 + c < a.N; c += 64 * WR * WC) {
             float sum = check[c];
 #pragma unroll
@@ -255,9 +259,10 @@ __device__ __forceinline__ uint32_t pair_tile(GemmF32Args a, lds_byte lds, const
     int* const ex = reinterpret_cast<int*>(mx + SLOTS);                       // [SLOTS] exponent of a slot's scale
     uint32_t* const few = mx + 2 * SLOTS;                                     // [SLOTS] values of the sample that the scale leaves few bits,
     float* const gam = reinterpret_cast<float*>(few);                         //         then what that means for the slot
-    int* const bias = reinterpret_cast<int*>(mx + 3 * SLOTS);                 // [SLOTS] sum of what they lose, away from zero, in 2^-33,
+    uint32_t* const mx2 = mx + 3 * SLOTS;                                     // [SLOTS] largest |x| but for the diagonal, then
+    int* const bias = reinterpret_cast<int*>(mx2);                            //         sum of what those values lose, away from zero, in 2^-33,
     float* const odd = reinterpret_cast<float*>(bias);                        //         then the share of gam against an ordinary row, < 0: odd row
-    uint32_t* const mt = mx + 4 * SLOTS;                                      // rows, columns of the tile; a count; the largest weight
+    uint32_t* const mt = mx + 4 * SLOTS;                                      // rows, list, columns of the tile; the largest weight; odd rows
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave / WC, wn = wave % WC;
     const auto [tm, tn, split] = gemm_f32_tile(a);
@@ -450,21 +455,28 @@ __device__ __forceinline__ uint32_t pair_tile(GemmF32Args a, lds_byte lds, const
             constexpr int QS = 4;
             fetch(za, zb, zw, 0);
             for (int t = threadIdx.x; t < SLOTS; t += THREADS) mx[t] = few[t] = bias[t] = 0;
-            if (threadIdx.x < 4) mt[threadIdx.x] = 0;
+            if (threadIdx.x < 5) mt[threadIdx.x] = 0;
             auto place = [&](int at, float of) { return (uint32_t)(((float)at + 0.5f) * ((float)nf * of)); };       // below nf
             const bool more = ng >= 64;                        // uniform: short ranges are sampled in two groups
             // The last group of a row holds the diagonal, if the range does: that of a nearly diagonal matrix (an inverse) towers above
-            // the rest of the row.
-            auto diagonal = [&](const Side& o, int i) { return (o.first + chunk_row(o, i)) / 32 - g0; };              // wraps below the range
+            // the rest of the row, which is scaled as if it was not there as far as fp16 reaches.
+            auto diagonal = [&](const Side& o, int i) {        // its group, ng outside of the range
+                const uint64_t d = (o.first + chunk_row(o, i)) / 32 - g0;             // wraps below the range
+                return nf != 0 && d < ng && !past(o, i) ? (uint32_t)d : ng;
+            };
+            const uint32_t group[QS] = {0, (uint32_t)__builtin_amdgcn_readfirstlane(place(0, more ? 1.0f / 3.0f : 1.0f)),
+                                        (uint32_t)__builtin_amdgcn_readfirstlane(place(1, 1.0f / 3.0f)),
+                                        (uint32_t)__builtin_amdgcn_readfirstlane(place(2, 1.0f / 3.0f))};             // of a row's parts
             auto look = [&](auto km, const Side& o, gfloat p, uint32_t gofs, int t, int i) {
                 uint32_t g;
                 if constexpr (decltype(km)::value) {
                     g = place(((t - 1) * 4 + i) * 8 + first_k(km, o, ln) / 4, more ? 1.0f / 96.0f : 1.0f / 32.0f);
                     if (nf == 0 || (t != 1 && !more)) return f32x4{0.0f, 0.0f, 0.0f, 0.0f};                           // uniform
                 } else {
-                    const bool d = t == QS - 1 && diagonal(o, i) < nf;
-                    g = d ? (uint32_t)diagonal(o, i) : place(t - 1, more ? 1.0f / 3.0f : 1.0f);
-                    if (nf == 0 || (t != 1 && !more && !d)) return f32x4{0.0f, 0.0f, 0.0f, 0.0f};                     // uniform
+                    const uint32_t d = t == QS - 1 ? diagonal(o, i) : ng;
+                    if (d < ng && d >= nf) return load_part(km, p, o, gofs, i, d, ln);                                // uniform
+                    g = d < nf ? d : group[t];
+                    if (nf == 0 || (t != 1 && !more && d >= nf)) return f32x4{0.0f, 0.0f, 0.0f, 0.0f};                // uniform
                 }
                 return f32x4(*(gvec)((gbyte)p + gofs + (uint64_t)g * (4 * o.step)));
             };
@@ -495,17 +507,30 @@ __device__ __forceinline__ uint32_t pair_tile(GemmF32Args a, lds_byte lds, const
             auto add = [](auto x, auto y) { return x + y; };
             auto post = [&](auto km, const Side& o, const auto& y, const gfloat* p, const bool* c, uint32_t gofs, uint32_t gofs_cut, auto n) {
                 constexpr int N = decltype(n)::value;
-                float m[N];
+                float m[N], diag[N];
                 bool uneven = false;
 #pragma unroll
                 for (int i = 0; i < N; ++i) {
                     uint32_t quads = 0;                        // that are not zero
                     float l[QS];
+                    diag[i] = 0.0f;
+                    const uint32_t d = decltype(km)::value ? ng : diagonal(o, i);
 #pragma unroll
-                    for (int t = 0; t < QS; ++t) {
-                        l[t] = largest(values(km, y[t], i));
-                        quads += l[t] != 0.0f;
-                        if constexpr (!decltype(km)::value) l[t] = over_8_lanes(l[t], top);
+                    for (int t = QS - 1; t >= 0; --t) {
+                        f32x4 v = values(km, y[t], i);
+                        quads += largest(v) != 0.0f;
+                        if (!decltype(km)::value && t == QS - 1 && d < ng) {          // uniform
+                            const int row = (int)((o.first + chunk_row(o, i)) & 31) + (ln >> 3);
+                            const bool mine = row >> 2 == (ln & 7);
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                if (mine && (row & 3) == e) { diag[i] = __builtin_fabsf(v[e]); v[e] = 0.0f; }
+                        }
+                        l[t] = largest(v);
+                        if constexpr (!decltype(km)::value) {
+                            l[t] = over_8_lanes(l[t], top);
+                            if (t < QS - 1 && d == group[t]) l[t] = l[QS - 1];        // the same group, without the diagonal
+                        }
                     }
                     m[i] = top(top(l[0], l[1]), l[2]);
                     uneven |= __builtin_fminf(__builtin_fminf(l[0], l[1]), more ? l[2] : l[1]) * 64.0f <= m[i];
@@ -535,8 +560,13 @@ __device__ __forceinline__ uint32_t pair_tile(GemmF32Args a, lds_byte lds, const
                 }
 #pragma unroll
                 for (int i = 0; i < N; ++i) {
-                    if constexpr (decltype(km)::value) atomicMax(&mx[slot_of(km, o, ln, i)], __float_as_uint(m[i]));
-                    else mx[slot_of(km, o, ln, i)] = __float_as_uint(m[i]);
+                    const int slot = slot_of(km, o, ln, i);
+                    if constexpr (decltype(km)::value) {
+                        atomicMax(&mx[slot], __float_as_uint(m[i]));
+                    } else {
+                        mx[slot] = __float_as_uint(top(m[i], over_8_lanes(diag[i], top)));
+                        mx2[slot] = __float_as_uint(m[i]);
+                    }
                 }
             };
             __syncthreads();
@@ -553,13 +583,20 @@ __device__ __forceinline__ uint32_t pair_tile(GemmF32Args a, lds_byte lds, const
             // ones, not runs), too many samples are empty by chance, and sums of nothing (which do not pass) are frequent.
             for (int t = threadIdx.x; t < SLOTS; t += THREADS) {
                 const bool side = t >= TM;                     // uniform
-                uint32_t u = mx[t];
-                if (WEIGHT && !side) u = __float_as_uint(__uint_as_float(u) * __uint_as_float(mt[3]));
-                ex[t] = u ? clamp_exponent(kSampleTop - lead_exponent(u)) : 127;
+                uint32_t u = mx[t], u2 = (side ? BKN : AKN) ? u : mx2[t];
+                if (WEIGHT && !side) {
+                    u = __float_as_uint(__uint_as_float(u) * __uint_as_float(mt[3]));
+                    u2 = __float_as_uint(__uint_as_float(u2) * __uint_as_float(mt[3]));
+                }
+                int e = 127;
+                if (u != 0) e = kSampleTop - lead_exponent(u2 != 0 ? u2 : u);
+                if (u2 != 0 && e > kDiagonalTop - lead_exponent(u)) e = kDiagonalTop - lead_exponent(u);
+                ex[t] = clamp_exponent(e);
                 const bool live = u != 0 && (side ? inside(km_b, sb, t) : inside(km_a, sa, t));
                 const uint32_t n = __builtin_popcountll(__ballot(live)), rare = __builtin_popcountll(__ballot(live && few[t] - 1 < 5));
                 if ((t & 63) == 0) atomicAdd(&mt[side ? 2 : 0], n << 16 | rare);
                 mx[t] = 0;
+                bias[t] = 0;
                 few[t] = live ? 0 : ~0u;
             }
             __syncthreads();
@@ -630,6 +667,7 @@ __device__ __forceinline__ uint32_t pair_tile(GemmF32Args a, lds_byte lds, const
                 const float lean = c < 4.0f ? 0.25f : __builtin_fabsf((float)bias[t]) / (256.0f * c) - 1.2f * __builtin_amdgcn_rsqf(c);
                 const float share = __builtin_fmaxf(0.25f, __builtin_fminf(1.0f, 2.0f * __builtin_sqrtf(f)));
                 odd[t] = few[t] >> 16 < 24 ? -share : share;
+                if (in && odd[t] < 0.0f) mt[4] = 1;
                 nrm[t] = in ? __builtin_sqrtf((float)mx[t] * (kr / 16.0f) + 4194304.0f) : 0.0f;
                 gam[t] = in ? __builtin_fmaxf(2.0f, __builtin_sqrtf(f) * __builtin_fmaxf(4.0f, lean * __builtin_sqrtf(kr))) : 0.0f;
             }
@@ -793,6 +831,7 @@ __device__ __forceinline__ uint32_t pair_tile(GemmF32Args a, lds_byte lds, const
     const float* const gb = gam + TM + wn * NB * 16 + lc;
     const float* const oa = odd + wm * RB * 16 + 4 * lq;
     const float* const ob = odd + TM + wn * NB * 16 + lc;
+    const bool any_odd = mt[4] != 0;                           // uniform
     if constexpr (GRAD) {
         auto r = [&](int i, int j, int e) { return __builtin_ldexpf(acc[i][j][e], -(ea[i * 16 + e] + eb[j * 16])); };
         auto lost = [&](int i, int e) {
@@ -800,7 +839,9 @@ __device__ __forceinline__ uint32_t pair_tile(GemmF32Args a, lds_byte lds, const
             return f32x2{x * na[i * 16 + e], x * ga[i * 16 + e]};
         };
         auto col = [&](int j) { return f32x2{__builtin_ldexpf(gb[j * 16], -eb[j * 16]), __builtin_ldexpf(nb[j * 16], -eb[j * 16])}; };
-        return grad_tail<RB, NB, WR, WC, true>(a, *tail, reinterpret_cast<double*>(smem), n0, r, lost, col) ? kDone : kExact;
+        double* const part = reinterpret_cast<double*>(smem);
+        if (any_odd) return grad_tail<RB, NB, WR, WC, kSize>(a, *tail, part, n0, r, lost, col) ? kDone : kExact;          // uniform
+        return grad_tail<RB, NB, WR, WC, kFinite>(a, *tail, part, n0, r, lost, col) ? kDone : kExact;
     } else {
         // Sums that do not pass, 4 bits each (e) of the 4 blocks of a row of blocks.  Slots without a value other than zero have
         // nothing to lose.
@@ -812,12 +853,16 @@ __device__ __forceinline__ uint32_t pair_tile(GemmF32Args a, lds_byte lds, const
         for (int i = 0; i < RB; ++i) {
             float worst = 0.0f, sum = 0.0f;                    // cheaply first: 128 sums a lane
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float x = 4.0f / 3.0f * unit * na[i * 16 + e], g = 4.0f / 3.0f * unit * ga[i * 16 + e];
+            for (int e = 0; e < 4; ++e)
 #pragma unroll
-                for (int j = 0; j < NB; ++j) {
-                    worst = __builtin_fmaxf(worst, __builtin_fmaf(x, gb[j * 16], __builtin_fmaf(g, nb[j * 16], -__builtin_fabsf(acc[i][j][e]))));
-                    sum = __builtin_fmaf(acc[i][j][e], 0.0f, sum);
+                for (int j = 0; j < NB; ++j) sum = __builtin_fmaf(acc[i][j][e], 0.0f, sum);
+            if (any_odd) {                                     // uniform
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float x = 4.0f / 3.0f * unit * na[i * 16 + e], g = 4.0f / 3.0f * unit * ga[i * 16 + e];
+#pragma unroll
+                    for (int j = 0; j < NB; ++j)
+                        worst = __builtin_fmaxf(worst, __builtin_fmaf(x, gb[j * 16], __builtin_fmaf(g, nb[j * 16], -__builtin_fabsf(acc[i][j][e]))));
                 }
             }
             if (!__any(!(worst <= 0.0f && sum == 0.0f))) continue;                    // uniform
@@ -926,13 +971,13 @@ __global__ void __launch_bounds__(64 * WR * WC, 2) gemm_pair_grad_kernel(GemmF32
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const uint64_t c0 = n0 + (wave % WC) * NB * 16 + 4 * (lane & 15);
     auto r = [&](int i, int j, int e) { return a.C[(uint64_t)((wave / WC * RB + i) * 16 + 4 * (lane >> 4) + e) * a.ldc + c0 + j]; };
-    grad_tail<RB, NB, WR, WC, false>(a, t, reinterpret_cast<double*>(smem), n0, r, [](int, int) { return f32x2{}; }, [](int) { return f32x2{}; });
+    grad_tail<RB, NB, WR, WC, kNothing>(a, t, reinterpret_cast<double*>(smem), n0, r, [](int, int) { return f32x2{}; }, [](int) { return f32x2{}; });
 }
 
 template <int RB, int NB, int WR, int WC, bool AKN, bool BKN, bool WEIGHT = false>
 static hipError_t launch_pair(GemmF32Args a, hipStream_t st) {
     constexpr uint64_t TM = 16 * RB * WR, TN = 16 * NB * WC;
-    constexpr uint64_t lds = 2 * 8 * (TM + TN) * 16 + (TM + TN) * 16 + 16;
+    constexpr uint64_t lds = 2 * 8 * (TM + TN) * 16 + (TM + TN) * 16 + 32;
     static_assert(lds <= kLdsBytes, "LDS");
     a.tiles_m = (uint32_t)ceil_div(a.M, TM);
     a.tiles_n = (uint32_t)ceil_div(a.N, TN);
@@ -954,7 +999,7 @@ hipError_t gemm_f32_pair_weighted(const GemmF32Args& a, hipStream_t st) {
 template <int RB, int NB, int WR, int WC>
 static hipError_t launch_pair_grad(GemmF32Args a, const GradTail& t, hipStream_t st) {
     constexpr uint64_t TM = 16 * RB * WR, TN = 16 * NB * WC;
-    constexpr uint64_t lds = 2 * 8 * (TM + TN) * 16 + (TM + TN) * 16 + 16;
+    constexpr uint64_t lds = 2 * 8 * (TM + TN) * 16 + (TM + TN) * 16 + 32;
     a.tiles_m = 1;
     a.tiles_n = (uint32_t)ceil_div(a.N, TN);
     static LdsOptIn opt_in;

@@ -287,6 +287,21 @@ def test_columns_that_miss_the_large_value_of_another(grass, N, k, spike):
     _strict(grass.grass_fim(G) * N, G.T, G.T)
 
 
+@pytest.mark.parametrize("N,k", [(3_000, 1_100), (1_000, 1_100), (300, 1_024), (4_096, 2_080), (5_000, 4_096)])
+@pytest.mark.parametrize("peak", [2.0 ** 4, 2.0 ** 12, 2.0 ** 24])
+def test_rows_times_a_nearly_diagonal_matrix(grass, N, k, peak):
+    """Preconditioning with the inverse of a matrix: the diagonal towers above the rest of its rows, also where it lies in the last
+    group of a ragged k, and some rows are zero there."""
+    G, W = synth.dense_normal(N, k, seed=48, device=_dev()), synth.dense_normal(k, k, seed=49, device=_dev())
+    W = W + W.T
+    W.diagonal().mul_(peak)
+    W[k // 2, k // 2] = 0.0
+    G[::3, ::2] = 0.0
+    got = grass.grass_ifvp(G, W)
+    _strict(got, G, W)
+    assert float((got - G @ W).norm()) <= 4e-6 * float(got.norm())
+
+
 def test_rows_with_one_value(grass):
     """The sums are single products of values that are small beside the largest of their row."""
     te, tr = synth.dense_normal(300, 1_000, seed=46, device=_dev()), torch.zeros(5_000, 1_000, device=_dev())
