@@ -174,7 +174,7 @@ __global__ void __launch_bounds__(256) sm_objective_kernel(const double* corr, u
 
 struct SmLayout {
     uint64_t ld_w, n_pad, pc, parts;
-    size_t off_gtw, off_b, off_c, off_corr, off_sig, off_r, off_part, total;
+    size_t off_gtw, off_b, off_c, off_corr, off_sig, off_part, total;
 };
 static size_t up256(size_t x) { return (x + 255) / 256 * 256; }
 static GemmPlan sm_forward_plan(uint64_t n, uint64_t m, uint64_t p) {
@@ -187,14 +187,14 @@ static SmLayout sm_layout(uint64_t n, uint64_t m, uint64_t p, uint64_t p2 = 0) {
     L.n_pad = (n + 15) / 16 * 16;
     // columns of R at a time: a 128 MiB block stays in the last-level cache for the kernel that reads it next; at least
     // 4,096 columns; whole rounds of the backward product's tiles where a block holds more than one (100 x 1,000 x 335,488
-    // columns are 5.1 rounds and took 570 us, 327,680 are 5 and take 495).  Up to 128 rows need the block only for rows too far
-    // apart for 32-bit offsets, slices of a longer gradient for instance, which the sizes here do not tell.
+    // columns are 5.1 rounds and took 570 us, 327,680 are 5 and take 495).  R lies where the weighted test gradients were, which
+    // the forward product has read by then: never more than their ld_w columns.
     uint64_t pc = (1ull << 25) / m;
     if (pc < 4096) pc = 4096;
     pc = pc / 64 * 64;
     const uint64_t round = gemm_f32_round_columns(gemm_f32_plan(false, true, m, pc, n, 0, false, 1), m);
     if (round > 0 && pc > round) pc = pc / round * round;
-    if (pc > (p + 63) / 64 * 64) pc = (p + 63) / 64 * 64;
+    if (pc > L.ld_w) pc = L.ld_w;
     L.pc = pc;
     L.parts = ceil_div(L.ld_w, 256);
     size_t o = 0;
@@ -203,7 +203,6 @@ static SmLayout sm_layout(uint64_t n, uint64_t m, uint64_t p, uint64_t p2 = 0) {
     L.off_c = o; o += up256((size_t)m * L.n_pad * 4);
     L.off_corr = o; o += up256((size_t)m * 8);
     L.off_sig = o; o += up256((size_t)L.parts * 8);
-    L.off_r = o; o += up256((size_t)m * pc * 4);
     // K-range partial sums of B when its m x n output has too few tiles to fill the chip
     L.off_part = o;
     uint32_t splits = sm_forward_plan(n, m, p).splits;
@@ -251,12 +250,12 @@ static grass_status sm_backward(const SmLayout& L, unsigned char* base, const fl
     // With one row of tiles a workgroup has all rows of its columns of R = C G, and the gradient comes out of its registers: the
     // round trip of R and a kernel behind every block are saved (100 rows, 327,680 columns: 379 + 53 -> 393 us).  As nothing has to
     // stay in a cache all columns are one launch (100 + 1,000 rows of 1,863,690, two steps: 9.83 -> 9.78 ms for six a step).  Tiles
-    // that have to be computed again use the memory of the weighted test gradients.
+    // that have to be computed again use the memory of the weighted test gradients, as R does elsewhere.
     if (m <= 128 && gemm_f32_plan(false, true, m, p, n, ld_max, false, 1).pair) {
         const GemmF32Args a{C, G, reinterpret_cast<float*>(base + L.off_gtw), m, p, n, L.n_pad, ldg, (p + 3) / 4 * 4, 0, 0, 0, 0, 1, 0};
         return gemm_f32_pair_grad(a, GradTail{Gt, ldgt, S, inv_temp, lambda, grad}, hs) == hipSuccess ? GRASS_OK : GRASS_EHIP;
     }
-    float* Rc = reinterpret_cast<float*>(base + L.off_r);
+    float* Rc = reinterpret_cast<float*>(base + L.off_gtw);
     for (uint64_t j0 = 0; j0 < p; j0 += L.pc) {
         const uint64_t pc = j0 + L.pc <= p ? L.pc : p - j0;
         // Rc (m x pc) = C G[:, j0 : j0+pc], a contraction over the n rows of G

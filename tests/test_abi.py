@@ -66,6 +66,18 @@ def test_workspace_queries_validate_on_the_host(lib):
     assert lib.factgrass_linear_workspace_bytes(8, 0, 64, 64, 1024, 1, None, ctypes.byref(out)) == b.GRASS_EINVAL
 
 
+@pytest.mark.parametrize("n, m, p", [(1000, 100, 1_863_690), (200, 100, 300_001), (40, 3, 50)])
+def test_selective_mask_workspace_holds_what_a_step_uses(lib, n, m, p):
+    """The weighted test gradients, at whose place the backward product works later, two matrices of scores, up to 64 partial sums
+    of them where they have few tiles, and a sum per 256 columns and per test row; no block beside these."""
+    from paper_2505_18976_amd import binding as b
+    out = ctypes.c_size_t(0)
+    assert lib.grass_selective_mask_grad_workspace_bytes(n, m, p, ctypes.byref(out)) == b.GRASS_OK
+    gradients, scores, sums = m * ((p + 3) // 4 * 4) * 4, m * ((n + 15) // 16 * 16) * 4, m * 8 + (p + 255) // 256 * 8
+    partial = 64 * m * n * 4 if n * m < 256 * 128 * 256 else 0
+    assert gradients + 2 * scores + sums <= out.value <= gradients + 2 * scores + sums + partial + 6 * 256
+
+
 def test_bad_arguments_are_rejected_before_any_launch(lib):
     """These calls must return on the host: this process has no GPU."""
     from paper_2505_18976_amd import binding as b
