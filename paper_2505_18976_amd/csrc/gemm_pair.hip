@@ -240,9 +240,10 @@ __device__ __attribute__((noinline)) void sum_again(GemmF32Args a, lds_byte lds,
 
 // One workgroup owns a TM x TN tile of C; its WR x WC wavefronts own RB x NB blocks of 16 x 16 each.  K is consumed in groups
 // of 32 through two LDS stages.  A group travels from memory into registers one group before it is split and stored, which
-// is spread over the multiplication of the group before it; a register is loaded again as soon as it is stored.  The barrier
-// of a group sits before its last row of blocks: by then every wavefront has the fragments of this group in registers and its
-// part of the next group in LDS.
+// is spread over the multiplication of the group before it.  A row-major B is loaded again register by register as they are stored,
+// A in one bunch behind its last store: one by one it takes longer (1,024 x 65,536 x 65,536 19.1 -> 20.1 ms, 1,000 x 50,001 x 4,096
+// 0.990 -> 0.998, 65,536 x 4,096 cached 11.59 -> 11.66, mask training 9.64 -> 9.65).  The barrier of a group sits before its last row
+// of blocks: by then every wavefront has the fragments of this group in registers and its part of the next group in LDS.
 // AKN / BKN: the operand is stored K-major (K x M resp. K x N).
 // Returns kDone, kExact (the tile's data do not suit two fp16 pieces; nothing has been stored) or how many sums are left for
 // sum_again.
@@ -743,9 +744,8 @@ __device__ __forceinline__ uint32_t pair_tile(GemmF32Args a, lds_byte lds, const
                         if (q < CA) {
                             stash(km_a, xa, &xw, wa, fsa[q], q, nxt);
                             if constexpr (FULL) {
-                                if (WEIGHT && q == CA - 1) xw = weight_at(gi + 2);
-                                if (!AKN) xa[q] = load_a(q, gi + 2);
-                                else if (q == CA - 1) {
+                                if (q == CA - 1) {
+                                    if (WEIGHT) xw = weight_at(gi + 2);
 #pragma unroll
                                     for (int r = 0; r < CA; ++r) xa[r] = load_a(r, gi + 2);
                                 }
