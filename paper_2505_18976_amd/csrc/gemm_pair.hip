@@ -20,7 +20,7 @@
 // known to be large: it is scaled to 2^14..2^15 at most and the rest of the row as if it was not there.
 //
 // Bound: the power that the matrix cores and the data on the way to them draw.  1,024 x 65,536 x 4,096 takes 1.45 ms = 1,140
-// TFLOP/s of fp16 products at 1.5 GHz, matrix cores 74 % busy; without loads and splitting it would be 1.15 ms, a loop of
+// TFLOP/s of fp16 products at 1.4 to 1.7 GHz, matrix cores 65 to 69 % busy; without loads and splitting it would be 1.15 ms, a loop of
 // matrix instructions alone 0.95.  What counts is therefore work beside the matrix instructions: 16 x 16 x 32 instructions
 // (1,806 TFLOP/s alone on random data; 32 x 32 x 16: 1,611), whole lines of 32 k per load, one exclusive or against bank
 // conflicts (26 % of the cycles before), no arithmetic on addresses, five vector operations per pair of values.
